@@ -146,9 +146,9 @@ int pga_last_hip_error(void);     /* hipError_t of the last PGA_ERR_HIP on this 
  * C_hi / C_lo (nullable, both or neither): also write the BF16 split of C
  * (as pga_split). Requires 1 <= N <= PGA_N_MAX, T >= 2. */
 /* Workspace: 2N doubles (row means, sums of squares) and the partial Gram
- * tiles of the FP64 MFMA Gram (the t range of each 64 x 64 tile of the upper
- * triangle is split into up to 8 slices, added in slice order). 0 for N < 1
- * or N > PGA_N_MAX. */
+ * tiles of the FP64 MFMA Gram (the t range of each 128 x 128 tile of the upper
+ * triangle is split into up to 16 slices, added in slice order; small windows
+ * take one launch that uses neither). 0 for N < 1 or N > PGA_N_MAX. */
 size_t pga_correlate_ws_bytes(int32_t N);
 int pga_correlate(const double *R, int32_t N, int32_t T, int64_t ld_r, double *C,
                   uint16_t *C_hi, uint16_t *C_lo, int32_t *status, void *ws, size_t ws_bytes,
@@ -179,8 +179,9 @@ int pga_split(const double *C, int32_t N, uint16_t *C_hi, uint16_t *C_lo, void *
  * x_it scaled by sqrt((1 - lambda) lambda^(T-1-t)) (FP64 throughout).
  * Errors: PGA_ERR_ARG (null pointer, N < 1, T < 1, ld_r < T, lambda outside
  * [0, 1), unknown flag, one of hi/lo), PGA_ERR_UNSUPPORTED (N > PGA_N_MAX),
- * PGA_ERR_WORKSPACE (pga_ewma_ws_bytes(N, T): the weighted returns, N x T
- * doubles, and the partial Gram tiles as pga_correlate). Async. */
+ * PGA_ERR_WORKSPACE (pga_ewma_ws_bytes(N, T): the T market means and weight
+ * roots, the N old variances, and the partial Gram tiles as pga_correlate).
+ * Async. */
 size_t pga_ewma_ws_bytes(int32_t N, int32_t T);
 int pga_ewma(const double *R, int32_t N, int32_t T, int32_t ld_r, double lambda, int32_t flags,
              double *S, double *C, uint16_t *C_hi, uint16_t *C_lo, int32_t *status, void *ws,

@@ -405,12 +405,7 @@ int pga_correlate(const double *R, int32_t N, int32_t T, int64_t ld_r, double *C
     hipStream_t s = (hipStream_t)stream;
     double *mu = (double *)ws, *ss = mu + N;
     double *part = (double *)((char *)ws + align_up(sizeof(double) * 2 * (size_t)N, 256));
-    HIP_TRY(timed(5, s, [&] {
-        hipError_t e = launch_row_stats(R, N, T, ld_r, mu, ss, status, s);
-        if (e != hipSuccess) return e;
-        return launch_corr(R, N, T, ld_r, mu, ss, C, part, s);
-    }));
-    if (C_hi) HIP_TRY(timed(6, s, [&] { return launch_split(C, N, C_hi, C_lo, s); }));
+    HIP_TRY(timed(5, s, [&] { return launch_corr(R, N, T, ld_r, mu, ss, C, C_hi, C_lo, part, status, s); }));
     return PGA_OK;
 }
 
@@ -425,7 +420,7 @@ int pga_split(const double *C, int32_t N, uint16_t *C_hi, uint16_t *C_lo, void *
 // ---- online EWMA correlation -------------------------------------------------------------
 size_t pga_ewma_ws_bytes(int32_t N, int32_t T) {
     if (N < 1 || T < 1 || N > PGA_N_MAX) return 0;
-    return align_up(sizeof(double) * (size_t)N * (size_t)T, 256) + sizeof(double) * gram_ws_doubles(N);
+    return align_up(sizeof(double) * ewma_ws_doubles(N, T), 256) + sizeof(double) * gram_ws_doubles(N);
 }
 
 int pga_ewma(const double *R, int32_t N, int32_t T, int32_t ld_r, double lambda, int32_t flags, double *S,
@@ -438,12 +433,11 @@ int pga_ewma(const double *R, int32_t N, int32_t T, int32_t ld_r, double lambda,
     if (N > PGA_N_MAX) return PGA_ERR_UNSUPPORTED;
     if (!ws || ws_bytes < pga_ewma_ws_bytes(N, T)) return PGA_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
-    double *part = (double *)((char *)ws + align_up(sizeof(double) * (size_t)N * (size_t)T, 256));
+    double *part = (double *)((char *)ws + align_up(sizeof(double) * ewma_ws_doubles(N, T), 256));
     HIP_TRY(timed(9, s, [&] {
         return launch_ewma(R, N, T, ld_r, lambda, (flags & PGA_EWMA_RESET) ? 1 : 0,
-                           (flags & PGA_EWMA_MARKET) ? 1 : 0, S, C, (double *)ws, part, status, s);
+                           (flags & PGA_EWMA_MARKET) ? 1 : 0, S, C, C_hi, C_lo, (double *)ws, part, status, s);
     }));
-    if (C_hi) HIP_TRY(timed(6, s, [&] { return launch_split(C, N, C_hi, C_lo, s); }));
     return PGA_OK;
 }
 

@@ -293,14 +293,13 @@ __device__ __forceinline__ void route_append(const Tables &t, const InstDesc &d,
 }
 
 // ---- launchers (defined in the kernel translation units) ---------------------
-hipError_t launch_row_stats(const double *R, int N, int T, int64_t ld, double *mu, double *ss,
-                            int32_t *status, hipStream_t s);
-hipError_t launch_corr(const double *R, int N, int T, int64_t ld, const double *mu, const double *ss,
-                       double *C, double *part, hipStream_t s);
+hipError_t launch_corr(const double *R, int N, int T, int64_t ld, double *mu, double *ss, double *C, uint16_t *hi,
+                       uint16_t *lo, double *part, int32_t *status, hipStream_t s);
 size_t gram_ws_doubles(int N);      // partial Gram tiles of the FP64 MFMA Gram (correlation, EWMA)
 hipError_t launch_split(const double *C, int N, uint16_t *hi, uint16_t *lo, hipStream_t s);
+size_t ewma_ws_doubles(int N, int T);   // market means, weight roots and the old diagonal
 hipError_t launch_ewma(const double *R, int N, int T, int64_t ld, double lam, int reset, int market, double *S,
-                       double *C, double *X, double *part, int32_t *status, hipStream_t s);
+                       double *C, uint16_t *hi, uint16_t *lo, double *ws, double *part, int32_t *status, hipStream_t s);
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix2, hipStream_t s);
 hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, const Variant &v, hipStream_t s);
