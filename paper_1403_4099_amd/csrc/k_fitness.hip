@@ -23,13 +23,13 @@ namespace pga {
 // tables travel as kernel arguments, so no host buffer has to outlive the call.
 struct DescBlob {
     InstDesc d;
-    int32_t prefix[4];   // {0, tiles}, {0, P}; the route list counters follow, zeroed
+    int32_t prefix[6];   // {0, tiles}, {0, P}, {0, evaluation blocks}; the list counters follow, zeroed
 };
 
 __global__ void k_write_desc(DescBlob b, InstDesc *dst, int32_t *prefix) {
     if (threadIdx.x == 0) *dst = b.d;
-    if (threadIdx.x < 4) prefix[threadIdx.x] = b.prefix[threadIdx.x];
-    for (int i = threadIdx.x; i < kListCounters; i += blockDim.x) prefix[4 + i] = 0;
+    if (threadIdx.x < 6) prefix[threadIdx.x] = b.prefix[threadIdx.x];
+    for (int i = threadIdx.x; i < kListCounters; i += blockDim.x) prefix[6 + i] = 0;
 }
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix, hipStream_t s) {
@@ -39,6 +39,8 @@ hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, in
     b.prefix[1] = tiles;
     b.prefix[2] = 0;
     b.prefix[3] = d.P;
+    b.prefix[4] = 0;
+    b.prefix[5] = eval_blocks(d.N, d.P);
     hipLaunchKernelGGL(k_write_desc, dim3(1), dim3(256), 0, s, b, dst, prefix);
     return hipGetLastError();
 }
@@ -561,9 +563,9 @@ __global__ __launch_bounds__(kFinThreads) void k_finish_listed(Tables t, int max
                                                                int32_t *status) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int slice = (int)blockIdx.x % slices, per = (int)gridDim.x / slices;
-    const int n = __builtin_amdgcn_readfirstlane(gld(list_count(t, parity, kListDense, slice)));
+    const int n = __builtin_amdgcn_readfirstlane(gld(list_count(t, parity, slice)));
     for (int at = (int)blockIdx.x / slices; at < n; at += per) {
-        const int32_t *e = list_entry(t, kListDense, slice, cap, at);
+        const int32_t *e = list_entry(t, slice, cap, at);
         const int p = __builtin_amdgcn_readfirstlane(gld(e));
         const int k = __builtin_amdgcn_readfirstlane(gld(e + 1));
         finish_one(t, k, p, max_n, parity, status, smem);
@@ -591,433 +593,63 @@ hipError_t launch_finish(Tables t, int total_inds, int max_n, int parity, int li
 // ---------------------------------------------------------------------------
 // Cluster-pair fitness (exact FP64 route). c_s of Eq. 6 only involves the pairs
 // inside cluster s, so an individual with few such pairs is evaluated from
-// them directly instead of by the O(N^2) pair-sum: one 256-thread workgroup
-// per individual
-//   1. labels and the diagonal of C (a contiguous copy; not read when every
-//      C_jj is 1) into registers, the labels also into LDS (invalid labels:
-//      fitness -inf, as the finish does);
-//   2. n_s by LDS atomics; pairs = sum_s n_s (n_s - 1) / 2 and max n_s;
-//   3. pairs above the limit: route[p] = 1 (the pair-sum and finish kernels
-//      evaluate it) and stop;
-//   4. members grouped by cluster (counting sort on the exclusive prefix of
-//      n_s); the same scan gives PP, the exclusive prefix of the pair counts
-//      n_s (n_s - 1) / 2, which numbers the pairs: pair q belongs to the
-//      cluster s with PP[s] <= q < PP[s+1], and r = q - PP[s] = b (b-1)/2 + a
-//      (a < b) joins its members a and b;
-//   5. c_s = sum_{j in s} C_jj + 2 sum_{pairs} C_ij (upper triangle, as the
-//      FP64 pair-sum reads it) accumulated in 64-bit fixed point: with
+// them directly instead of by the O(N^2) pair-sum, by a group of GL lanes: 16
+// (N <= 32), 32 (N <= 64), a wave (N <= 512) or a workgroup (N <= 2048), so that
+// a 256-thread workgroup holds 16, 8, 4 or 1 individuals of one instance:
+//   1. labels into registers; n_s by LDS atomics, whose old values add up to
+//      the pair count sum_s n_s (n_s - 1) / 2 and give max n_s; a second atomic
+//      exchanges the label's last stock for this one, which chains the stocks
+//      of a cluster: prev[j] is the stock of j's cluster before it (N: none), so
+//      the pairs of a cluster are j with every stock on j's chain, once each;
+//   2. pairs above the limit: route[p] = 1 (the pair-sum and finish evaluate it,
+//      through the dense list in large launches) and stop; the pair count of an
+//      individual with N <= 64 is within the limit whatever its labels;
+//   3. the labels with n_s > 1 compacted in ascending order (their n_s, and
+//      csum, which starts with the sum of the diagonal), then the stocks with
+//      a predecessor as items, so that the lanes of step 4 are busy whatever the
+//      labels;
+//   4. per item, its chain: the entries C_ij (upper triangle, as the FP64 pair-sum
+//      reads it), four at a time in flight, summed in 64-bit fixed point: with
 //      |C| <= 1 every partial sum is bounded by max n_s^2, and the scale 2^sc
-//      keeps max n_s^2 2^sc <= 2^61, so the integer sums are exact and the
-//      result does not depend on the order of the atomics;
-//   6. an entry with |C| > 1 or not finite sends the individual to the dense
-//      route (step 3's flag), which treats it exactly as before; otherwise
-//      route[p] = 0 and the log terms follow as in the finish.
+//      keeps max n_s^2 2^sc <= 2^61, so the integer sums are exact and no result
+//      depends on the order of the chain or of the atomics;
+//   5. an entry with |C| > 1 or not finite sends the individual to the dense
+//      route (step 2's flag), which treats it exactly as without this route; for
+//      N <= 64 the wave evaluates it so itself (dense_small), and the launches of
+//      a batch of small instances need no pair-sum and no finish. Otherwise the
+//      log terms follow, added in the finish's order, so an individual has the
+//      same bits whatever GL evaluates it.
+// A chain needs no sort and no scan over the labels: the counting sort, the pair
+// prefix and the search and square root per pair run that it replaces were half of
+// the instructions at N = 272. What bounds it: vector instructions (log terms,
+// fixed point) and the latency of LDS and C reads, about evenly.
 constexpr int kSparseMaxN = 2048;                  // larger instances always take the dense route
-constexpr int kSparseCache = kSparseMaxN / kFinThreads;   // stocks per thread, all in registers
+constexpr int kSmallMaxN = kRouteAllPairsMaxN;     // evaluated here even when a C entry is out of range
 
 __host__ __device__ constexpr size_t pad16(size_t b) { return (b + 15) / 16 * 16; }
-__host__ __device__ constexpr size_t sparse_members_bytes(int n) {
-    const size_t m = pad16(2 * (size_t)n), l = finish_lst_bytes(n);
-    return m > l ? m : l;
+__host__ __device__ constexpr int eval_lanes(int N) { return N <= 32 ? 16 : N <= 64 ? 32 : N <= 512 ? 64 : 256; }
+// LDS of one individual: n_s, then the items, uint32[n] | a cluster's last stock, then its
+// list index, uint32[n], then csum int64[n / 2 + 1] | prev uint16[n + 1] | list uint32[n / 2 + 1].
+// 12 n bytes: at N = 512 six workgroups per CU.
+__host__ __device__ constexpr size_t eval_bytes(int n) {
+    return pad16(4 * (size_t)n) + pad16(8 * ((size_t)n / 2 + 1)) + pad16(2 * ((size_t)n + 1)) +
+           pad16(4 * ((size_t)n / 2 + 1));
 }
-// LDS: csum int64[n] | cnt int32[n] | begin int32[n + 1] | PP int32[n + 1] | members,
-// then the finish lists | kFinWaves x 2 doubles | 16 int32.
-// 22.7 KB at N = 1024 (seven workgroups per CU).
-__host__ __device__ constexpr size_t sparse_lds_bytes(int n) {
-    return pad16(8 * (size_t)n) + pad16(4 * (size_t)n) + 2 * pad16(4 * ((size_t)n + 1)) + sparse_members_bytes(n) +
-           2 * kFinWaves * sizeof(double) + 16 * sizeof(int);
+constexpr uint32_t kNoCluster = 0xFFFFu;           // list index of a label with n_s <= 1
+constexpr size_t kSmallScratch = 64 * (8 + 4 + 4);  // dense_small, per wave
+__host__ __device__ constexpr size_t eval_lds_bytes(int N) {
+    const int g = 256 / eval_lanes(N);
+    return (size_t)g * eval_bytes(N) + (N <= kSmallMaxN ? 4 * kSmallScratch : 0) + (g == 1 ? 256 : 0);
 }
-constexpr bool sparse_layout_ok() {
-    for (int n = 1; n <= kSparseMaxN; ++n) {
-        if (sparse_members_bytes(n) % 16) return false;
-        if (sparse_lds_bytes(n) > (size_t)kMaxLdsBytes) return false;
-    }
+constexpr bool eval_layout_ok() {
+    for (int n = 1; n <= kSparseMaxN; ++n)
+        if (eval_bytes(n) % 16 || eval_lds_bytes(n) > (size_t)kMaxLdsBytes) return false;
     return true;
 }
-static_assert(sparse_layout_ok(), "cluster-pair LDS layout: aligned regions within the LDS limit");
+static_assert(eval_layout_ok(), "cluster-pair LDS layout: aligned regions within the LDS limit");
 
-// Exclusive prefixes of n_s (begin) and of n_s (n_s - 1) / 2 (pp) over
-// [0, n), as block_exscan; returns the number of pairs and sets nmax to the
-// largest n_s; wtot: 12 ints.
-__device__ __forceinline__ int block_exscan_cnt_pairs(const int *cnt, int *begin, int *pp, int n, int *wtot,
-                                                      int &nmax) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (n + kFinThreads - 1) / kFinThreads;
-    const int b0 = min(n, tid * per), b1 = min(n, b0 + per);
-    int own = 0, ownp = 0, mx = 0;
-    for (int x = b0; x < b1; ++x) {
-        const int c = cnt[x];
-        own += c;
-        ownp += c * (c - 1) / 2;
-        mx = max(mx, c);
-    }
-    int inc = own, incp = ownp;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o, 64), yp = __shfl_up(incp, o, 64);
-        if (lane >= o) {
-            inc += y;
-            incp += yp;
-        }
-        mx = max(mx, __shfl_xor(mx, o, 64));
-    }
-    if (lane == 63) {
-        wtot[wave] = inc;
-        wtot[kFinWaves + wave] = incp;
-        wtot[2 * kFinWaves + wave] = mx;
-    }
-    __syncthreads();
-    int run = inc - own, runp = incp - ownp, totalp = 0;
-    nmax = 0;
-#pragma unroll
-    for (int w = 0; w < kFinWaves; ++w) {
-        if (w < wave) {
-            run += wtot[w];
-            runp += wtot[kFinWaves + w];
-        }
-        totalp += wtot[kFinWaves + w];
-        nmax = max(nmax, wtot[2 * kFinWaves + w]);
-    }
-    for (int x = b0; x < b1; ++x) {
-        const int c = cnt[x];
-        begin[x] = run;
-        pp[x] = runp;
-        run += c;
-        runp += c * (c - 1) / 2;
-    }
-    __syncthreads();
-    return totalp;
-}
-
-// Exclusive prefix sum of a[0 .. n) into out (may alias a); thread t scans a
-// contiguous run of ceil(n / 256). Returns the total; ends with a barrier.
-__device__ __forceinline__ int block_exscan(const int *a, int *out, int n, int *wtot) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = (n + kFinThreads - 1) / kFinThreads;
-    const int b0 = min(n, tid * per), b1 = min(n, b0 + per);
-    int own = 0;
-    for (int x = b0; x < b1; ++x) own += a[x];
-    int inc = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) wtot[wave] = inc;
-    __syncthreads();
-    int run = inc - own, total = 0;
-#pragma unroll
-    for (int w = 0; w < kFinWaves; ++w) {
-        if (w < wave) run += wtot[w];
-        total += wtot[w];
-    }
-    for (int x = b0; x < b1; ++x) {
-        const int v = a[x];
-        out[x] = run;
-        run += v;
-    }
-    __syncthreads();
-    return total;
-}
-
-__device__ __forceinline__ unsigned long long fixed_pt(double c, int sc) {
-    return (unsigned long long)llrint(ldexp(c, sc));
-}
-
-// Route of every individual, one wave each (four per workgroup): n_s by LDS
-// atomics, whose return values add up to the pair count sum_s n_s (n_s - 1) / 2
-// exactly. An individual at or under the limit, or with a label outside
-// [0, N), goes to the sparse list (route 0), the others to the dense list
-// (route 1). Workgroup w appends to slice w mod slices of each list with
-// one atomic per list; the order within a slice depends on timing, the
-// content does not. Workgroup 0 also empties the other parity's lists.
-__global__ __launch_bounds__(256) void k_route(Tables t, int lds_n, int parity, double frac, int slices, int cap) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int kind[4], ent[4][2];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < 2 * kListSlices; i += 256) gst(t.sq + (2 * (parity ^ 1)) * kListSlices + i, 0);
-    const int g = __builtin_amdgcn_readfirstlane(4 * (int)blockIdx.x + wave);
-    int mine = -1, k = 0, p = 0;                     // mine: the list this wave's individual joins
-    if (g < t.inds[t.n_inst]) {                      // the grid may exceed the total (capacity-sized graph)
-        k = find_inst(t.inds, t.n_inst, g);
-        const InstDesc &d = t.desc[k];
-        const int N = d.N;
-        p = g - t.inds[k];
-        if (inst_stopped(d)) {
-        } else if (N > lds_n) {                      // lds_n <= kSparseMaxN
-            if (lane == 0) gst(d.route + p, 1);
-            mine = kListDense;
-        } else if (N <= kRouteAllPairsMaxN) {        // within the limit whatever its labels
-            if (lane == 0) gst(d.route + p, 0);
-            mine = kListSparse;
-        } else {
-            int *cnt = (int *)(smem + (size_t)wave * pad16(4 * (size_t)lds_n));
-            for (int s = lane; s < N; s += 64) cnt[s] = 0;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const int32_t *__restrict__ lab = d.pop[parity] + (size_t)p * N;
-            int pairs = 0, bad = 0;
-            for (int j0 = lane; j0 < N; j0 += 4 * 64) {     // four labels per lane in flight
-                int l[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) l[u] = j0 + 64 * u < N ? gld(lab + j0 + 64 * u) : 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    if (j0 + 64 * u >= N) break;
-                    if (l[u] < 0 || l[u] >= N) bad = 1;
-                    else pairs += atomicAdd(&cnt[l[u]], 1);
-                }
-            }
-#pragma unroll
-            for (int m = 32; m > 0; m >>= 1) pairs += __shfl_xor(pairs, m, 64);
-            const bool sparse = __any(bad) || (double)pairs <= route_limit(N, frac);
-            if (lane == 0) gst(d.route + p, sparse ? 0 : 1);
-            mine = sparse ? kListSparse : kListDense;
-        }
-    }
-    if (lane == 0) {
-        kind[wave] = mine;
-        ent[wave][0] = p;
-        ent[wave][1] = k;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {                           // thread L appends this workgroup's individuals of list L
-        const int L = threadIdx.x;
-        int n = 0;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) n += kind[w] == L ? 1 : 0;
-        if (n > 0) {
-            const int slice = (int)blockIdx.x % slices;
-            int at = atomicAdd(list_count(t, parity, L, slice), n);
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-                if (kind[w] == L) {
-                    int32_t *e = list_entry(t, L, slice, cap, at++);
-                    gst(e, ent[w][0]);
-                    gst(e + 1, ent[w][1]);
-                }
-        }
-    }
-}
-
-// An individual the cluster-pair kernel hands back to the pair-sum route joins
-// the dense list (one thread; the slice it came from has room for it there).
-// slice < 0: no lists in use (the finish reads every individual's route).
-__device__ __forceinline__ void list_dense(const Tables &t, int parity, int slice, int cap, int p, int k) {
-    if (slice < 0) return;
-    int32_t *e = list_entry(t, kListDense, slice, cap, atomicAdd(list_count(t, parity, kListDense, slice), 1));
-    gst(e, p);
-    gst(e + 1, k);
-}
-
-__host__ __device__ constexpr size_t route_lds_bytes(int n) { return 4 * pad16(4 * (size_t)n); }
-static_assert(route_lds_bytes(kSparseMaxN) <= (size_t)kMaxLdsBytes, "route LDS within the limit");
-
-// The cluster-pair evaluation of individual p of instance k (all threads of the
-// workgroup), taken from slice `slice` of the sparse list. An individual it
-// hands to the pair-sum route (route 1) joins the dense list.
-__device__ void sparse_one(const Tables &t, int k, int p, int slice, int cap, int lds_n, int parity, double frac,
-                           int32_t *status, unsigned char *smem) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
-    const InstDesc &d = t.desc[k];
-    if (inst_stopped(d)) return;                     // uniform over the workgroup
-    const int N = d.N;
-    if (N > lds_n) {                                 // lds_n <= kSparseMaxN
-        if (tid == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
-        }
-        return;
-    }
-    const size_t n = (size_t)lds_n;
-    unsigned char *b = smem;
-    long long *csum = (long long *)b;   b += pad16(8 * n);
-    int *cnt = (int *)b;                b += pad16(4 * n);
-    int *begin = (int *)b;              b += pad16(4 * (n + 1));
-    int *PP = (int *)b;                 b += pad16(4 * (n + 1));
-    uint16_t *members = (uint16_t *)b;  b += sparse_members_bytes(lds_n);
-    uint16_t *lst = members;            // the finish lists replace members after the pairs
-    double *red = (double *)b;          b += 2 * kFinWaves * sizeof(double);
-    int *ired = (int *)b;               // [0, 4) flags, [4, 16) scan totals, then [12, 16) list lengths
-
-    const int32_t *__restrict__ lab = d.pop[parity] + (size_t)p * N;
-    const double *__restrict__ C = d.C;
-
-    // Stocks j = tid + 256 u, u < ucache (uniform), all of them (N <= 2048).
-    const int ucache = (N + kFinThreads - 1) / kFinThreads;
-    const bool ones = gld(d.diag + N) == 1.0;        // every C_jj is 1 (uniform)
-    int lr[kSparseCache];
-    double dg[kSparseCache];
-#pragma unroll
-    for (int u = 0; u < kSparseCache; ++u) {
-        if (u >= ucache) break;
-        const int j = tid + kFinThreads * u;
-        lr[u] = j < N ? gld(lab + j) : 0;
-        dg[u] = (!ones && j < N) ? gld(d.diag + j) : 1.0;
-    }
-    int bad = 0;
-#pragma unroll
-    for (int u = 0; u < kSparseCache; ++u) {
-        if (u >= ucache) break;
-        const int j = tid + kFinThreads * u;
-        if (j < N) {
-            if (lr[u] < 0 || lr[u] >= N) bad = 1;
-            cnt[j] = 0;
-            csum[j] = 0;
-        }
-    }
-    const int wbad = __any(bad) ? 1 : 0;             // all lanes vote, lane 0 records
-    if (lane == 0) ired[wave] = wbad;
-    __syncthreads();
-    if (ired[0] | ired[1] | ired[2] | ired[3]) {     // as the finish: labels outside [0, N)
-        if (tid == 0) {
-            gst(d.route + p, 0);
-            d.fitness[p] = -INFINITY;
-            if (status) {
-                atomicAdd(&status[PGA_ST_LABEL], 1);
-                atomicAdd(&status[PGA_ST_NONFINITE], 1);
-            }
-        }
-        if (d.n_s_out)
-            for (int s = tid; s < N; s += kFinThreads) d.n_s_out[(size_t)p * N + s] = 0;
-        if (d.c_s_out)
-            for (int s = tid; s < N; s += kFinThreads) d.c_s_out[(size_t)p * N + s] = 0.0;
-        return;
-    }
-#pragma unroll
-    for (int u = 0; u < kSparseCache; ++u) {
-        if (u >= ucache) break;
-        if (tid + kFinThreads * u < N) atomicAdd(&cnt[lr[u]], 1);
-    }
-    __syncthreads();
-
-    // begin[s]: first position of cluster s; PP[s]: pairs of the clusters below s
-    int nmax;
-    const int T = block_exscan_cnt_pairs(cnt, begin, PP, N, ired + 4, nmax);   // T == pairs
-    if ((double)T > route_limit(N, frac)) {
-        if (tid == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
-        }
-        return;                                      // uniform
-    }
-    int e;
-    frexp((double)nmax * (double)nmax, &e);          // max n_s^2 < 2^e
-    const int sc = 61 - e;
-    if (tid == 0) PP[N] = T;
-    int badc = 0;
-#pragma unroll
-    for (int u = 0; u < kSparseCache; ++u) {
-        if (u >= ucache) break;
-        const int j = tid + kFinThreads * u;
-        if (j < N) {
-            members[atomicAdd(&begin[lr[u]], 1)] = (uint16_t)j;
-            if (!ones) {
-                if (!(fabs(dg[u]) <= 1.0)) badc = 1;
-                else atomicAdd((unsigned long long *)&csum[lr[u]], fixed_pt(dg[u], sc));
-            }
-        }
-    }
-    if (ones)                                        // sum of n_s diagonal ones, exact
-        for (int s = tid; s < N; s += kFinThreads) csum[s] = (long long)cnt[s] << sc;
-    __syncthreads();                                 // begin[s] is now the end of cluster s
-
-    // Each thread takes kq consecutive pairs per round (one search, then a forward
-    // walk) with their loads issued together; kq = ceil(T / 256), at most kQ, so
-    // every thread has work. Consecutive pairs mostly share a cluster, so the
-    // terms are summed in a register while the label stays the same and added to
-    // csum once per run (fewer atomics on one LDS address).
-    constexpr int kQ = 8;
-    const int kq = min(kQ, max(1, (T + kFinThreads - 1) / kFinThreads));   // uniform
-    for (int q0 = tid * kq; q0 < T; q0 += kq * kFinThreads) {
-        int cs = 0, hi = N;                          // PP[cs] <= q0 < PP[hi]
-        while (hi - cs > 1) {
-            const int mid = (cs + hi) >> 1;
-            if (PP[mid] <= q0) cs = mid;
-            else hi = mid;
-        }
-        const int r = q0 - PP[cs];                   // = bq (bq - 1) / 2 + aq, aq < bq
-        int bq = (int)((1.0 + sqrt(1.0 + 8.0 * (double)r)) * 0.5);
-        while (bq * (bq - 1) / 2 > r) --bq;
-        while ((bq + 1) * bq / 2 <= r) ++bq;
-        int aq = r - bq * (bq - 1) / 2;
-        int st = begin[cs] - cnt[cs];                // first position of cluster cs
-        int pend = PP[cs + 1];                       // first pair of the clusters above cs
-        double c[kQ];
-        int l[kQ];
-#pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            const int q = q0 + u;
-            l[u] = -1;
-            c[u] = 0.0;
-            if (u < kq && q < T) {
-                while (q >= pend) {                  // next cluster with pairs (PP[N] = T > q)
-                    ++cs;
-                    pend = PP[cs + 1];
-                    st = begin[cs] - cnt[cs];
-                    aq = 0;
-                    bq = 1;
-                }
-                const int j = members[st + bq], i = members[st + aq];
-                c[u] = gld(C + (size_t)min(i, j) * N + max(i, j));
-                l[u] = cs;
-                if (++aq == bq) {
-                    ++bq;
-                    aq = 0;
-                }
-            }
-        }
-        long long run = 0;
-        int cur = -1;
-#pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            if (l[u] < 0) continue;
-            if (!(fabs(c[u]) <= 1.0)) {
-                badc = 1;
-                continue;
-            }
-            if (l[u] != cur) {
-                if (cur >= 0) atomicAdd((unsigned long long *)&csum[cur], (unsigned long long)run);
-                cur = l[u];
-                run = 0;
-            }
-            run += fixed_pt(2.0 * c[u], sc);
-        }
-        if (cur >= 0) atomicAdd((unsigned long long *)&csum[cur], (unsigned long long)run);
-    }
-    const int wbadc = __any(badc) ? 1 : 0;
-    if (lane == 0) ired[wave] = wbadc;
-    __syncthreads();
-    if (ired[0] | ired[1] | ired[2] | ired[3]) {
-        if (tid == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
-        }
-        return;
-    }
-    if (tid == 0) gst(d.route + p, 0);
-    finish_terms(d, p, N, cnt, csum, sc, lst, finish_quarter(lds_n), red, ired + 12, status);
-}
-
-// The same evaluation by one wave (a 64-thread workgroup) for N <= 512: at the
-// batched form's sizes a whole workgroup per individual repeats its scans,
-// reductions and barriers in every wave and holds eight individuals per
-// compute unit. The steps and their integer results are those of sparse_one;
-// the log terms are added in the workgroup kernel's order (entry m of the
-// label list to virtual thread m mod 256, each virtual wave's lanes by the
-// same butterfly, the four virtual waves in order), so the fitness has the
-// same bits whichever of the two kernels evaluates it.
-// LDS (18 N bytes): csum int64 [N] | n_s, then the cluster starts, then their
-// ends, int32 [N + 1] | PP int32 [N + 1] | members uint16 [N], later the list
-// of labels with n_s > 1.
-constexpr int kSparseWaveMaxN = 512;
-constexpr int kSwCache = kSparseWaveMaxN / 64;     // stocks per lane, all in registers
-
-__host__ __device__ constexpr size_t sparse_wave_lds_bytes(int n) {
-    return pad16(8 * (size_t)n) + 2 * pad16(4 * ((size_t)n + 1)) + pad16(2 * (size_t)n);
-}
-static_assert(sparse_wave_lds_bytes(kSparseWaveMaxN) <= (size_t)kMaxLdsBytes, "wave cluster-pair LDS");
+int eval_blocks(int N, int P) { return N > kSparseMaxN ? (P + 255) / 256 : ceil_div(P, 256 / eval_lanes(N)); }
+size_t eval_lds(int N) { return N > kSparseMaxN ? 0 : eval_lds_bytes(N); }
 
 // Orders the LDS accesses of the wave's lanes (one wave: no barrier needed).
 __device__ __forceinline__ void wave_lds_sync() {
@@ -1025,57 +657,261 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-__device__ void sparse_one_wave(const Tables &t, int k, int p, int slice, int cap, int lds_n, int parity,
-                                double frac, int32_t *status, unsigned char *smem) {
-    const int lane = threadIdx.x;
-    const InstDesc &d = t.desc[k];
-    if (inst_stopped(d)) return;
-    const int N = d.N;
-    if (N > lds_n) {                                 // lds_n <= kSparseWaveMaxN
-        if (lane == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
+// Cross-lane steps without LDS: rotations within rows of 16 lanes (DPP), and the swaps of
+// neighbouring rows and of the wave's halves.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+constexpr int kRor8 = 0x128, kRor4 = 0x124, kRor2 = 0x122, kRor1 = 0x121;   // row_ror:n
+constexpr int kQuad2 = 0x4E, kQuad1 = 0xB1;                                  // quad_perm [2,3,0,1], [1,0,3,2]
+
+template <int GL, class Op>                       // over GL <= 64 lanes; op commutative and associative
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
+    v = op(v, dpp<kRor8>(v));
+    v = op(v, dpp<kRor4>(v));
+    v = op(v, dpp<kRor2>(v));
+    v = op(v, dpp<kRor1>(v));
+    if constexpr (GL >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = op(r[0], r[1]);
+    }
+    if constexpr (GL >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = op(r[0], r[1]);
+    }
+    return v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b);
+    return v + __builtin_bit_cast(double, o);
+}
+// The butterfly wave_sum (lane l with l ^ 32, 16, 8, 4, 2, 1), the same bits: a step's sum is commutative,
+// and once the values repeat with period 8 (4) in a row, the row's rotation by 4 (2) pairs the same
+// values as the exchange. GL = 32 and 16: the wave_sum of the group's values followed by zeros.
+template <int GL>
+__device__ __forceinline__ double group_sum(double v) {
+    auto halves = [](double x, auto swap) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const auto l = swap((uint32_t)b), h = swap((uint32_t)(b >> 32));
+        return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+               __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+    };
+    if constexpr (GL >= 64)
+        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    if constexpr (GL >= 32)
+        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = dpp_add<kRor8>(v);
+    v = dpp_add<kRor4>(v);
+    v = dpp_add<kQuad2>(v);
+    return dpp_add<kQuad1>(v);
+}
+
+__device__ __forceinline__ unsigned long long fixed_pt(double c, int sc) {
+    return (unsigned long long)llrint(ldexp(c, sc));
+}
+
+// An individual that goes to the pair-sum route joins the dense list (one
+// thread). listed = 0: no lists in use (the finish reads every individual's route).
+__device__ __forceinline__ void to_dense(const Tables &t, const InstDesc &d, int k, int p, int parity, int listed,
+                                         int slices, int cap) {
+    gst(d.route + p, 1);
+    if (!listed) return;
+    const int slice = ((t.inds[k] + p) >> 2) % slices;
+    int32_t *e = list_entry(t, slice, cap, atomicAdd(list_count(t, parity, slice), 1));
+    gst(e, p);
+    gst(e + 1, k);
+}
+
+// The log terms of Eq. 8 of one cluster of n stocks; false if c is outside (0, n^2).
+__device__ __forceinline__ bool cluster_term(int n, long long csum, int sc, double &term) {
+    const double nd = (double)n;
+    const double c = ldexp((double)csum, -sc);
+    const double n2 = nd * nd;
+    if (!(c > 0.0 && c < n2)) return false;
+    term = log(nd / c) + (nd - 1.0) * log((n2 - nd) / (n2 - c));
+    return true;
+}
+
+__device__ __forceinline__ void store_fitness(const InstDesc &d, int p, double Ltot, int nbad, int32_t *status) {
+    if (nbad > 0) {
+        d.fitness[p] = -INFINITY;
+        if (status) {
+            atomicAdd(&status[PGA_ST_DOMAIN], nbad);
+            atomicAdd(&status[PGA_ST_NONFINITE], 1);
         }
+    } else {
+        d.fitness[p] = 0.5 * Ltot;
+    }
+}
+
+// Individual p (N <= 64, valid labels, all 64 lanes of a wave) as the pair-sum and the finish evaluate
+// it: lane j holds stock j. scratch: kSmallScratch bytes of LDS.
+typedef __bf16 fit_bf16x8 __attribute__((ext_vector_type(8)));
+typedef float fit_floatx4 __attribute__((ext_vector_type(4)));
+__device__ __attribute__((noinline)) void dense_small(const InstDesc &d, int p, int parity, int form, int32_t *status,
+                                                      unsigned char *scratch) {
+    const int lane = threadIdx.x & 63, N = d.N;
+    long long *csum = (long long *)scratch;
+    int *cnt = (int *)(scratch + 64 * 8), *lst = cnt + 64;
+    const bool in = lane < N;
+    const int j = min(lane, N - 1);
+    const int l = gld(d.pop[parity] + (size_t)p * N + j);
+    double acc = 0.0;
+    if (form == PGA_FORM_FP64) {
+        for (int i = 0; i + 1 < N; ++i) {
+            const int li = __builtin_amdgcn_readlane(l, i);
+            if (i < j && li == l) acc += gld(d.C + (size_t)i * N + j);
+        }
+    } else {
+        // the column kernel's MFMAs: 16 stocks at a time (lane: row and column n, rows 8 g ..), the
+        // scaled split parts from their tile-major copies, the one-hot 2^-125 where i < j share a label
+        const int n = lane & 15, g = lane >> 4, nti = d.ld_h >> 5;
+        for (int jt = 0; 16 * jt < N; ++jt) {
+            const int jj = 16 * jt + n, lj = __shfl(l, min(jj, N - 1), 64);
+            fit_floatx4 a4 = {0.f, 0.f, 0.f, 0.f};
+            for (int i0 = 0; i0 < min(16 * jt + 16, N); i0 += 32) {
+                const size_t off = ((size_t)jt * nti + (i0 >> 5)) * 512 + (size_t)lane * 8;
+                const fit_bf16x8 Ah = __builtin_bit_cast(fit_bf16x8, gld_u4(d.hs + off));
+                const fit_bf16x8 Al = __builtin_bit_cast(fit_bf16x8, gld_u4(d.ls + off));
+                uint32_t b[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int i = i0 + 8 * g + e;
+                    const int li = __shfl(l, min(i, N - 1), 64);
+                    if (i < jj && li == lj) b[e >> 1] |= 0x0100u << (16 * (e & 1));
+                }
+                const fit_bf16x8 B = __builtin_bit_cast(fit_bf16x8, make_uint4(b[0], b[1], b[2], b[3]));
+                a4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ah, B, a4, 0, 0, 0);
+                a4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Al, B, a4, 0, 0, 0);
+            }
+            // D[n][n] is register n % 4 of the lane of column n whose row group holds row n
+            const int r = n & 3;
+            const float v = r == 0 ? a4[0] : r == 1 ? a4[1] : r == 2 ? a4[2] : a4[3];
+            const float s = __shfl(v, 16 * ((lane & 15) >> 2) + (lane & 15), 64);
+            if ((lane >> 4) == jt) acc += (double)s;
+        }
+    }
+    const double v = in ? fma(2.0, acc, gld(d.C + (size_t)j * N + j)) : 0.0;
+    const bool nonfinite = __any(!isfinite(v));
+    const double mx = wave_max(isfinite(v) ? fabs(v) : 0.0);
+    cnt[lane] = 0;
+    csum[lane] = 0;
+    wave_lds_sync();
+    if (nonfinite) {
+        if (lane == 0) {
+            d.fitness[p] = -INFINITY;
+            if (status) atomicAdd(&status[PGA_ST_NONFINITE], 1);
+        }
+        if (in && d.n_s_out) gst(d.n_s_out + (size_t)p * N + lane, 0);
+        if (in && d.c_s_out) gst(d.c_s_out + (size_t)p * N + lane, 0.0);
         return;
     }
-    const size_t n = (size_t)lds_n;
-    unsigned char *b = smem;
-    long long *csum = (long long *)b;   b += pad16(8 * n);
-    int *cb = (int *)b;                 b += pad16(4 * (n + 1));
-    int *PP = (int *)b;                 b += pad16(4 * (n + 1));
-    uint16_t *members = (uint16_t *)b;
-    const int32_t *__restrict__ lab = d.pop[parity] + (size_t)p * N;
-    const double *__restrict__ C = d.C;
+    int sc = 0;
+    if (mx > 0.0) {
+        int e;
+        frexp(mx * (double)N, &e);
+        sc = 61 - e;
+    }
+    if (in) {
+        atomicAdd(&cnt[l], 1);
+        atomicAdd((unsigned long long *)&csum[l], (unsigned long long)llrint(ldexp(v, sc)));
+    }
+    wave_lds_sync();
+    const int ns = in ? cnt[lane] : 0;
+    if (in && d.n_s_out) gst(d.n_s_out + (size_t)p * N + lane, ns);
+    if (in && d.c_s_out) gst(d.c_s_out + (size_t)p * N + lane, ldexp((double)csum[lane], -sc));
+    const uint64_t m = __ballot(ns > 1);
+    if (ns > 1) lst[__popcll(m & ((1ull << lane) - 1ull))] = lane;
+    wave_lds_sync();
+    double term = 0.0;
+    bool bad = false;
+    if (lane < __popcll(m)) {
+        const int s = lst[lane];
+        bad = !cluster_term(cnt[s], csum[s], sc, term);
+        if (bad) term = 0.0;
+    }
+    const double Ltot = group_sum<64>(term);
+    const int nbad = __popcll(__ballot(bad));
+    if (lane == 0) store_fitness(d, p, Ltot, nbad, status);
+    wave_lds_sync();                                 // the next individual reuses the scratch
+}
 
-    const int ucache = (N + 63) / 64;                // uniform
-    int lr[kSwCache];
-    double dg[kSwCache];
+// The evaluation of individuals local * (256 / GL) + (group) of instance k by the groups of a
+// 256-thread workgroup (see above). SL: stocks per lane.
+template <int GL, int SL>
+__device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, int k, int local, int parity,
+                                           double frac, int listed, int slices, int cap, int form, int32_t *status,
+                                           unsigned char *smem) {
+    constexpr bool kBlock = GL == 256;
+    constexpr int WL = kBlock ? 64 : GL;             // lanes that vote together
+    constexpr int NW = kBlock ? 4 : 1;               // such sets per individual
+    const int tid = threadIdx.x, lane = tid & 63, gl = tid & (GL - 1), grp = tid / GL;
+    const int wv = kBlock ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
+    const int N = d.N, P = d.P;
+    int p = local * (256 / GL) + grp;
+    if constexpr (GL == 64) p = __builtin_amdgcn_readfirstlane(p);
+    const bool live = p < P;                         // GL < 64: a group past P works on P - 1 and stores nothing
+    if (GL >= 64 && !live) return;
+    const int pc = min(p, P - 1);
+    unsigned char *b = smem + (size_t)grp * eval_bytes(N);
+    uint32_t *cnt = (uint32_t *)b;          b += pad16(4 * (size_t)N);
+    uint32_t *last = (uint32_t *)b;
+    unsigned long long *csum = (unsigned long long *)b;   b += pad16(8 * ((size_t)N / 2 + 1));
+    uint16_t *prev = (uint16_t *)b;         b += pad16(2 * ((size_t)N + 1));
+    uint32_t *lst = (uint32_t *)b;
+    int *ired = (int *)(smem + eval_bytes(N));       // kBlock: 16 ints, then 8 doubles
+    double *red = (double *)(ired + 16);
+    auto sync = [&]() {
+        if constexpr (kBlock) __syncthreads();
+        else wave_lds_sync();
+    };
+    // votes of a set of WL lanes; bit i: its lane i
+    auto vote = [&](bool x) -> uint64_t {
+        const uint64_t m = __ballot(x);
+        if constexpr (WL == 64) return m;
+        else return (m >> (lane & ~(WL - 1))) & ((1ull << WL) - 1ull);
+    };
+    auto any = [&](bool x) -> bool {
+        if constexpr (kBlock) return __syncthreads_or(x) != 0;
+        else return vote(x) != 0;
+    };
+    const int wl = lane & (WL - 1);
+    const uint64_t below = (1ull << wl) - 1ull;
+
+    const int32_t *__restrict__ lab = d.pop[parity] + (size_t)pc * N;
+    const double *__restrict__ C = d.C;
+    const int nu = (N + GL - 1) / GL;                // slots in use, uniform
+    uint32_t lr[SL];
 #pragma unroll
-    for (int u = 0; u < kSwCache; ++u) {             // the labels are requested first, then the flag
-        if (u >= ucache) break;
-        const int j = lane + 64 * u;
-        lr[u] = j < N ? gld(lab + j) : 0;
+    for (int u = 0; u < SL; ++u) {
+        if (u >= nu) break;
+        const int j = gl + GL * u;
+        lr[u] = j < N ? (uint32_t)gld(lab + j) : 0u;
     }
-    const bool ones = gld(d.diag + N) == 1.0;
+    const bool ones = gld(d.diag + N) == 1.0;        // every C_jj is 1 (uniform)
+    bool badl = false;
 #pragma unroll
-    for (int u = 0; u < kSwCache; ++u) {
-        if (u >= ucache) break;
-        const int j = lane + 64 * u;
-        dg[u] = (!ones && j < N) ? gld(d.diag + j) : 1.0;
-    }
-    int bad = 0;
-#pragma unroll
-    for (int u = 0; u < kSwCache; ++u) {
-        if (u >= ucache) break;
-        const int j = lane + 64 * u;
+    for (int u = 0; u < SL; ++u) {
+        if (u >= nu) break;
+        const int j = gl + GL * u;
         if (j < N) {
-            if (lr[u] < 0 || lr[u] >= N) bad = 1;
-            cb[j] = 0;
-            csum[j] = 0;
+            cnt[j] = 0;
+            last[j] = (uint32_t)N;
+            if (lr[u] >= (uint32_t)N) {
+                badl = true;
+                lr[u] = 0;
+            }
         }
     }
-    if (__any(bad)) {                                // as the finish: labels outside [0, N)
-        if (lane == 0) {
+    if (gl == 0) prev[N] = (uint16_t)N;
+    const bool bad_label = any(badl);                // closes the writes above for a workgroup
+    if constexpr (!kBlock) sync();
+    if (bad_label && live) {                         // as the finish: labels outside [0, N)
+        if (gl == 0) {
             gst(d.route + p, 0);
             d.fitness[p] = -INFINITY;
             if (status) {
@@ -1083,270 +919,267 @@ __device__ void sparse_one_wave(const Tables &t, int k, int p, int slice, int ca
                 atomicAdd(&status[PGA_ST_NONFINITE], 1);
             }
         }
-        if (d.n_s_out)
-            for (int s = lane; s < N; s += 64) d.n_s_out[(size_t)p * N + s] = 0;
-        if (d.c_s_out)
-            for (int s = lane; s < N; s += 64) d.c_s_out[(size_t)p * N + s] = 0.0;
-        return;
+        for (int s = gl; s < N; s += GL) {
+            if (d.n_s_out) gst(d.n_s_out + (size_t)p * N + s, 0);
+            if (d.c_s_out) gst(d.c_s_out + (size_t)p * N + s, 0.0);
+        }
     }
-    wave_lds_sync();
-    // n_s; the atomics' old values add up to the pair count, their maximum + 1 is max n_s
-    int T = 0, nmax = 0;
+    if (GL >= 64 && bad_label) return;
+    const bool good = live && !bad_label;
+
+    // ---- n_s, pair count, chains
+    uint32_t T = 0, nmax = 0;
+    uint32_t has = 0;                                // bit u: the slot's stock has a predecessor
 #pragma unroll
-    for (int u = 0; u < kSwCache; ++u) {
-        if (u >= ucache) break;
-        if (lane + 64 * u < N) {
-            const int old = atomicAdd(&cb[lr[u]], 1);
+    for (int u = 0; u < SL; ++u) {
+        if (u >= nu) break;
+        const int j = gl + GL * u;
+        if (j < N) {
+            const uint32_t old = atomicAdd(&cnt[lr[u]], 1u);
+            const uint32_t pv = atomicExch(&last[lr[u]], (uint32_t)j);
             T += old;
             nmax = max(nmax, old + 1);
+            prev[j] = (uint16_t)pv;
+            has |= (pv < (uint32_t)N ? 1u : 0u) << u;
         }
     }
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-        T += __shfl_xor(T, m, 64);
-        nmax = max(nmax, __shfl_xor(nmax, m, 64));
-    }
-    if ((double)T > route_limit(N, frac)) {
-        if (lane == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
-        }
-        return;
-    }
-    int e;
-    frexp((double)nmax * (double)nmax, &e);          // max n_s^2 < 2^e
-    const int sc = 61 - e;
-    wave_lds_sync();
-    // exclusive prefixes of n_s (in place: cluster starts) and of the pair counts
-    {
-        const int per = (N + 63) / 64;
-        const int b0 = min(N, lane * per), b1 = min(N, b0 + per);
-        int own = 0, ownp = 0;
-        for (int x = b0; x < b1; ++x) {
-            const int c = cb[x];
-            own += c;
-            ownp += c * (c - 1) / 2;
-        }
-        int inc = own, incp = ownp;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(inc, o, 64), yp = __shfl_up(incp, o, 64);
-            if (lane >= o) {
-                inc += y;
-                incp += yp;
-            }
-        }
-        int run = inc - own, runp = incp - ownp;
-        for (int x = b0; x < b1; ++x) {
-            const int c = cb[x];
-            cb[x] = run;
-            PP[x] = runp;
-            run += c;
-            runp += c * (c - 1) / 2;
-        }
-        if (lane == 0) PP[N] = T;
-    }
-    wave_lds_sync();
-    // members grouped by cluster; cb[s] becomes the end of cluster s, whose start is cb[s - 1]
-    int badc = 0;
-#pragma unroll
-    for (int u = 0; u < kSwCache; ++u) {
-        if (u >= ucache) break;
-        const int j = lane + 64 * u;
-        if (j < N) {
-            members[atomicAdd(&cb[lr[u]], 1)] = (uint16_t)j;
-            if (!ones) {
-                if (!(fabs(dg[u]) <= 1.0)) badc = 1;
-                else atomicAdd((unsigned long long *)&csum[lr[u]], fixed_pt(dg[u], sc));
-            }
+    nmax = group_reduce<WL>(nmax, [](uint32_t a, uint32_t c) { return max(a, c); });
+    if constexpr (GL >= 64) T = group_reduce<WL>(T, [](uint32_t a, uint32_t c) { return a + c; });
+    if constexpr (kBlock) {
+        if (wl == 0) {
+            ired[wv] = (int)T;
+            ired[4 + wv] = (int)nmax;
         }
     }
-    wave_lds_sync();
-    if (ones)                                        // sum of n_s diagonal ones, exact
-        for (int s = lane; s < N; s += 64) csum[s] = (long long)(cb[s] - (s ? cb[s - 1] : 0)) << sc;
-    wave_lds_sync();
+    sync();
+    if constexpr (kBlock) {
+        T = (uint32_t)(ired[0] + ired[1] + ired[2] + ired[3]);
+        nmax = (uint32_t)max(max(ired[4], ired[5]), max(ired[6], ired[7]));
+    }
+    if (GL >= 64 && (double)T > route_limit(N, frac)) {
+        if (gl == 0) to_dense(t, d, k, p, parity, listed, slices, cap);
+        return;                                      // uniform over the individual's lanes
+    }
+    const int sc = 61 - (32 - __builtin_clz(nmax * nmax));   // max n_s^2 < 2^(61 - sc)
 
-    // pairs: kq consecutive ones per lane and round, as the workgroup kernel takes them
-    constexpr int kQ = 8;
-    const int kq = min(kQ, max(1, (T + 63) / 64));   // uniform
-    for (int q0 = lane * kq; q0 < T; q0 += kq * 64) {
-        int cs = 0, hi = N;                          // PP[cs] <= q0 < PP[hi]
-        while (hi - cs > 1) {
-            const int mid = (cs + hi) >> 1;
-            if (PP[mid] <= q0) cs = mid;
-            else hi = mid;
-        }
-        const int r = q0 - PP[cs];                   // = bq (bq - 1) / 2 + aq, aq < bq
-        int bq = (int)((1.0 + sqrt(1.0 + 8.0 * (double)r)) * 0.5);
-        while (bq * (bq - 1) / 2 > r) --bq;
-        while ((bq + 1) * bq / 2 <= r) ++bq;
-        int aq = r - bq * (bq - 1) / 2;
-        int st = cs ? cb[cs - 1] : 0;                // first position of cluster cs
-        int pend = PP[cs + 1];
-        double c[kQ];
-        int l[kQ];
+    // ---- clusters with n_s > 1, ascending (wave w of a workgroup: the w-th quarter of the labels)
+    const int QN = (N + NW - 1) / NW, s_lo = wv * QN, s_hi = min(N, s_lo + QN);
+    int nl = 0, base = 0;
+    if constexpr (kBlock) {
+        int own = 0;
+        for (int s0 = s_lo; s0 < s_hi; s0 += 64) own += __popcll(__ballot(s0 + wl < s_hi && cnt[s0 + wl] > 1));
+        if (wl == 0) ired[8 + wv] = own;
+        if (tid == 0) ired[12] = 0;                  // items
+        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            const int q = q0 + u;
-            l[u] = -1;
-            c[u] = 0.0;
-            if (u < kq && q < T) {
-                while (q >= pend) {                  // next cluster with pairs (PP[N] = T > q)
-                    st = cb[cs];
-                    ++cs;
-                    pend = PP[cs + 1];
-                    aq = 0;
-                    bq = 1;
+        for (int w = 0; w < NW; ++w) {
+            if (w < wv) base += ired[8 + w];
+            nl += ired[8 + w];
+        }
+    }
+    bool badc = false;
+    for (int s0 = s_lo; s0 < s_hi; s0 += WL) {
+        const int s = s0 + wl;
+        const uint32_t n = s < s_hi ? cnt[s] : 0;
+        if (good && s < s_hi) {
+            if (d.n_s_out) gst(d.n_s_out + (size_t)p * N + s, (int32_t)n);
+            if (d.c_s_out && n <= 1)                 // an unused label, or a singleton's diagonal entry
+                gst(d.c_s_out + (size_t)p * N + s,
+                    n == 0 ? 0.0 : ones ? 1.0 : ldexp((double)(long long)fixed_pt(gld(d.diag + last[s]), sc), -sc));
+        }
+        const uint64_t m = vote(n > 1);
+        const int at = base + __popcll(m & below);
+        if (n > 1) {
+            lst[at] = n | ((uint32_t)s << 16);
+        }
+        if (s < s_hi) last[s] = n > 1 ? (uint32_t)at : kNoCluster;   // the chains are complete: now the list index
+        base += __popcll(m);
+    }
+    if constexpr (!kBlock) nl = base;
+    sync();
+    // ---- items: stocks with a predecessor, with their cluster (in the place of n_s)
+    int ni = 0;
+    if constexpr (kBlock) {
+        int own = 0;
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (u >= nu) break;
+            own += __popcll(__ballot((has >> u) & 1u));
+        }
+        int at = 0;
+        if (wl == 0) at = atomicAdd(&ired[12], own);
+        ni = __builtin_amdgcn_readfirstlane(at);
+    }
+#pragma unroll
+    for (int u = 0; u < SL; ++u) {
+        if (u >= nu) break;
+        const bool h = (has >> u) & 1u;
+        const uint64_t m = vote(h);
+        lr[u] = last[lr[u]];                         // the list index from here on
+        if (h) cnt[ni + __popcll(m & below)] = (uint32_t)(gl + GL * u) | (lr[u] << 16);
+        ni += __popcll(m);
+    }
+    sync();
+    if constexpr (kBlock) ni = ired[12];
+    // csum takes the place of last: it starts with the sum of the diagonal
+    for (int m = gl; m < nl; m += GL) csum[m] = ones ? (unsigned long long)(lst[m] & 0xFFFFu) << sc : 0ull;
+    sync();
+    if (!ones) {
+#pragma unroll
+        for (int u = 0; u < SL; ++u) {
+            if (u >= nu) break;
+            const int j = gl + GL * u;
+            if (j < N) {
+                const double dg = gld(d.diag + j);
+                if (!(fabs(dg) <= 1.0)) badc = true;
+                else if (lr[u] != kNoCluster) atomicAdd(&csum[lr[u]], fixed_pt(dg, sc));
+            }
+        }
+        sync();
+    }
+
+    // ---- pairs
+    const double S = ldexp(2.0, sc);                 // rint(c S) = the fixed point of 2 c (exact scaling)
+    for (int x = gl; x < ni; x += GL) {
+        const uint32_t it = cnt[x];
+        const int j = (int)(it & 0xFFFFu);
+        double hi = 0.0, lo = 0.0;                   // the integer sum as hi 2^32 + lo, both exact
+        auto entry = [&](int i) {                    // the pair's entry; past the end of a chain: the diagonal, unused
+            const int a = i < N ? i : j;
+            return gld(C + (uint32_t)(min(a, j) * N + max(a, j)));
+        };
+        auto take = [&](double c) {
+            badc |= !(fabs(c) <= 1.0);
+            const double q = rint(c * S);
+            const double h = floor(q * 0x1p-32);
+            hi += h;
+            lo += fma(h, -0x1p32, q);
+        };
+        int i = prev[j];
+        do {
+            const int i1 = prev[i], i2 = prev[i1], i3 = prev[i2];
+            const bool v1 = i1 < N, v2 = i2 < N, v3 = i3 < N;
+            const double c0 = entry(i);
+            if (__any(v1)) {
+                const double c1 = entry(i1);
+                if (__any(v2)) {
+                    const double c2 = entry(i2), c3 = entry(i3);
+                    take(v2 ? c2 : 0.0);
+                    take(v3 ? c3 : 0.0);
                 }
-                const int j = members[st + bq], i = members[st + aq];
-                c[u] = gld(C + (size_t)min(i, j) * N + max(i, j));
-                l[u] = cs;
-                if (++aq == bq) {
-                    ++bq;
-                    aq = 0;
-                }
+                take(v1 ? c1 : 0.0);
             }
-        }
-        long long run = 0;
-        int cur = -1;
-#pragma unroll
-        for (int u = 0; u < kQ; ++u) {
-            if (l[u] < 0) continue;
-            if (!(fabs(c[u]) <= 1.0)) {
-                badc = 1;
-                continue;
-            }
-            if (l[u] != cur) {
-                if (cur >= 0) atomicAdd((unsigned long long *)&csum[cur], (unsigned long long)run);
-                cur = l[u];
-                run = 0;
-            }
-            run += fixed_pt(2.0 * c[u], sc);
-        }
-        if (cur >= 0) atomicAdd((unsigned long long *)&csum[cur], (unsigned long long)run);
+            take(c0);
+            i = prev[i3];
+        } while (i < N);
+        const double h2 = floor(lo * 0x1p-32);
+        const unsigned long long v = ((unsigned long long)(uint32_t)((int)hi + (int)h2) << 32) +
+                                     (uint32_t)fma(h2, -0x1p32, lo);
+        atomicAdd(&csum[it >> 16], v);
     }
-    if (__any(badc)) {
-        if (lane == 0) {
-            gst(d.route + p, 1);
-            list_dense(t, parity, slice, cap, p, k);
+    const bool handed = any(badc);                   // (a workgroup: also closes the atomics)
+    if constexpr (!kBlock) sync();
+    if constexpr (GL >= 64) {
+        if (handed) {
+            if (gl == 0) to_dense(t, d, k, p, parity, listed, slices, cap);
+            return;
         }
-        return;
     }
-    if (lane == 0) gst(d.route + p, 0);
-    wave_lds_sync();
 
-    // per-label outputs and the list of labels with n_s > 1, ascending (into members)
-    uint16_t *lst = members;
-    int nlist = 0;
-    for (int s0 = 0; s0 < N; s0 += 64) {
-        const int s = s0 + lane;
-        const int ns = s < N ? cb[s] - (s ? cb[s - 1] : 0) : 0;
-        if (s < N) {
-            if (d.n_s_out) gst(d.n_s_out + (size_t)p * N + s, ns);
-            if (d.c_s_out) gst(d.c_s_out + (size_t)p * N + s, ldexp((double)csum[s], -sc));
+    // ---- log terms, in the finish's order: entry m of the list to virtual thread m mod 256, the
+    // virtual waves' butterflies, then the four in order
+    if (d.c_s_out && good && !handed)
+        for (int m = gl; m < nl; m += GL)
+            gst(d.c_s_out + (size_t)p * N + (lst[m] >> 16), ldexp((double)(long long)csum[m], -sc));
+    double Ltot = 0.0;
+    int nbad = 0;
+    if constexpr (kBlock) {
+        double L = 0.0;
+        for (int m = tid; m < nl; m += 256) {
+            double term;
+            if (cluster_term((int)(lst[m] & 0xFFFFu), (long long)csum[m], sc, term)) L += term;
+            else ++nbad;
         }
-        const uint64_t m = __ballot(ns > 1);
-        if (ns > 1) lst[nlist + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)s;
-        nlist += __popcll(m);
-    }
-    wave_lds_sync();
-    // entry m belongs to virtual thread m mod 256, i.e. virtual wave (m / 64) mod 4
-    double L[kFinWaves] = {0.0, 0.0, 0.0, 0.0};
-    int nbad[kFinWaves] = {0, 0, 0, 0};
-    for (int m = lane; m < nlist; m += 64) {
-        const int w = (m >> 6) & (kFinWaves - 1);
-        const int s = lst[m];
-        const int ni = cb[s] - (s ? cb[s - 1] : 0);
-        const double nd = (double)ni;
-        const double c = ldexp((double)csum[s], -sc);
-        const double n2 = nd * nd;
-        const bool ok = c > 0.0 && c < n2;
-        const double term = ok ? log(nd / c) + (nd - 1.0) * log((n2 - nd) / (n2 - c)) : 0.0;
-#pragma unroll
-        for (int v = 0; v < kFinWaves; ++v)
-            if (v == w) {
-                if (ok) L[v] += term;
-                else nbad[v] += 1;
+        L = group_sum<64>(L);
+        nbad = (int)group_reduce<64>((uint32_t)nbad, [](uint32_t a, uint32_t c) { return a + c; });
+        if (wl == 0) {
+            red[wv] = L;
+            ired[wv] = nbad;
+        }
+        __syncthreads();
+        for (int w = 0; w < 4; ++w) Ltot += red[w];
+        nbad = ired[0] + ired[1] + ired[2] + ired[3];
+    } else {
+        for (int m0 = 0; m0 < nl; m0 += GL) {        // GL < 64: one round, nl <= N / 2 <= GL
+            const int m = m0 + gl;
+            double term = 0.0;
+            bool bad = false;
+            if (m < nl) {
+                bad = !cluster_term((int)(lst[m] & 0xFFFFu), (long long)csum[m], sc, term);
+                if (bad) term = 0.0;
             }
+            Ltot += group_sum<GL>(0.0 + term);
+            nbad += __popcll(vote(bad));
+        }
     }
-    double Ltot = 0.0, badtot = 0.0;
-#pragma unroll
-    for (int v = 0; v < kFinWaves; ++v) {
-        Ltot += wave_sum(L[v]);
-        badtot += wave_sum((double)nbad[v]);
+    if (gl == 0 && good && !handed) {
+        gst(d.route + p, 0);
+        store_fitness(d, p, Ltot, nbad, status);
     }
-    if (lane == 0) {
-        if (badtot > 0.0) {
-            d.fitness[p] = -INFINITY;
-            if (status) {
-                atomicAdd(&status[PGA_ST_DOMAIN], (int)badtot);
-                atomicAdd(&status[PGA_ST_NONFINITE], 1);
-            }
-        } else {
-            d.fitness[p] = 0.5 * Ltot;
+    if constexpr (GL < 64) {
+        // individuals with an entry out of range, one after another by the whole wave
+        uint64_t todo = __ballot(gl == 0 && good && handed);
+        while (todo) {
+            const int src = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int q = __builtin_amdgcn_readlane(p, src);
+            if (lane == 0) gst(d.route + q, 0);
+            dense_small(d, q, parity, form, status,
+                        smem + (size_t)(256 / GL) * eval_bytes(N) + (size_t)(tid >> 6) * kSmallScratch);
         }
     }
 }
 
-// Listed: entry i / slices of slice i mod slices of this parity's sparse list
-// (workgroups past their slice's length end at once). Else individual i, the
-// route decided here as in the workgroup kernel.
-__device__ __forceinline__ bool sparse_target(const Tables &t, int listed, int parity, int slices, int cap, int &k,
-                                              int &p, int &slice) {
-    if (listed) {
-        slice = (int)blockIdx.x % slices;
-        const int at = (int)blockIdx.x / slices;
-        const int32_t *e = list_entry(t, kListSparse, slice, cap, at);   // read with the count: in bounds
-        const int n = *list_count(t, parity, kListSparse, slice);
-        p = __builtin_amdgcn_readfirstlane(gld(e));
-        k = __builtin_amdgcn_readfirstlane(gld(e + 1));
-        return at < n;
-    }
-    const int g = blockIdx.x;
-    if (g >= t.inds[t.n_inst]) return false;         // the grid may exceed the total (capacity-sized graph)
-    k = find_inst(t.inds, t.n_inst, g);
-    p = g - t.inds[k];
-    slice = -1;
-    return true;
-}
+constexpr int kEvalRun = 128;
 
-__global__ __launch_bounds__(64) void k_sparse_wave(Tables t, int lds_n, int parity, double frac, int listed,
-                                                    int slices, int cap, int32_t *status) {
+// Workgroup b takes the next individuals of the instance that t.evals gives it. In large launches
+// (listed) workgroup 0 also empties the dense list of the other parity, which the evaluation
+// before this one used. Instances above kSparseMaxN: a thread per individual sends it to the
+// dense route.
+__global__ __launch_bounds__(256, 8) void k_eval(Tables t, int parity, double frac, int listed, int slices, int cap,
+                                                 int form, int32_t *status) {
     extern __shared__ __align__(16) unsigned char smem[];
-    int k, p, slice;
-    if (!sparse_target(t, listed, parity, slices, cap, k, p, slice)) return;
-    sparse_one_wave(t, k, p, slice, cap, lds_n, parity, frac, status, smem);
+    const int b = blockIdx.x;
+    if (listed && b == 0)
+        for (int i = threadIdx.x; i < kListSlices; i += 256) gst(list_count(t, parity ^ 1, i), 0);
+    if (b >= t.evals[t.n_inst]) return;              // the grid may exceed the total (capacity-sized graph)
+    // Workgroups go to the XCDs in turn; runs of kEvalRun consecutive ones are given to one XCD, so
+    // that it reads the C of few instances at a time (256 instances, N ~ U{32..512}: 334 us without,
+    // 290 with runs of 128 to 512; a run of an eighth of the launch is less even).
+    const int total = t.evals[t.n_inst], run8 = b / (kXcds * kEvalRun), in8 = b % (kXcds * kEvalRun);
+    const int bb = (run8 + 1) * kXcds * kEvalRun > total
+                       ? b
+                       : run8 * kXcds * kEvalRun + in8 % kXcds * kEvalRun + in8 / kXcds;
+    const int k = find_inst(t.evals, t.n_inst, bb);
+    const InstDesc &d = t.desc[k];
+    if (inst_stopped(d)) return;
+    const int N = d.N, local = bb - t.evals[k];
+    if (N <= 32) eval_pairs<16, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+    else if (N <= 64) eval_pairs<32, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+    else if (N <= 512) eval_pairs<64, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+    else if (N <= kSparseMaxN)
+        eval_pairs<256, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+    else {
+        const int p = 256 * local + threadIdx.x;
+        if (p < d.P) to_dense(t, d, k, p, parity, listed, slices, cap);
+    }
 }
 
-// A workgroup per list entry or individual (see sparse_target). (A grid-stride
-// loop over a smaller grid holds the per-thread values of the body across
-// iterations: 85 registers instead of 52, five waves per SIMD instead of
-// eight.)
-__global__ __launch_bounds__(kFinThreads) void k_sparse(Tables t, int lds_n, int parity, double frac, int listed,
-                                                        int slices, int cap, int32_t *status) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    int k, p, slice;
-    if (!sparse_target(t, listed, parity, slices, cap, k, p, slice)) return;
-    sparse_one(t, k, p, slice, cap, lds_n, parity, frac, status, smem);
-}
-
-hipError_t launch_sparse(Tables t, int total_inds, int max_n, int parity, double frac, int listed, int lists_ready,
-                         int32_t *status, hipStream_t s) {
-    if (total_inds <= 0) return hipSuccess;
-    const int n = std::min(max_n, kSparseMaxN);
+hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int parity, double frac, int listed, int form,
+                       int32_t *status, hipStream_t s) {
+    if (blocks <= 0) return hipSuccess;
     const int n_wg = (total_inds + 3) / 4, slices = list_slices(n_wg), cap = list_slice_cap(n_wg);
-    if (listed && !lists_ready) {
-        hipLaunchKernelGGL(k_route, dim3(n_wg), dim3(256), route_lds_bytes(n), s, t, n, parity, frac, slices, cap);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    const int grid = listed ? slices * cap : total_inds;
-    if (n <= kSparseWaveMaxN)
-        hipLaunchKernelGGL(k_sparse_wave, dim3(grid), dim3(64), sparse_wave_lds_bytes(n), s, t, n, parity, frac,
-                           listed, slices, cap, status);
-    else
-        hipLaunchKernelGGL(k_sparse, dim3(grid), dim3(kFinThreads), sparse_lds_bytes(n), s, t, n, parity, frac,
-                           listed, slices, cap, status);
+    hipLaunchKernelGGL(k_eval, dim3(blocks), dim3(256), lds, s, t, parity, frac, listed, slices, cap, form, status);
     return hipGetLastError();
 }
 

@@ -170,8 +170,8 @@ int bucket(int x) {
 }
 
 // ---- workspace layout ----------------------------------------------------------
-// [InstDesc x n][prefix tiles n+1][prefix inds n+1][route list counters kListCounters int32]
-// [route list entries: list_words(ceil(bucket(sum of P) / 4)) int32]
+// [InstDesc x n][prefix tiles n+1][prefix inds n+1][prefix evals n+1][dense list counters kListCounters int32]
+// [dense list entries: list_words(ceil(bucket(sum of P) / 4)) int32]
 // then per instance: [wsum P x N doubles][elite PGA_E_MAX int32]
 // and, for the BF16x2 form, [hi * 2^125 ld x ld][lo * 2^125 ld x ld] (bf16),
 // and, for SUS selection, [rank P int32][weight prefix P uint64],
@@ -190,7 +190,7 @@ Layout make_layout(const int32_t *Ns, const int32_t *Ps, int n, int form, const 
     Layout L;
     L.desc_off = 0;
     L.pre_off = align_up(sizeof(InstDesc) * (size_t)n, 256);
-    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (2 * ((size_t)n + 1) + (size_t)kListCounters), 256);
+    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (3 * ((size_t)n + 1) + (size_t)kListCounters), 256);
     L.list_off = L.inst_off;
     int sum_p = 0;
     for (int k = 0; k < n; ++k) sum_p += Ps[k];
@@ -229,7 +229,8 @@ Tables tables_at(void *ws, const Layout &L, int n) {
     t.desc = (const InstDesc *)(b + L.desc_off);
     t.tiles = (const int32_t *)(b + L.pre_off);
     t.inds = t.tiles + (n + 1);
-    t.sq = (int32_t *)(b + L.pre_off) + 2 * (n + 1);
+    t.evals = t.tiles + 2 * (n + 1);
+    t.sq = (int32_t *)(b + L.pre_off) + 3 * (n + 1);
     t.sq_list = (int32_t *)(b + L.list_off);
     t.n_inst = n;
     return t;
@@ -242,18 +243,25 @@ struct Shape {
     int max_p, sus;      // largest P; 1 if an instance selects by SUS
     int stop;            // 1 if an instance may stop early (termination test on)
     double frac;         // cluster-pair route limit (0: off; then every route pointer is null)
+    int evals;           // cluster-pair workgroups
+    size_t lds;          // LDS of one of them
 };
 
-// lists_ready: the breed launch that made this population already filled its route lists.
-hipError_t run_fitness(const Tables &t, const Shape &sh, int form, int parity, int32_t *status, hipStream_t s,
-                       int lists_ready = 0) {
+// Tiles of the pair-sum: none for the instances that the cluster-pair kernel always evaluates.
+int dense_tiles(int N, int P, const Variant &v, double frac) {
+    return frac > 0.0 && N <= kRouteAllPairsMaxN ? 0 : pair_tiles(N, P, v);
+}
+
+hipError_t run_fitness(const Tables &t, const Shape &sh, int form, int parity, int32_t *status, hipStream_t s) {
     hipError_t e;
     const int listed = sh.frac > 0.0 && sh.inds >= kManyInds ? 1 : 0;
-    if (sh.frac > 0.0 && (e = timed(10, s, [&] {
-                              return launch_sparse(t, sh.inds, sh.max_n, parity, sh.frac, listed, lists_ready, status,
-                                                   s);
-                          })) != hipSuccess)
-        return e;
+    if (sh.frac > 0.0) {
+        e = timed(10, s, [&] {
+            return launch_eval(t, sh.inds, sh.evals, sh.lds, parity, sh.frac, listed, form, status, s);
+        });
+        // with every N <= 64 no individual is left to the pair-sum and the finish
+        if (e != hipSuccess || sh.max_n <= kRouteAllPairsMaxN) return e;
+    }
     if (form == PGA_FORM_FP64) {
         e = timed(0, s, [&] { return launch_pairsum_fp64(t, sh.tiles, parity, sh.v, s); });
     } else {
@@ -269,27 +277,22 @@ hipError_t run_fitness(const Tables &t, const Shape &sh, int form, int parity, i
 hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, int32_t *status,
                            hipStream_t s) {
     hipError_t e;
-    int lists_ready = 0;
     for (int k = 0; k < G; ++k) {
         const int parity = k & 1;
-        if ((e = run_fitness(t, sh, form, parity, status, s, lists_ready)) != hipSuccess) return e;
+        if ((e = run_fitness(t, sh, form, parity, status, s)) != hipSuccess) return e;
         // Without SUS or an early stop, breeding needs the ranking only for the elite
         // slots, and the breed kernel does it itself (fold); otherwise rank first.
         const int by_wave = sh.max_n <= kBreedWaveMaxN && sh.inds >= kManyInds ? 1 : 0;
         const int fold = (!sh.sus && !sh.stop) ? 1 : 0;
-        // with the route lists in use and every N <= 64 (every individual on the cluster-pair
-        // route), the wave-per-slot breed fills the next evaluation's list itself
-        const int classify = by_wave && sh.frac > 0.0 && sh.max_n <= kRouteAllPairsMaxN ? 1 : 0;
         if (!fold && (e = timed(3, s, [&] { return launch_rank(t, k, 0, s); })) != hipSuccess) return e;
         if (sh.sus && (e = timed(8, s, [&] { return launch_sus(t, sh.max_p, s); })) != hipSuccess) return e;
         if ((e = timed(4, s, [&] {
-                 return launch_breed(t, sh.inds, parity, k, fold, by_wave, sh.max_n, classify, s);
+                 return launch_breed(t, sh.inds, parity, k, fold, by_wave, sh.max_n, s);
              })) != hipSuccess)
             return e;
-        lists_ready = classify;
     }
     const int parity = G & 1;
-    if ((e = run_fitness(t, sh, form, parity, status, s, lists_ready)) != hipSuccess) return e;
+    if ((e = run_fitness(t, sh, form, parity, status, s)) != hipSuccess) return e;
     if ((e = timed(3, s, [&] { return launch_rank(t, G, 1, s); })) != hipSuccess) return e;
     return launch_copy_back(t, sh.inds, G, s);
 }
@@ -300,12 +303,13 @@ hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, in
 struct GraphKey {
     void *ws;
     int32_t *status;
-    int n_inst, form, G, tiles, inds, max_n, ipg, order, kind, max_p, sus, stop;
+    int n_inst, form, G, tiles, inds, evals, max_n, ipg, order, kind, max_p, sus, stop;
+    size_t lds;
     double frac;
     bool operator<(const GraphKey &o) const {
-        return std::tie(ws, status, n_inst, form, G, tiles, inds, max_n, ipg, order, kind, max_p, sus, stop, frac) <
-               std::tie(o.ws, o.status, o.n_inst, o.form, o.G, o.tiles, o.inds, o.max_n, o.ipg, o.order, o.kind,
-                        o.max_p, o.sus, o.stop, o.frac);
+        return std::tie(ws, status, n_inst, form, G, tiles, inds, evals, max_n, ipg, order, kind, max_p, sus, stop, lds,
+                        frac) < std::tie(o.ws, o.status, o.n_inst, o.form, o.G, o.tiles, o.inds, o.evals, o.max_n,
+                                         o.ipg, o.order, o.kind, o.max_p, o.sus, o.stop, o.lds, o.frac);
     }
 };
 
@@ -496,6 +500,8 @@ int prepare_single(const double *C, const uint16_t *C_hi, const uint16_t *C_lo, 
     sh->sus = 0;
     sh->stop = 0;
     sh->frac = frac;
+    sh->evals = eval_blocks(N, P);
+    sh->lds = eval_lds(N);
     *dd = d;
     if (form == PGA_FORM_BF16X2) {
         HIP_TRY(launch_write_desc(d, 0, (InstDesc *)t->desc, (int32_t *)t->tiles, s));
@@ -507,7 +513,7 @@ int prepare_single(const double *C, const uint16_t *C_hi, const uint16_t *C_lo, 
 // Writes the tile prefix of variant v into the descriptor area and sets sh.
 hipError_t use_variant(const InstDesc &d, const Tables &t, int form, int vi, Shape *sh, hipStream_t s) {
     sh->v = variant_at(form, vi);
-    sh->tiles = pair_tiles(d.N, d.P, sh->v);
+    sh->tiles = dense_tiles(d.N, d.P, sh->v, sh->frac);
     return launch_write_desc(d, sh->tiles, (InstDesc *)t.desc, (int32_t *)t.tiles, s);
 }
 }  // namespace
@@ -761,10 +767,10 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     char *hb = (char *)ctx->staging;
     InstDesc *hd = (InstDesc *)(hb + L.desc_off);
     int32_t *pf = (int32_t *)(hb + L.pre_off);
-    int32_t *pi = pf + (nb + 1);
-    pf[0] = pi[0] = 0;
-    memset(pi + (nb + 1), 0, sizeof(int32_t) * kListCounters);     // the route lists start empty
-    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac()};
+    int32_t *pi = pf + (nb + 1), *pe = pi + (nb + 1);
+    pf[0] = pi[0] = pe[0] = 0;
+    memset(pe + (nb + 1), 0, sizeof(int32_t) * kListCounters);     // the dense lists start empty
+    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0};
     int total_p = 0;
     for (int k = 0; k < n_inst; ++k) {
         sh.max_n = std::max(sh.max_n, (int)inst[k].N);
@@ -816,14 +822,19 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         }
         d.ind0 = pi[k];
         hd[k] = d;
-        pf[k + 1] = pf[k] + pair_tiles(I.N, I.P, sh.v);
+        pf[k + 1] = pf[k] + dense_tiles(I.N, I.P, sh.v, sh.frac);
         pi[k + 1] = pi[k] + I.P;
+        pe[k + 1] = pe[k] + eval_blocks(I.N, I.P);
+        sh.lds = std::max(sh.lds, eval_lds(I.N));
     }
     for (int k = n_inst; k < nb; ++k) {              // padding slots: no individuals, no tiles
         hd[k] = InstDesc{};
         pf[k + 1] = pf[k];
         pi[k + 1] = pi[k];
+        pe[k + 1] = pe[k];
     }
+    sh.evals = bucket(pe[nb]);
+    sh.lds = align_up(sh.lds, 2048);                 // part of a captured graph's key: few values
     sh.tiles = bucket(pf[nb]);                       // launch sizes; the kernels stop at the real totals
     sh.inds = bucket(pi[nb]);
     HIP_TRY(hipMemcpyAsync(ws, ctx->staging, head, hipMemcpyHostToDevice, s));
@@ -840,8 +851,8 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         HIP_TRY(run_generations(t, sh, form, generations, status, s));
         return PGA_OK;
     }
-    GraphKey key{ws, status, nb, form, generations, sh.tiles, sh.inds, sh.max_n, sh.v.ipg, sh.v.order, sh.v.kind,
-                 sh.max_p, sh.sus, sh.stop, sh.frac};
+    GraphKey key{ws, status, nb, form, generations, sh.tiles, sh.inds, sh.evals, sh.max_n, sh.v.ipg, sh.v.order,
+                 sh.v.kind, sh.max_p, sh.sus, sh.stop, sh.lds, sh.frac};
     auto it = ctx->graphs.find(key);
     if (it == ctx->graphs.end()) {
         // bounded cache: drop the least recently launched graph
