@@ -23,13 +23,13 @@ namespace pga {
 // tables travel as kernel arguments, so no host buffer has to outlive the call.
 struct DescBlob {
     InstDesc d;
-    int32_t prefix[6];   // {0, tiles}, {0, P}, {0, evaluation blocks}; the list counters follow, zeroed
+    int32_t prefix[8];   // {0, tiles}, {0, P}, {0, evaluation blocks}, {0, 0}; the list counters follow, zeroed
 };
 
 __global__ void k_write_desc(DescBlob b, InstDesc *dst, int32_t *prefix) {
     if (threadIdx.x == 0) *dst = b.d;
-    if (threadIdx.x < 6) prefix[threadIdx.x] = b.prefix[threadIdx.x];
-    for (int i = threadIdx.x; i < kListCounters; i += blockDim.x) prefix[6 + i] = 0;
+    if (threadIdx.x < 8) prefix[threadIdx.x] = b.prefix[threadIdx.x];
+    for (int i = threadIdx.x; i < kListCounters; i += blockDim.x) prefix[8 + i] = 0;
 }
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix, hipStream_t s) {
@@ -41,6 +41,7 @@ hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, in
     b.prefix[3] = d.P;
     b.prefix[4] = 0;
     b.prefix[5] = eval_blocks(d.N, d.P);
+    b.prefix[6] = b.prefix[7] = 0;
     hipLaunchKernelGGL(k_write_desc, dim3(1), dim3(256), 0, s, b, dst, prefix);
     return hipGetLastError();
 }
@@ -314,11 +315,7 @@ hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, const Vari
 //      takes entries t, t + 256, ... of the four lists in wave order and sums
 //      their terms in that order, each wave adds its lanes by a butterfly, and
 //      the four wave sums are added in wave order (a fixed order).
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
-}
+__device__ __forceinline__ double wave_sum(double v) { return group_sum<64>(v); }
 
 __device__ __forceinline__ double wave_max(double v) {
 #pragma unroll
@@ -655,59 +652,6 @@ size_t eval_lds(int N) { return N > kSparseMaxN ? 0 : eval_lds_bytes(N); }
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-}
-
-// Cross-lane steps without LDS: rotations within rows of 16 lanes (DPP), and the swaps of
-// neighbouring rows and of the wave's halves.
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-constexpr int kRor8 = 0x128, kRor4 = 0x124, kRor2 = 0x122, kRor1 = 0x121;   // row_ror:n
-constexpr int kQuad2 = 0x4E, kQuad1 = 0xB1;                                  // quad_perm [2,3,0,1], [1,0,3,2]
-
-template <int GL, class Op>                       // over GL <= 64 lanes; op commutative and associative
-__device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
-    v = op(v, dpp<kRor8>(v));
-    v = op(v, dpp<kRor4>(v));
-    v = op(v, dpp<kRor2>(v));
-    v = op(v, dpp<kRor1>(v));
-    if constexpr (GL >= 32) {
-        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-        v = op(r[0], r[1]);
-    }
-    if constexpr (GL >= 64) {
-        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        v = op(r[0], r[1]);
-    }
-    return v;
-}
-
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b);
-    return v + __builtin_bit_cast(double, o);
-}
-// The butterfly wave_sum (lane l with l ^ 32, 16, 8, 4, 2, 1), the same bits: a step's sum is commutative,
-// and once the values repeat with period 8 (4) in a row, the row's rotation by 4 (2) pairs the same
-// values as the exchange. GL = 32 and 16: the wave_sum of the group's values followed by zeros.
-template <int GL>
-__device__ __forceinline__ double group_sum(double v) {
-    auto halves = [](double x, auto swap) {
-        const uint64_t b = __builtin_bit_cast(uint64_t, x);
-        const auto l = swap((uint32_t)b), h = swap((uint32_t)(b >> 32));
-        return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
-               __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
-    };
-    if constexpr (GL >= 64)
-        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
-    if constexpr (GL >= 32)
-        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
-    v = dpp_add<kRor8>(v);
-    v = dpp_add<kRor4>(v);
-    v = dpp_add<kQuad2>(v);
-    return dpp_add<kQuad1>(v);
 }
 
 __device__ __forceinline__ unsigned long long fixed_pt(double c, int sc) {

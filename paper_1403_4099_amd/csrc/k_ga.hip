@@ -81,28 +81,37 @@ __device__ Cand block_best(Cand c, double *rf, int *ri) {
     return r;
 }
 
-// Wave butterflies: the comparison is a total order and the sums run in a fixed
-// pattern, so every lane ends with the same, reproducible value.
-__device__ __forceinline__ Cand wave_best(Cand c) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-        const double fo = __shfl_xor(c.f, m, 64);
-        const int io = __shfl_xor(c.i, m, 64);
-        if (io >= 0 && (c.i < 0 || ranks_before(fo, io, c.f, c.i))) c = Cand{fo, io};
-    }
-    return c;
+// Best of a wave, in every lane: the comparison is a total order, so the lane exchanges can
+// run in any pattern (row rotations and row and half swaps here, without LDS).
+__device__ __forceinline__ Cand cand_max(Cand a, Cand b) {
+    return b.i >= 0 && (a.i < 0 || ranks_before(b.f, b.i, a.f, a.i)) ? b : a;
 }
-
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
+template <int CTRL>
+__device__ __forceinline__ Cand cand_dpp(Cand c) {
+    const uint64_t f = __builtin_bit_cast(uint64_t, c.f);
+    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(f >> 32)) << 32) | dpp<CTRL>((uint32_t)f);
+    return Cand{__builtin_bit_cast(double, o), (int)dpp<CTRL>((uint32_t)c.i)};
+}
+template <class Swap>
+__device__ __forceinline__ Cand cand_swap(Cand c, Swap swap) {
+    const uint64_t f = __builtin_bit_cast(uint64_t, c.f);
+    const auto l = swap((uint32_t)f), h = swap((uint32_t)(f >> 32)), i = swap((uint32_t)c.i);
+    return cand_max(Cand{__builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]), (int)i[0]},
+                    Cand{__builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]), (int)i[1]});
+}
+__device__ __forceinline__ Cand wave_best(Cand c) {
+    c = cand_max(c, cand_dpp<kRor8>(c));
+    c = cand_max(c, cand_dpp<kRor4>(c));
+    c = cand_max(c, cand_dpp<kRor2>(c));
+    c = cand_max(c, cand_dpp<kRor1>(c));
+    c = cand_swap(c, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    return cand_swap(c, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
 }
 
 // Elite selection, termination state and statistics of one instance by one
 // workgroup of kRankThreads threads: the rank kernel, and, when the breed
-// kernel does the ranking itself (no SUS, no early stop), the breed workgroups
-// of the elite slots. Both use this code with the same thread count, so their
+// kernel does the ranking itself (no SUS, no early stop), a breed workgroup per
+// instance. Both use this code with the same thread count, so their
 // statistics agree bit for bit. Each thread keeps up to CACHE of its fitness
 // values in registers (all loads issued at once) and re-reads the rest; every
 // thread visits its values in the same order whatever CACHE is, so CACHE
@@ -171,15 +180,21 @@ struct RankBlock {
         __syncthreads();
         return b;
     }
-    __device__ double block_sum(double v) {
+    // Sums of a and b over the workgroup, for thread 0.
+    __device__ void block_sum2(double &a, double &b) {
         const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        v = wave_sum_d(v);
-        if (lane == 0) sh.wf[wave] = v;
+        a = group_sum<64>(a);
+        b = group_sum<64>(b);
+        if (lane == 0) {
+            sh.wf[wave] = a;
+            sh.wi[wave] = (int)b;
+        }
         __syncthreads();
-        double r = 0.0;
-        for (int w = 0; w < kRankWaves; ++w) r += sh.wf[w];
-        __syncthreads();
-        return r;
+        a = b = 0.0;
+        for (int w = 0; w < kRankWaves; ++w) {
+            a += sh.wf[w];
+            b += (double)sh.wi[w];
+        }
     }
     // The r-th ranked individual for r = 0 .. rounds-1: calls visit(r, cand) in order.
     template <typename F>
@@ -249,8 +264,9 @@ struct RankBlock {
     // Ranks 0 .. rounds-1 (visit(r, cand) in order) and, with stats set, the
     // statistics row gen_off; returns the best. A single read of the values
     // serves up to kTop ranks, more take one read per rank.
-    template <typename F>
-    __device__ Cand rank_and_stats(const InstDesc &d, int rounds, int gen_off, bool stats, F &&visit) {
+    // between(): called once the ranks are known, before the statistics.
+    template <typename F, typename B>
+    __device__ Cand rank_and_stats(const InstDesc &d, int rounds, int gen_off, bool stats, F &&visit, B &&between) {
         Cand best{-INFINITY, 0};
         if (rounds <= kTop) {
             double sum, ninv;
@@ -258,12 +274,14 @@ struct RankBlock {
                 if (r == 0) best = b;
                 visit(r, b);
             });
-            if (stats) store_stats(d, gen_off, best, block_sum(sum), block_sum(ninv));
+            between();
+            if (stats) store_stats(d, gen_off, best, sum, ninv);
         } else {
             ranked(rounds, [&](int r, Cand b) {
                 if (r == 0) best = b;
                 visit(r, b);
             });
+            between();
             if (stats) write_stats(d, gen_off, best);
         }
         return best;
@@ -283,9 +301,10 @@ struct RankBlock {
             if (isfinite(fp)) sum += fp;
             else ninv += 1.0;
         }
-        store_stats(d, gen_off, best, block_sum(sum), block_sum(ninv));
+        store_stats(d, gen_off, best, sum, ninv);
     }
-    __device__ void store_stats(const InstDesc &d, int gen_off, Cand best, double total, double inv) const {
+    __device__ void store_stats(const InstDesc &d, int gen_off, Cand best, double total, double inv) {
+        block_sum2(total, inv);
         if (threadIdx.x == 0) {
             double *row = d.stats + 4 * (size_t)gen_off;
             const double nfin = (double)P - inv;
@@ -348,7 +367,7 @@ __global__ __launch_bounds__(kRankThreads) void k_rank(Tables t, int gen_off, in
         for (int p = threadIdx.x; p < P; p += kRankThreads) gst(d.sus_rank + p, 1);
     const Cand best = rb.rank_and_stats(d, E > 1 ? E : 1, gen_off, d.stats != nullptr, [&](int r, Cand b) {
         if (r < E && threadIdx.x == 0) d.elite[r] = b.i;
-    });
+    }, [] {});
     if (d.term && threadIdx.x == 0) term_update(d, st, best.f, final, gen_off == 0);
 }
 
@@ -358,7 +377,7 @@ hipError_t launch_rank(Tables t, int gen_off, int final, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Breed: one workgroup per slot c of the next population.
+// Breed: slot c of the next population.
 //   c < E : copy elite c unchanged (elitism).
 //   c >= E: parents A, B = winners of two tournaments of two on draw
 //           (0, c, g, SELECT); crossover iff word 0 of (0, c, g, CROSSOVER)
@@ -366,9 +385,7 @@ hipError_t launch_rank(Tables t, int gen_off, int final, hipStream_t s) {
 //           of (1 + j/128, c, g, CROSSOVER); mutation of gene j iff word
 //           2(j%2) of (j/2, c, g, MUTATION) < p_mut, new label from the
 //           next word.
-// Each thread takes gene pairs (j, j+1) so one mutation draw covers two
-// genes; one wave covers 128 genes, so the crossover-bit draw is the same
-// for the whole wave.
+// A thread takes gene pairs (j, j+1) so one mutation draw covers two genes.
 __device__ __forceinline__ int tournament2(const double *f, int a, int b) {
     const double fa = f[a], fb = f[b];
     return ranks_before(fa, a, fb, b) ? a : b;
@@ -497,109 +514,12 @@ __device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which) {
     return sus_pick(d, k, n, u, W);
 }
 
-// Genes of child c from parents A and B (crossover and mutation), written to
-// out by `width` threads with index tid: a whole workgroup or one wave. Every
-// draw is keyed by gene pair, so the child does not depend on the split. One
-// wave covers 128 consecutive genes per pass in either split, so the
-// crossover-bit draw is the same for the whole wave.
-__device__ __forceinline__ void breed_genes(const InstDesc &d, int c, uint32_t gen, const int32_t *__restrict__ ra,
-                                            const int32_t *__restrict__ rb, int32_t *__restrict__ out, int tid,
-                                            int width) {
-    const int N = d.N;
-    const bool cross = draw(0u, (uint32_t)c, gen, kTagXov, d.inst_id, d.seed).x < d.p_cross;
-    const uint32_t pm = d.p_mut;
-    const int npair = (N + 1) >> 1;
-    for (int jp = tid; jp < npair; jp += width) {
-        const int j = 2 * jp;
-        const bool has1 = j + 1 < N;
-        int32_t g0 = ra[j];
-        int32_t g1 = has1 ? ra[j + 1] : 0;
-        if (cross) {
-            const uint32_t q = __builtin_amdgcn_readfirstlane((uint32_t)(j >> 7));
-            const U4 xb = draw(1u + q, (uint32_t)c, gen, kTagXov, d.inst_id, d.seed);
-            const int r = j & 127;
-            const int wsel = r >> 5;
-            const uint32_t word = wsel == 0 ? xb.x : wsel == 1 ? xb.y : wsel == 2 ? xb.z : xb.w;
-            const int bit = r & 31;
-            if ((word >> bit) & 1u) g0 = rb[j];
-            if (has1 && ((word >> (bit + 1)) & 1u)) g1 = rb[j + 1];
-        }
-        const U4 m = draw((uint32_t)jp, (uint32_t)c, gen, kTagMut, d.inst_id, d.seed);
-        if (m.x < pm) g0 = (int32_t)scale_u32(m.y, (uint32_t)N);
-        if (m.z < pm) g1 = (int32_t)scale_u32(m.w, (uint32_t)N);
-        out[j] = g0;
-        if (has1) out[j + 1] = g1;
-    }
-}
-
-// With `fold` set (no instance selects by SUS or can stop early), the breed
-// workgroups of the elite slots rank the population themselves: workgroup
-// c < E finds the c-th ranked individual and copies it, and workgroup 0 also
-// keeps the termination state and writes the statistics row, so the rank
-// kernel is not launched between fitness and breeding. Children need only the
-// fitness values (tournaments), so the result is the same as with the rank
-// kernel before breed.
-__global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold) {
-    const int g = blockIdx.x;
-    if (g >= t.inds[t.n_inst]) return;                     // the grid may exceed the total (capacity-sized graph)
-    const int k = find_inst(t.inds, t.n_inst, g);
-    const InstDesc &d = t.desc[k];
-    if (inst_stopped(d)) return;                           // set by this generation's rank
-    const int N = d.N, P = d.P, E = d.E;
-    const int c = g - t.inds[k];
-    const int32_t *__restrict__ src = d.pop[parity];
-    int32_t *__restrict__ out = d.pop[parity ^ 1] + (size_t)c * N;
-
-    // Ranking work of the fold: workgroup c < E finds the c-th ranked individual;
-    // workgroup 0 (an elite slot, or child 0 when E = 0) keeps the termination
-    // state and writes the statistics row. The condition is uniform per workgroup.
-    int ec = -1;
-    if (fold && (c < E || (c == 0 && (d.term || d.stats)))) {
-        __shared__ RankLds sh;
-        RankBlock<4> rb{d.fitness, P, sh};                    // few registers: the child slots share the kernel
-        rb.load();
-        pga_term_state st{};
-        if (c == 0 && d.term && threadIdx.x == 0) st = *d.term;
-        Cand pick{-INFINITY, 0};
-        const Cand best = rb.rank_and_stats(d, c + 1, gen_off, c == 0 && d.stats, [&](int, Cand b) { pick = b; });
-        if (c == 0 && d.term && threadIdx.x == 0) {
-            if (gen_off == 0) st.call_gens = 0;
-            term_update(d, st, best.f, 0, gen_off == 0);
-        }
-        ec = pick.i;
-    }
-    if (c < E) {
-        if (!fold) ec = d.elite[c];
-        const int32_t *__restrict__ e = src + (size_t)ec * N;
-        for (int j = threadIdx.x; j < N; j += 256) out[j] = e[j];
-        return;
-    }
-    const uint32_t gen = d.gen0 + (uint32_t)gen_off;
-    int A, B;
-    if (d.selection == PGA_SELECT_SUS) {
-        __shared__ int par_s[2];
-        if (threadIdx.x < 2) par_s[threadIdx.x] = sus_parent(d, c, gen, threadIdx.x);
-        __syncthreads();
-        A = par_s[0];
-        B = par_s[1];
-    } else {
-        const double *__restrict__ f = d.fitness;
-        const U4 sel = draw(0u, (uint32_t)c, gen, kTagSel, d.inst_id, d.seed);
-        A = tournament2(f, (int)scale_u32(sel.x, (uint32_t)P), (int)scale_u32(sel.y, (uint32_t)P));
-        B = tournament2(f, (int)scale_u32(sel.z, (uint32_t)P), (int)scale_u32(sel.w, (uint32_t)P));
-    }
-    breed_genes(d, c, gen, src + (size_t)A * N, src + (size_t)B * N, out, threadIdx.x, 256);
-}
-
-// The same step with one wave per slot of the next population (four slots per
-// workgroup, possibly of different instances): at small N a workgroup per slot
-// leaves most of its threads idle and bounds the slots in flight by the
-// workgroup limit per compute unit. With `fold` set, workgroup k < n_inst
-// ranks instance k instead (the same RankBlock code and thread count as the
-// rank kernel, so the statistics are the same bits), copies its elites and
-// keeps its termination state and statistics row, and the slot workgroups
-// follow; otherwise the elite slots copy the individuals the rank kernel
-// listed.
+// Ranking by the breed launch ("fold": no instance selects by SUS or can stop
+// early): workgroup k < n_inst ranks instance k (the RankBlock code and thread
+// count of the rank kernel, so the statistics are the same bits), copies its
+// elites and keeps its termination state and statistics row, beside the
+// workgroups that make the children, which need only the fitness values
+// (tournaments): no rank launch between fitness and breeding.
 __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, int gen_off) {
     __shared__ RankLds sh;
     const InstDesc &d = t.desc[k];
@@ -629,34 +549,42 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
         const int32_t *__restrict__ e = src + (size_t)b.i * N;
         int32_t *__restrict__ o = dst + (size_t)r * N;
         for (int j = threadIdx.x; j < N; j += kRankThreads) o[j] = e[j];
+    }, [&] {
+        if (E <= kQ)
+            for (int j = threadIdx.x; j < N; j += kRankThreads) {
+                int32_t v[kQ];
+#pragma unroll
+                for (int q = 0; q < kQ; ++q)
+                    if (q < E) v[q] = src[(size_t)eq[q] * N + j];
+#pragma unroll
+                for (int q = 0; q < kQ; ++q)
+                    if (q < E) dst[(size_t)q * N + j] = v[q];
+            }
     });
     if (d.term && threadIdx.x == 0) {
         if (gen_off == 0) st.call_gens = 0;
         term_update(d, st, best.f, 0, gen_off == 0);
     }
-    if (E <= kQ)
-        for (int j = threadIdx.x; j < N; j += kRankThreads) {
-            int32_t v[kQ];
-#pragma unroll
-            for (int q = 0; q < kQ; ++q)
-                if (q < E) v[q] = src[(size_t)eq[q] * N + j];
-#pragma unroll
-            for (int q = 0; q < kQ; ++q)
-                if (q < E) dst[(size_t)q * N + j] = v[q];
-        }
 }
 
-// The slot workgroups are taken XCD by XCD: the x-th eighth of them runs on XCD
-// x (workgroup i goes to XCD i mod 8), so the parents an XCD reads come from a
-// few instances' populations and stay in its L2.
-// GL lanes per slot: 64 (one wave), or 32 and 16 when the launch's largest N
-// is at most 2 GL genes (a lane makes two genes per pass), so that a wave
-// breeds 64 / GL children at the paper's sizes (N = 18) instead of keeping 55
-// of its 64 lanes idle. The lanes of one slot share its instance and child,
-// so their control flow is the same.
-template <int GL>
-__global__ __launch_bounds__(256) void k_breed_wave(Tables t, int parity, int gen_off, int fold, int slot_wgs) {
-    constexpr int S = 64 / GL;                             // slots per wave
+// A workgroup makes the slots [c0, c0 + chr) of one instance (chr a power of
+// two), gl lanes per slot and 256 / gl slots at a time (breed_split). No draw is
+// made twice:
+//   1. the draws that all genes of a child share (its parents, whether it
+//      crosses, a 128-bit crossover word per 128 genes), one per thread over the
+//      children of the workgroup, into LDS (made by every lane of a child's
+//      wave they were five of its eight draws at N = 272);
+//   2. per gene pair the mutation draw and the two parents' genes; with 16
+//      lanes per slot a pass of a wave serves four slots, and the last pass of a
+//      slot leaves few lanes idle (136 pairs: 9 passes of 16, against 3 of 64).
+// Every draw is keyed by child and gene pair, so a child is the same bits
+// whatever gl and chr are. Large launches are near the memory: 256 instances of
+// N ~ U{32..512} read two parents per child and write it, 430 MB in 133 us (3.2
+// TB/s; 198 us with a wave per slot and all draws in it). (Loading the next
+// pass's genes before the draw: 139 us, and no gain in small launches.)
+typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));
+__global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold, BreedShape shape) {
+    extern __shared__ __align__(16) uint32_t blds[];       // [parent A, B | crosses][chr], words [4 nq][chr]
     int wg = blockIdx.x;
     if (fold) {
         if (wg < t.n_inst) {
@@ -665,62 +593,104 @@ __global__ __launch_bounds__(256) void k_breed_wave(Tables t, int parity, int ge
         }
         wg -= t.n_inst;
     }
-    wg = (wg % kXcds) * (slot_wgs / kXcds) + wg / kXcds;  // slot_wgs is a multiple of 8
-    const int lane = threadIdx.x & 63, sub = lane / GL, gl = lane % GL;
-    int g = (4 * wg + (int)(threadIdx.x >> 6)) * S + sub;
-    if constexpr (GL == 64) g = __builtin_amdgcn_readfirstlane(g);
-    if (g >= t.inds[t.n_inst]) return;                     // the grid may exceed the total (capacity-sized graph)
-    const int k = find_inst(t.inds, t.n_inst, g);
+    const int total = t.breeds[t.n_inst];
+    if (wg >= total) return;                               // the grid may exceed the total (capacity-sized graph)
+    // runs of workgroups of up to 512 children on one XCD: its L2 holds their instance's parents
+    const int run = shape.run, run8 = wg / (kXcds * run), in8 = wg % (kXcds * run);
+    if ((run8 + 1) * kXcds * run <= total) wg = run8 * kXcds * run + in8 % kXcds * run + in8 / kXcds;
+    const int k = find_inst(t.breeds, t.n_inst, wg);
     const InstDesc &d = t.desc[k];
     if (inst_stopped(d)) return;                           // set by this generation's rank
-    const int N = d.N, P = d.P, E = d.E;
-    const int c = g - t.inds[k];
+    const int N = d.N, P = d.P, E = d.E, tid = threadIdx.x;
+    const BreedSplit split = breed_split(N, shape);
+    const int chr = split.chr, gl_n = split.gl, c0 = (wg - t.breeds[k]) * chr;
     const int32_t *__restrict__ src = d.pop[parity];
-    int32_t *__restrict__ out = d.pop[parity ^ 1] + (size_t)c * N;
-    if (c < E) {
-        if (fold) return;                                  // copied by the instance's ranking workgroup
-        const int32_t *__restrict__ e = src + (size_t)d.elite[c] * N;
-        for (int j = gl; j < N; j += GL) out[j] = e[j];
-        return;
-    }
     const uint32_t gen = d.gen0 + (uint32_t)gen_off;
-    int A, B;
-    if (d.selection == PGA_SELECT_SUS) {
-        int pick = 0;
-        if (gl < 2) pick = sus_parent(d, c, gen, gl);
-        if constexpr (GL == 64) {
-            A = __builtin_amdgcn_readlane(pick, 0);
-            B = __builtin_amdgcn_readlane(pick, 1);
-        } else {                                           // from the slot's first two lanes
-            A = __shfl(pick, sub * GL, 64);
-            B = __shfl(pick, sub * GL + 1, 64);
+    const bool sus = d.selection == PGA_SELECT_SUS;
+    const int nq = (N + 127) >> 7;
+    int32_t *par = (int32_t *)blds;
+    uint32_t *crosses = blds + 2 * chr, *words = blds + 3 * chr;
+
+    {
+        const int ci = tid & (chr - 1), c = c0 + ci;
+        const int kinds = (sus ? 3 : 2) + nq;              // parents (one thread, or one each with SUS), cross, words
+        for (int x = tid / chr; x < kinds; x += 256 / chr) {
+            if (c >= P || c < E) continue;
+            if (sus && x < 2) {
+                par[x * chr + ci] = sus_parent(d, c, gen, x);
+                continue;
+            }
+            const int y = sus ? x - 1 : x;                 // 0 parents, 1 cross, 2 + q: word q
+            const U4 w = draw(y < 2 ? 0u : (uint32_t)(y - 1), (uint32_t)c, gen, y == 0 ? kTagSel : kTagXov, d.inst_id,
+                              d.seed);
+            if (y == 0) {
+                const double *__restrict__ f = d.fitness;
+                par[ci] = tournament2(f, (int)scale_u32(w.x, (uint32_t)P), (int)scale_u32(w.y, (uint32_t)P));
+                par[chr + ci] = tournament2(f, (int)scale_u32(w.z, (uint32_t)P), (int)scale_u32(w.w, (uint32_t)P));
+            } else if (y == 1) {
+                crosses[ci] = w.x < d.p_cross ? 1u : 0u;
+            } else {
+                uint32_t *o = words + (size_t)(4 * (y - 2)) * chr + ci;
+                o[0] = w.x;
+                o[chr] = w.y;
+                o[2 * chr] = w.z;
+                o[3 * chr] = w.w;
+            }
         }
-    } else {
-        const double *__restrict__ f = d.fitness;
-        const U4 sel = draw(0u, (uint32_t)c, gen, kTagSel, d.inst_id, d.seed);
-        A = tournament2(f, (int)scale_u32(sel.x, (uint32_t)P), (int)scale_u32(sel.y, (uint32_t)P));
-        B = tournament2(f, (int)scale_u32(sel.z, (uint32_t)P), (int)scale_u32(sel.w, (uint32_t)P));
     }
-    breed_genes(d, c, gen, src + (size_t)A * N, src + (size_t)B * N, out, gl, GL);
+    __syncthreads();
+
+    const int gl = tid & (gl_n - 1), npair = (N + 1) >> 1;
+    const uint32_t pm = d.p_mut;
+    for (int ci = tid / gl_n; ci < chr; ci += 256 / gl_n) {
+        const int c = c0 + ci;
+        if (c >= P) break;
+        int32_t *__restrict__ out = d.pop[parity ^ 1] + (size_t)c * N;
+        if (c < E) {
+            if (fold) continue;                            // copied by the instance's ranking workgroup
+            const int32_t *__restrict__ e = src + (size_t)d.elite[c] * N;
+            for (int j = gl; j < N; j += gl_n) out[j] = e[j];
+            continue;
+        }
+        const int32_t *__restrict__ ra = src + (size_t)par[ci] * N;
+        const int32_t *__restrict__ rb = src + (size_t)par[chr + ci] * N;
+        const bool cross = crosses[ci] != 0;
+        for (int jp = gl; jp < npair; jp += gl_n) {
+            const int j = 2 * jp;
+            const bool has1 = j + 1 < N;
+            // genes j, j + 1 (the last pair of an odd N: gene j twice)
+            auto pair = [&](const int32_t *r) -> gene2 {
+                if (has1) return *(const PGA_GLOBAL gene2 *)(r + j);
+                const int32_t g = gld(r + j);
+                return gene2{g, g};
+            };
+            gene2 g = pair(ra);
+            if (cross) {
+                const gene2 h = pair(rb);
+                const uint32_t w = words[(size_t)(j >> 5) * chr + ci] >> (j & 31);
+                if (w & 1u) g.x = h.x;
+                if (w & 2u) g.y = h.y;
+            }
+            const U4 m = draw((uint32_t)jp, (uint32_t)c, gen, kTagMut, d.inst_id, d.seed);
+            if (m.x < pm) g.x = (int32_t)scale_u32(m.y, (uint32_t)N);
+            if (m.z < pm) g.y = (int32_t)scale_u32(m.w, (uint32_t)N);
+            if (has1) *(PGA_GLOBAL gene2 *)(out + j) = g;
+            else gst(out + j, g.x);
+        }
+    }
 }
 
-hipError_t launch_breed(Tables t, int total_inds, int parity, int gen_off, int fold, int by_wave, int max_n,
+hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int max_n,
                         hipStream_t s) {
-    if (total_inds <= 0) return hipSuccess;
-    if (by_wave) {
-        const int gl = max_n <= 32 ? 16 : max_n <= 64 ? 32 : 64;   // lanes per slot
-        const int per_wg = 4 * (64 / gl);                          // slots per workgroup
-        const int slot_wgs = ((total_inds + per_wg - 1) / per_wg + kXcds - 1) / kXcds * kXcds;
-        const dim3 grid((fold ? t.n_inst : 0) + slot_wgs);
-        if (gl == 16)
-            hipLaunchKernelGGL(k_breed_wave<16>, grid, dim3(256), 0, s, t, parity, gen_off, fold, slot_wgs);
-        else if (gl == 32)
-            hipLaunchKernelGGL(k_breed_wave<32>, grid, dim3(256), 0, s, t, parity, gen_off, fold, slot_wgs);
-        else
-            hipLaunchKernelGGL(k_breed_wave<64>, grid, dim3(256), 0, s, t, parity, gen_off, fold, slot_wgs);
+    const int grid = (fold ? t.n_inst : 0) + blocks;
+    if (grid <= 0) return hipSuccess;
+    // the shared draws of the largest split (slots fall as N rises, words rise)
+    size_t words = 0;
+    for (int n = 1; n < 2 * max_n; n *= 2) {
+        const int N = n < max_n ? n : max_n;
+        words = std::max(words, (size_t)breed_split(N, b).chr * (3 + 4 * (size_t)((2 * N + 127) / 128)));
     }
-    else
-        hipLaunchKernelGGL(k_breed, dim3(total_inds), dim3(256), 0, s, t, parity, gen_off, fold);
+    hipLaunchKernelGGL(k_breed, dim3(grid), dim3(256), sizeof(uint32_t) * words, s, t, parity, gen_off, fold, b);
     return hipGetLastError();
 }
 

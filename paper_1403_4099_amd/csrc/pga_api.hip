@@ -170,7 +170,8 @@ int bucket(int x) {
 }
 
 // ---- workspace layout ----------------------------------------------------------
-// [InstDesc x n][prefix tiles n+1][prefix inds n+1][prefix evals n+1][dense list counters kListCounters int32]
+// [InstDesc x n][prefix tiles n+1][prefix inds n+1][prefix evals n+1][prefix breeds n+1]
+// [dense list counters kListCounters int32]
 // [dense list entries: list_words(ceil(bucket(sum of P) / 4)) int32]
 // then per instance: [wsum P x N doubles][elite PGA_E_MAX int32]
 // and, for the BF16x2 form, [hi * 2^125 ld x ld][lo * 2^125 ld x ld] (bf16),
@@ -190,7 +191,7 @@ Layout make_layout(const int32_t *Ns, const int32_t *Ps, int n, int form, const 
     Layout L;
     L.desc_off = 0;
     L.pre_off = align_up(sizeof(InstDesc) * (size_t)n, 256);
-    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (3 * ((size_t)n + 1) + (size_t)kListCounters), 256);
+    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (4 * ((size_t)n + 1) + (size_t)kListCounters), 256);
     L.list_off = L.inst_off;
     int sum_p = 0;
     for (int k = 0; k < n; ++k) sum_p += Ps[k];
@@ -230,7 +231,8 @@ Tables tables_at(void *ws, const Layout &L, int n) {
     t.tiles = (const int32_t *)(b + L.pre_off);
     t.inds = t.tiles + (n + 1);
     t.evals = t.tiles + 2 * (n + 1);
-    t.sq = (int32_t *)(b + L.pre_off) + 3 * (n + 1);
+    t.breeds = t.tiles + 3 * (n + 1);
+    t.sq = (int32_t *)(b + L.pre_off) + 4 * (n + 1);
     t.sq_list = (int32_t *)(b + L.list_off);
     t.n_inst = n;
     return t;
@@ -245,6 +247,8 @@ struct Shape {
     double frac;         // cluster-pair route limit (0: off; then every route pointer is null)
     int evals;           // cluster-pair workgroups
     size_t lds;          // LDS of one of them
+    BreedShape breed;
+    int breeds;          // breed workgroups
 };
 
 // Tiles of the pair-sum: none for the instances that the cluster-pair kernel always evaluates.
@@ -282,12 +286,11 @@ hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, in
         if ((e = run_fitness(t, sh, form, parity, status, s)) != hipSuccess) return e;
         // Without SUS or an early stop, breeding needs the ranking only for the elite
         // slots, and the breed kernel does it itself (fold); otherwise rank first.
-        const int by_wave = sh.max_n <= kBreedWaveMaxN && sh.inds >= kManyInds ? 1 : 0;
         const int fold = (!sh.sus && !sh.stop) ? 1 : 0;
         if (!fold && (e = timed(3, s, [&] { return launch_rank(t, k, 0, s); })) != hipSuccess) return e;
         if (sh.sus && (e = timed(8, s, [&] { return launch_sus(t, sh.max_p, s); })) != hipSuccess) return e;
         if ((e = timed(4, s, [&] {
-                 return launch_breed(t, sh.inds, parity, k, fold, by_wave, sh.max_n, s);
+                 return launch_breed(t, sh.breeds, sh.breed, parity, k, fold, sh.max_n, s);
              })) != hipSuccess)
             return e;
     }
@@ -303,12 +306,12 @@ hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, in
 struct GraphKey {
     void *ws;
     int32_t *status;
-    int n_inst, form, G, tiles, inds, evals, max_n, ipg, order, kind, max_p, sus, stop;
+    int n_inst, form, G, tiles, inds, evals, breeds, max_n, ipg, order, kind, max_p, sus, stop;
     size_t lds;
     double frac;
     bool operator<(const GraphKey &o) const {
-        return std::tie(ws, status, n_inst, form, G, tiles, inds, evals, max_n, ipg, order, kind, max_p, sus, stop, lds,
-                        frac) < std::tie(o.ws, o.status, o.n_inst, o.form, o.G, o.tiles, o.inds, o.evals, o.max_n,
+        return std::tie(ws, status, n_inst, form, G, tiles, inds, evals, breeds, max_n, ipg, order, kind, max_p, sus, stop, lds,
+                        frac) < std::tie(o.ws, o.status, o.n_inst, o.form, o.G, o.tiles, o.inds, o.evals, o.breeds, o.max_n,
                                          o.ipg, o.order, o.kind, o.max_p, o.sus, o.stop, o.lds, o.frac);
     }
 };
@@ -767,10 +770,10 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     char *hb = (char *)ctx->staging;
     InstDesc *hd = (InstDesc *)(hb + L.desc_off);
     int32_t *pf = (int32_t *)(hb + L.pre_off);
-    int32_t *pi = pf + (nb + 1), *pe = pi + (nb + 1);
-    pf[0] = pi[0] = pe[0] = 0;
-    memset(pe + (nb + 1), 0, sizeof(int32_t) * kListCounters);     // the dense lists start empty
-    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0};
+    int32_t *pi = pf + (nb + 1), *pe = pi + (nb + 1), *pb = pe + (nb + 1);
+    pf[0] = pi[0] = pe[0] = pb[0] = 0;
+    memset(pb + (nb + 1), 0, sizeof(int32_t) * kListCounters);     // the dense lists start empty
+    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0, BreedShape{0, 0, 0}, 0};
     int total_p = 0;
     for (int k = 0; k < n_inst; ++k) {
         sh.max_n = std::max(sh.max_n, (int)inst[k].N);
@@ -782,6 +785,8 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     sh.max_n = bucket(sh.max_n);
     sh.max_p = bucket(sh.max_p);
     sh.v = variant_at(form, pick_variant(form, sh.max_n, total_p));
+    sh.inds = bucket(total_p);                       // launch sizes; the kernels stop at the real totals
+    sh.breed = breed_shape(sh.inds);                 // (a function of key values: part of no key itself)
     for (int k = 0; k < n_inst; ++k) {
         const pga_instance &I = inst[k];
         InstDesc d{};
@@ -825,6 +830,7 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         pf[k + 1] = pf[k] + dense_tiles(I.N, I.P, sh.v, sh.frac);
         pi[k + 1] = pi[k] + I.P;
         pe[k + 1] = pe[k] + eval_blocks(I.N, I.P);
+        pb[k + 1] = pb[k] + breed_blocks(I.N, I.P, sh.breed);
         sh.lds = std::max(sh.lds, eval_lds(I.N));
     }
     for (int k = n_inst; k < nb; ++k) {              // padding slots: no individuals, no tiles
@@ -832,11 +838,12 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         pf[k + 1] = pf[k];
         pi[k + 1] = pi[k];
         pe[k + 1] = pe[k];
+        pb[k + 1] = pb[k];
     }
     sh.evals = bucket(pe[nb]);
+    sh.breeds = bucket(pb[nb]);
     sh.lds = align_up(sh.lds, 2048);                 // part of a captured graph's key: few values
-    sh.tiles = bucket(pf[nb]);                       // launch sizes; the kernels stop at the real totals
-    sh.inds = bucket(pi[nb]);
+    sh.tiles = bucket(pf[nb]);
     HIP_TRY(hipMemcpyAsync(ws, ctx->staging, head, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(ctx->upload_done, s));
     ctx->upload_pending = true;
@@ -851,7 +858,7 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         HIP_TRY(run_generations(t, sh, form, generations, status, s));
         return PGA_OK;
     }
-    GraphKey key{ws, status, nb, form, generations, sh.tiles, sh.inds, sh.evals, sh.max_n, sh.v.ipg, sh.v.order,
+    GraphKey key{ws, status, nb, form, generations, sh.tiles, sh.inds, sh.evals, sh.breeds, sh.max_n, sh.v.ipg, sh.v.order,
                  sh.v.kind, sh.max_p, sh.sus, sh.stop, sh.lds, sh.frac};
     auto it = ctx->graphs.find(key);
     if (it == ctx->graphs.end()) {

@@ -47,6 +47,7 @@ struct Tables {
     const int32_t *tiles;       // prefix of pair-sum tiles (of the kernel variant in use)
     const int32_t *inds;        // prefix of individuals
     const int32_t *evals;       // prefix of cluster-pair workgroups (eval_blocks)
+    const int32_t *breeds;      // prefix of breed workgroups (of the launch's BreedShape)
     int32_t *sq;                // dense list counters (see list_count)
     int32_t *sq_list;           // dense list entries (see list_entry)
     int32_t n_inst;
@@ -224,6 +225,60 @@ __device__ __forceinline__ U4 draw(uint32_t blk, uint32_t who, uint32_t gen, uin
 // floor(w * m / 2^32)
 __device__ __forceinline__ uint32_t scale_u32(uint32_t w, uint32_t m) { return __umulhi(w, m); }
 
+// ---- lane groups ------------------------------------------------------------
+// Cross-lane steps without LDS: rotations within rows of 16 lanes (DPP), and the swaps of
+// neighbouring rows and of the wave's halves.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+constexpr int kRor8 = 0x128, kRor4 = 0x124, kRor2 = 0x122, kRor1 = 0x121;   // row_ror:n
+constexpr int kQuad2 = 0x4E, kQuad1 = 0xB1;                                  // quad_perm [2,3,0,1], [1,0,3,2]
+
+template <int GL, class Op>                       // over GL <= 64 lanes; op commutative and associative
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
+    v = op(v, dpp<kRor8>(v));
+    v = op(v, dpp<kRor4>(v));
+    v = op(v, dpp<kRor2>(v));
+    v = op(v, dpp<kRor1>(v));
+    if constexpr (GL >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = op(r[0], r[1]);
+    }
+    if constexpr (GL >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = op(r[0], r[1]);
+    }
+    return v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b);
+    return v + __builtin_bit_cast(double, o);
+}
+// The butterfly sum over a wave (lane l with l ^ 32, 16, 8, 4, 2, 1), in every lane: a step's sum is commutative,
+// and once the values repeat with period 8 (4) in a row, the row's rotation by 4 (2) pairs the same
+// values as the exchange. GL = 32 and 16: the sum of the group's values followed by zeros.
+template <int GL>
+__device__ __forceinline__ double group_sum(double v) {
+    auto halves = [](double x, auto swap) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const auto l = swap((uint32_t)b), h = swap((uint32_t)(b >> 32));
+        return __builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]) +
+               __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]);
+    };
+    if constexpr (GL >= 64)
+        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    if constexpr (GL >= 32)
+        v = halves(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = dpp_add<kRor8>(v);
+    v = dpp_add<kRor4>(v);
+    v = dpp_add<kQuad2>(v);
+    return dpp_add<kQuad1>(v);
+}
+
 // ---- explicit global-memory access ------------------------------------------
 // Pointers read from a descriptor are generic; the compiler then emits flat
 // loads, which count on the same wait counter as LDS operations, so a wait for
@@ -307,17 +362,35 @@ hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int par
 
 hipError_t launch_init(Tables t, int total_inds, hipStream_t s);
 hipError_t launch_rank(Tables t, int gen_off, int final, hipStream_t s);
-// by_wave: one wave per slot instead of one workgroup per slot.
-hipError_t launch_breed(Tables t, int total_inds, int parity, int gen_off, int fold, int by_wave, int max_n,
+// Shape of a breed launch: the most passes of a slot's lanes over its gene pairs (few in small
+// launches, whose time is a slot's chain of passes; many in large ones, where few lanes per
+// slot keep all of them busy), at least this many slots per workgroup, and the workgroups of a run on one XCD.
+struct BreedShape {
+    int passes, min_chr, run;
+};
+struct BreedSplit {
+    int gl, chr;             // lanes per slot, slots per workgroup: powers of two, gl chr >= 256
+};
+__host__ __device__ inline BreedSplit breed_split(int N, const BreedShape &b) {
+    const int npair = (N + 1) / 2;
+    int gl = 16;
+    while (gl < 256 && gl * b.passes < npair) gl *= 2;
+    const int chr = 256 / gl > b.min_chr ? 256 / gl : b.min_chr;
+    return BreedSplit{gl, chr};
+}
+// (us per generation at 2, 4 and 8 passes: one instance of 4096 slots, N = 1024: 74, 72, 71; ten
+// instances of 1024, N of 64 to 1024: 215, 212, 215; 131 072 slots of N ~ U{32..512}: 576 at 8, 16 and 32)
+inline BreedShape breed_shape(int inds) {
+    if (inds >= 65536) return BreedShape{16, 64, 8};
+    return BreedShape{inds >= 4096 ? 8 : 2, inds >= 16384 ? 8 : 1, 16};
+}
+inline int breed_blocks(int N, int P, const BreedShape &b) { return ceil_div(P, breed_split(N, b).chr); }
+hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int max_n,
                         hipStream_t s);
 // Launches of at least kManyInds individuals (more than the chip holds at a
-// workgroup each) take the per-individual kernels' throughput forms: the
-// listed finish and one wave per breed slot. Smaller ones (one instance of a
-// few thousand) are latency-bound: there a workgroup per slot finishes sooner.
+// workgroup each) run the finish over the dense list; smaller ones a workgroup
+// per individual.
 constexpr int kManyInds = 8192;
-// Largest N bred with one wave per slot: above it a workgroup per slot keeps more
-// genes of one child in flight.
-constexpr int kBreedWaveMaxN = 1024;
 hipError_t launch_sus(Tables t, int max_p, hipStream_t s);
 hipError_t launch_copy_back(Tables t, int total_inds, int G, hipStream_t s);
 // Records a hipError_t for pga_last_hip_error() on this thread.
