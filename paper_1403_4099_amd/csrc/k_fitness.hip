@@ -626,10 +626,13 @@ constexpr int kSmallMaxN = kRouteAllPairsMaxN;     // evaluated here even when a
 __host__ __device__ constexpr size_t pad16(size_t b) { return (b + 15) / 16 * 16; }
 __host__ __device__ constexpr int eval_lanes(int N) { return N <= 32 ? 16 : N <= 64 ? 32 : N <= 512 ? 64 : 256; }
 // LDS of one individual: n_s, then the items, uint32[n] | a cluster's last stock, then its
-// list index, uint32[n], then csum int64[n / 2 + 1] | prev uint16[n + 1] | list uint32[n / 2 + 1].
-// 12 n bytes: at N = 512 six workgroups per CU.
+// list index, uint32[n], then (N > 512: beside it) csum int64[n / 2 + 1] | prev uint16[n + 1] |
+// list uint32[n / 2 + 1]. 12 n bytes: at N = 512 six workgroups per CU; 16 n above.
+__host__ __device__ constexpr size_t eval_csum_off(int n) {
+    return pad16(4 * (size_t)n) + (eval_lanes(n) == 256 ? pad16(4 * (size_t)n) : 0);
+}
 __host__ __device__ constexpr size_t eval_bytes(int n) {
-    return pad16(4 * (size_t)n) + pad16(8 * ((size_t)n / 2 + 1)) + pad16(2 * ((size_t)n + 1)) +
+    return eval_csum_off(n) + pad16(8 * ((size_t)n / 2 + 1)) + pad16(2 * ((size_t)n + 1)) +
            pad16(4 * ((size_t)n / 2 + 1));
 }
 constexpr uint32_t kNoCluster = 0xFFFFu;           // list index of a label with n_s <= 1
@@ -802,13 +805,15 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
     if (GL >= 64 && !live) return;
     const int pc = min(p, P - 1);
     unsigned char *b = smem + (size_t)grp * eval_bytes(N);
-    uint32_t *cnt = (uint32_t *)b;          b += pad16(4 * (size_t)N);
-    uint32_t *last = (uint32_t *)b;
+    uint32_t *cnt = (uint32_t *)b;
+    uint32_t *last = (uint32_t *)(b + pad16(4 * (size_t)N));
+    b += eval_csum_off(N);
     unsigned long long *csum = (unsigned long long *)b;   b += pad16(8 * ((size_t)N / 2 + 1));
     uint16_t *prev = (uint16_t *)b;         b += pad16(2 * ((size_t)N + 1));
     uint32_t *lst = (uint32_t *)b;
-    int *ired = (int *)(smem + eval_bytes(N));       // kBlock: 16 ints, then 8 doubles
-    double *red = (double *)(ired + 16);
+    // kBlock: per wave T | max n_s | lists per label quarter (two words) | items, flags; then 4 doubles
+    uint32_t *ired = (uint32_t *)(smem + eval_bytes(N));
+    double *red = (double *)(ired + 20);
     auto sync = [&]() {
         if constexpr (kBlock) __syncthreads();
         else wave_lds_sync();
@@ -818,10 +823,6 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         const uint64_t m = __ballot(x);
         if constexpr (WL == 64) return m;
         else return (m >> (lane & ~(WL - 1))) & ((1ull << WL) - 1ull);
-    };
-    auto any = [&](bool x) -> bool {
-        if constexpr (kBlock) return __syncthreads_or(x) != 0;
-        else return vote(x) != 0;
     };
     const int wl = lane & (WL - 1);
     const uint64_t below = (1ull << wl) - 1ull;
@@ -851,10 +852,18 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
             }
         }
     }
-    if (gl == 0) prev[N] = (uint16_t)N;
-    const bool bad_label = any(badl);                // closes the writes above for a workgroup
-    if constexpr (!kBlock) sync();
-    if (bad_label && live) {                         // as the finish: labels outside [0, N)
+    if (gl == 0) {
+        prev[N] = (uint16_t)N;
+        if constexpr (kBlock) ired[16] = ired[17] = ired[18] = 0;   // items, a label out of range, an entry out of range
+    }
+    sync();
+    bool bad_label = false;
+    if constexpr (kBlock) {
+        if (badl) ired[17] = 1;                      // read after the next barrier
+    } else {
+        bad_label = vote(badl) != 0;
+    }
+    auto invalid = [&]() {                           // as the finish: labels outside [0, N)
         if (gl == 0) {
             gst(d.route + p, 0);
             d.fitness[p] = -INFINITY;
@@ -867,13 +876,18 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
             if (d.n_s_out) gst(d.n_s_out + (size_t)p * N + s, 0);
             if (d.c_s_out) gst(d.c_s_out + (size_t)p * N + s, 0.0);
         }
+    };
+    if constexpr (!kBlock) {
+        if (bad_label && live) invalid();
+        if (GL >= 64 && bad_label) return;
     }
-    if (GL >= 64 && bad_label) return;
     const bool good = live && !bad_label;
 
     // ---- n_s, pair count, chains
     uint32_t T = 0, nmax = 0;
     uint32_t has = 0;                                // bit u: the slot's stock has a predecessor
+    const int QN = (N + NW - 1) / NW;                // labels per wave of a workgroup
+    uint32_t ql = 0, qh = 0;                         // kBlock: labels that reach two stocks here, by quarter (16 bits each)
 #pragma unroll
     for (int u = 0; u < SL; ++u) {
         if (u >= nu) break;
@@ -883,22 +897,46 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
             const uint32_t pv = atomicExch(&last[lr[u]], (uint32_t)j);
             T += old;
             nmax = max(nmax, old + 1);
+            if constexpr (kBlock) {
+                if (old == 1) {
+                    const uint32_t l = lr[u];
+                    const uint32_t one = l >= (uint32_t)(2 * QN) ? (l >= (uint32_t)(3 * QN) ? 0x10000u : 1u)
+                                                                 : (l >= (uint32_t)QN ? 0x10000u : 1u);
+                    if (l >= (uint32_t)(2 * QN)) qh += one;
+                    else ql += one;
+                }
+            }
             prev[j] = (uint16_t)pv;
             has |= (pv < (uint32_t)N ? 1u : 0u) << u;
         }
     }
     nmax = group_reduce<WL>(nmax, [](uint32_t a, uint32_t c) { return max(a, c); });
     if constexpr (GL >= 64) T = group_reduce<WL>(T, [](uint32_t a, uint32_t c) { return a + c; });
+    int nl = 0, base = 0;                            // list entries, and this wave's first
     if constexpr (kBlock) {
+        const auto add = [](uint32_t a, uint32_t c) { return a + c; };
+        ql = group_reduce<64>(ql, add);
+        qh = group_reduce<64>(qh, add);
         if (wl == 0) {
-            ired[wv] = (int)T;
-            ired[4 + wv] = (int)nmax;
+            ired[wv] = T;
+            ired[4 + wv] = nmax;
+            ired[8 + wv] = ql;
+            ired[12 + wv] = qh;
         }
     }
     sync();
     if constexpr (kBlock) {
-        T = (uint32_t)(ired[0] + ired[1] + ired[2] + ired[3]);
-        nmax = (uint32_t)max(max(ired[4], ired[5]), max(ired[6], ired[7]));
+        if (ired[17]) {
+            invalid();
+            return;                                  // uniform
+        }
+        T = ired[0] + ired[1] + ired[2] + ired[3];
+        nmax = max(max(ired[4], ired[5]), max(ired[6], ired[7]));
+        ql = ired[8] + ired[9] + ired[10] + ired[11];
+        qh = ired[12] + ired[13] + ired[14] + ired[15];
+        const int q0 = (int)(ql & 0xFFFFu), q1 = (int)(ql >> 16), q2 = (int)(qh & 0xFFFFu), q3 = (int)(qh >> 16);
+        base = wv == 0 ? 0 : wv == 1 ? q0 : wv == 2 ? q0 + q1 : q0 + q1 + q2;
+        nl = q0 + q1 + q2 + q3;
     }
     if (GL >= 64 && (double)T > route_limit(N, frac)) {
         if (gl == 0) to_dense(t, d, k, p, parity, listed, slices, cap);
@@ -907,20 +945,7 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
     const int sc = 61 - (32 - __builtin_clz(nmax * nmax));   // max n_s^2 < 2^(61 - sc)
 
     // ---- clusters with n_s > 1, ascending (wave w of a workgroup: the w-th quarter of the labels)
-    const int QN = (N + NW - 1) / NW, s_lo = wv * QN, s_hi = min(N, s_lo + QN);
-    int nl = 0, base = 0;
-    if constexpr (kBlock) {
-        int own = 0;
-        for (int s0 = s_lo; s0 < s_hi; s0 += 64) own += __popcll(__ballot(s0 + wl < s_hi && cnt[s0 + wl] > 1));
-        if (wl == 0) ired[8 + wv] = own;
-        if (tid == 0) ired[12] = 0;                  // items
-        __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            if (w < wv) base += ired[8 + w];
-            nl += ired[8 + w];
-        }
-    }
+    const int s_lo = wv * QN, s_hi = min(N, s_lo + QN);
     bool badc = false;
     for (int s0 = s_lo; s0 < s_hi; s0 += WL) {
         const int s = s0 + wl;
@@ -935,6 +960,7 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         const int at = base + __popcll(m & below);
         if (n > 1) {
             lst[at] = n | ((uint32_t)s << 16);
+            if constexpr (kBlock) csum[at] = ones ? (unsigned long long)n << sc : 0ull;
         }
         if (s < s_hi) last[s] = n > 1 ? (uint32_t)at : kNoCluster;   // the chains are complete: now the list index
         base += __popcll(m);
@@ -951,7 +977,7 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
             own += __popcll(__ballot((has >> u) & 1u));
         }
         int at = 0;
-        if (wl == 0) at = atomicAdd(&ired[12], own);
+        if (wl == 0) at = (int)atomicAdd(&ired[16], (uint32_t)own);
         ni = __builtin_amdgcn_readfirstlane(at);
     }
 #pragma unroll
@@ -964,10 +990,12 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         ni += __popcll(m);
     }
     sync();
-    if constexpr (kBlock) ni = ired[12];
-    // csum takes the place of last: it starts with the sum of the diagonal
-    for (int m = gl; m < nl; m += GL) csum[m] = ones ? (unsigned long long)(lst[m] & 0xFFFFu) << sc : 0ull;
-    sync();
+    if constexpr (kBlock) {
+        ni = (int)ired[16];
+    } else {                                         // csum takes the place of last: the sum of the diagonal to start with
+        for (int m = gl; m < nl; m += GL) csum[m] = ones ? (unsigned long long)(lst[m] & 0xFFFFu) << sc : 0ull;
+        sync();
+    }
     if (!ones) {
 #pragma unroll
         for (int u = 0; u < SL; ++u) {
@@ -988,10 +1016,7 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         const uint32_t it = cnt[x];
         const int j = (int)(it & 0xFFFFu);
         double hi = 0.0, lo = 0.0;                   // the integer sum as hi 2^32 + lo, both exact
-        auto entry = [&](int i) {                    // the pair's entry; past the end of a chain: the diagonal, unused
-            const int a = i < N ? i : j;
-            return gld(C + (uint32_t)(min(a, j) * N + max(a, j)));
-        };
+        auto entry = [&](int i) { return gld(C + (uint32_t)(__mul24(min(i, j), N) + max(i, j))); };
         auto take = [&](double c) {
             badc |= !(fabs(c) <= 1.0);
             const double q = rint(c * S);
@@ -1002,17 +1027,19 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         int i = prev[j];
         do {
             const int i1 = prev[i], i2 = prev[i1], i3 = prev[i2];
+            // Past the end of its chain a lane loads nothing (an unused load still costs its line: with
+            // the diagonal entry in its place half of the L2 reads at N = 1024 were such loads).
             const bool v1 = i1 < N, v2 = i2 < N, v3 = i3 < N;
             const double c0 = entry(i);
-            if (__any(v1)) {
-                const double c1 = entry(i1);
-                if (__any(v2)) {
-                    const double c2 = entry(i2), c3 = entry(i3);
-                    take(v2 ? c2 : 0.0);
-                    take(v3 ? c3 : 0.0);
-                }
-                take(v1 ? c1 : 0.0);
+            double c1 = 0.0, c2 = 0.0, c3 = 0.0;
+            if (v1) c1 = entry(i1);
+            if (v2) c2 = entry(i2);
+            if (v3) c3 = entry(i3);
+            if (__any(v2)) {
+                take(c2);
+                take(c3);
             }
+            if (__any(v1)) take(c1);
             take(c0);
             i = prev[i3];
         } while (i < N);
@@ -1021,8 +1048,15 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
                                      (uint32_t)fma(h2, -0x1p32, lo);
         atomicAdd(&csum[it >> 16], v);
     }
-    const bool handed = any(badc);                   // (a workgroup: also closes the atomics)
-    if constexpr (!kBlock) sync();
+    bool handed = false;
+    if constexpr (kBlock) {
+        if (badc) ired[18] = 1;
+        __syncthreads();
+        handed = ired[18] != 0;
+    } else {
+        handed = vote(badc) != 0;
+        sync();
+    }
     if constexpr (GL >= 64) {
         if (handed) {
             if (gl == 0) to_dense(t, d, k, p, parity, listed, slices, cap);
@@ -1048,23 +1082,34 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         nbad = (int)group_reduce<64>((uint32_t)nbad, [](uint32_t a, uint32_t c) { return a + c; });
         if (wl == 0) {
             red[wv] = L;
-            ired[wv] = nbad;
+            ired[wv] = (uint32_t)nbad;
         }
         __syncthreads();
         for (int w = 0; w < 4; ++w) Ltot += red[w];
-        nbad = ired[0] + ired[1] + ired[2] + ired[3];
+        nbad = (int)(ired[0] + ired[1] + ired[2] + ired[3]);
     } else {
-        for (int m0 = 0; m0 < nl; m0 += GL) {        // GL < 64: one round, nl <= N / 2 <= GL
-            const int m = m0 + gl;
-            double term = 0.0;
-            bool bad = false;
-            if (m < nl) {
-                bad = !cluster_term((int)(lst[m] & 0xFFFFu), (long long)csum[m], sc, term);
-                if (bad) term = 0.0;
+        // The two logs of a term go to neighbouring lanes (half the vector work when the list is
+        // short, and in a converged population it is: 128 x 1000 individuals of N = 18, 42 to 39 us;
+        // a workgroup with four waves for one list gains nothing); the term replaces its cluster's csum.
+        double *terms = (double *)csum;
+        for (int x0 = 0; x0 < 2 * nl; x0 += GL) {
+            const int x = x0 + gl, m = x >> 1;
+            const bool in = x < 2 * nl;
+            const int n = in ? (int)(lst[m] & 0xFFFFu) : 2;
+            const double nd = (double)n, n2 = nd * nd;
+            const double c = in ? ldexp((double)(long long)csum[m], -sc) : 1.0;
+            const bool ok = c > 0.0 && c < n2;
+            const double l = log((x & 1 ? n2 - nd : nd) / (x & 1 ? n2 - c : c));
+            const double term = fma(nd - 1.0, dpp_val<kQuad1>(l), l);   // even lanes: log(n / c) + (n - 1) log(..)
+            if (in && !(x & 1)) {
+                terms[m] = ok ? term : 0.0;
+                nbad += ok ? 0 : 1;
             }
-            Ltot += group_sum<GL>(0.0 + term);
-            nbad += __popcll(vote(bad));
         }
+        nbad = (int)group_reduce<GL>((uint32_t)nbad, [](uint32_t a, uint32_t c) { return a + c; });
+        sync();
+        for (int m0 = 0; m0 < nl; m0 += GL)          // GL < 64: one round, nl <= N / 2 <= GL
+            Ltot += group_sum<GL>(0.0 + (m0 + gl < nl ? terms[m0 + gl] : 0.0));
     }
     if (gl == 0 && good && !handed) {
         gst(d.route + p, 0);

@@ -88,9 +88,7 @@ __device__ __forceinline__ Cand cand_max(Cand a, Cand b) {
 }
 template <int CTRL>
 __device__ __forceinline__ Cand cand_dpp(Cand c) {
-    const uint64_t f = __builtin_bit_cast(uint64_t, c.f);
-    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(f >> 32)) << 32) | dpp<CTRL>((uint32_t)f);
-    return Cand{__builtin_bit_cast(double, o), (int)dpp<CTRL>((uint32_t)c.i)};
+    return Cand{dpp_val<CTRL>(c.f), (int)dpp<CTRL>((uint32_t)c.i)};
 }
 template <class Swap>
 __device__ __forceinline__ Cand cand_swap(Cand c, Swap swap) {

@@ -253,10 +253,13 @@ __device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
 }
 
 template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
+__device__ __forceinline__ double dpp_val(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint64_t o = ((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b);
-    return v + __builtin_bit_cast(double, o);
+    return __builtin_bit_cast(double, ((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    return v + dpp_val<CTRL>(v);
 }
 // The butterfly sum over a wave (lane l with l ^ 32, 16, 8, 4, 2, 1), in every lane: a step's sum is commutative,
 // and once the values repeat with period 8 (4) in a row, the row's rotation by 4 (2) pairs the same
