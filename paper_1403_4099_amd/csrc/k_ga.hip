@@ -81,29 +81,29 @@ __device__ Cand block_best(Cand c, double *rf, int *ri) {
     return r;
 }
 
-// Best of a wave, in every lane: the comparison is a total order, so the lane exchanges can
-// run in any pattern (row rotations and row and half swaps here, without LDS).
-__device__ __forceinline__ Cand cand_max(Cand a, Cand b) {
-    return b.i >= 0 && (a.i < 0 || ranks_before(b.f, b.i, a.f, a.i)) ? b : a;
-}
-template <int CTRL>
-__device__ __forceinline__ Cand cand_dpp(Cand c) {
-    return Cand{dpp_val<CTRL>(c.f), (int)dpp<CTRL>((uint32_t)c.i)};
-}
-template <class Swap>
-__device__ __forceinline__ Cand cand_swap(Cand c, Swap swap) {
-    const uint64_t f = __builtin_bit_cast(uint64_t, c.f);
-    const auto l = swap((uint32_t)f), h = swap((uint32_t)(f >> 32)), i = swap((uint32_t)c.i);
-    return cand_max(Cand{__builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]), (int)i[0]},
-                    Cand{__builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]), (int)i[1]});
-}
+// Best of a wave (i < 0: no candidate), in every lane: the largest fitness, then the lowest index
+// among the lanes that hold it, by row rotations and row and half swaps without LDS. (Exchanges
+// of whole candidates with a comparison each are four times the instructions, in one chain.)
 __device__ __forceinline__ Cand wave_best(Cand c) {
-    c = cand_max(c, cand_dpp<kRor8>(c));
-    c = cand_max(c, cand_dpp<kRor4>(c));
-    c = cand_max(c, cand_dpp<kRor2>(c));
-    c = cand_max(c, cand_dpp<kRor1>(c));
-    c = cand_swap(c, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
-    return cand_swap(c, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    const auto swap16 = [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); };
+    const auto swap32 = [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); };
+    auto halves = [](double x, auto swap) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const auto l = swap((uint32_t)b), h = swap((uint32_t)(b >> 32));
+        return fmax(__builtin_bit_cast(double, ((uint64_t)h[0] << 32) | l[0]),
+                    __builtin_bit_cast(double, ((uint64_t)h[1] << 32) | l[1]));
+    };
+    const double own = c.i >= 0 ? c.f : -INFINITY;
+    double f = own;
+    f = fmax(f, dpp_val<kRor8>(f));
+    f = fmax(f, dpp_val<kRor4>(f));
+    f = fmax(f, dpp_val<kRor2>(f));
+    f = fmax(f, dpp_val<kRor1>(f));
+    f = halves(f, swap16);
+    f = halves(f, swap32);
+    const uint32_t i = group_reduce<64>(own == f ? (uint32_t)c.i : 0xFFFFFFFFu,   // -1 is the largest
+                                        [](uint32_t a, uint32_t b) { return min(a, b); });
+    return Cand{f, (int)i};
 }
 
 // Elite selection, termination state and statistics of one instance by one
@@ -121,6 +121,10 @@ constexpr int kRankCache = 16;
 struct RankLds {
     double wf[kRankWaves];
     int wi[kRankWaves];
+    double lf[kRankWaves * PGA_E_MAX];                     // each wave's best, in rank order
+    int li[kRankWaves * PGA_E_MAX];
+    int ord[PGA_E_MAX];                                    // the ranking
+    double best;
 };
 
 template <int CACHE>
@@ -164,20 +168,6 @@ struct RankBlock {
         }
         return c;
     }
-    __device__ Cand block_best(Cand c) {
-        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        c = wave_best(c);
-        if (lane == 0) {
-            sh.wf[wave] = c.f;
-            sh.wi[wave] = c.i;
-        }
-        __syncthreads();
-        Cand b{0.0, -1};
-        for (int w = 0; w < kRankWaves; ++w)
-            if (sh.wi[w] >= 0 && (b.i < 0 || ranks_before(sh.wf[w], sh.wi[w], b.f, b.i))) b = Cand{sh.wf[w], sh.wi[w]};
-        __syncthreads();
-        return b;
-    }
     // Sums of a and b over the workgroup, for thread 0.
     __device__ void block_sum2(double &a, double &b) {
         const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -194,24 +184,13 @@ struct RankBlock {
             b += (double)sh.wi[w];
         }
     }
-    // The r-th ranked individual for r = 0 .. rounds-1: calls visit(r, cand) in order.
-    template <typename F>
-    __device__ void ranked(int rounds, F &&visit) {
-        Cand prev{0.0, -1};
-        for (int r = 0; r < rounds; ++r) {
-            const Cand b = block_best(thread_best(prev));
-            visit(r, b);
-            prev = b;
-        }
-    }
-    // Ranks 0 .. rounds-1 (rounds <= kTop) from ONE read of the values: each
-    // thread keeps its kTop best in rank order, and round r takes the best of the
-    // threads' heads (the r-th ranked individual cannot be a thread's (kTop+1)-th
-    // best). The same read accumulates the statistics partials in the order
-    // write_stats takes them.
+    // Ranks 0 .. rounds-1 from one read of the values: each thread keeps its kTop
+    // best in rank order, and round r of a wave takes the best of its threads' heads. A
+    // thread whose kTop are all taken looks for its next best again (thread_best),
+    // so any number of ranks is exact; up to P = kTop kRankThreads no thread has more
+    // values than it keeps. The same read accumulates the statistics partials.
     static constexpr int kTop = 4;
-    template <typename F>
-    __device__ void ranked_once(int rounds, double &sum, double &ninv, F &&visit) {
+    __device__ void ranked_once(int rounds, double &sum, double &ninv) {
         Cand top[kTop];
 #pragma unroll
         for (int k = 0; k < kTop; ++k) top[k] = Cand{0.0, -1};
@@ -249,57 +228,52 @@ struct RankBlock {
                 take(fq[u], p);
             }
         }
+        // Each wave lists its own `rounds` best (no barrier between the rounds), then every listed
+        // candidate counts those that rank before it.
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
         for (int r = 0; r < rounds; ++r) {
-            const Cand b = block_best(top[0]);
+            const Cand b = wave_best(top[0]);
+            if (lane == 0) {
+                sh.lf[wave * rounds + r] = b.f;
+                sh.li[wave * rounds + r] = b.i;            // -1: the wave has no more
+            }
             if (b.i >= 0 && b.i == top[0].i) {                 // this thread's head was taken
 #pragma unroll
                 for (int k = 0; k + 1 < kTop; ++k) top[k] = top[k + 1];
                 top[kTop - 1] = Cand{0.0, -1};
+                if (top[0].i < 0 && r + 1 < rounds && (int)threadIdx.x + kTop * kRankThreads < P) top[0] = thread_best(b);
             }
-            visit(r, b);
         }
+        __syncthreads();
+        const int n = kRankWaves * rounds;                     // at most kRankThreads
+        if ((int)threadIdx.x < n) {
+            const double f = sh.lf[threadIdx.x];
+            const int i = sh.li[threadIdx.x];
+            int before = 0;
+#pragma unroll 8
+            for (int q = 0; q < n; ++q) {
+                const int iq = sh.li[q];
+                before += iq >= 0 && ranks_before(sh.lf[q], iq, f, i) ? 1 : 0;
+            }
+            if (i >= 0 && before < rounds) {
+                sh.ord[before] = i;
+                if (before == 0) sh.best = f;
+            }
+        }
+        __syncthreads();
     }
-    // Ranks 0 .. rounds-1 (visit(r, cand) in order) and, with stats set, the
-    // statistics row gen_off; returns the best. A single read of the values
-    // serves up to kTop ranks, more take one read per rank.
-    // between(): called once the ranks are known, before the statistics.
-    template <typename F, typename B>
-    __device__ Cand rank_and_stats(const InstDesc &d, int rounds, int gen_off, bool stats, F &&visit, B &&between) {
-        Cand best{-INFINITY, 0};
-        if (rounds <= kTop) {
-            double sum, ninv;
-            ranked_once(rounds, sum, ninv, [&](int r, Cand b) {
-                if (r == 0) best = b;
-                visit(r, b);
-            });
-            between();
-            if (stats) store_stats(d, gen_off, best, sum, ninv);
-        } else {
-            ranked(rounds, [&](int r, Cand b) {
-                if (r == 0) best = b;
-                visit(r, b);
-            });
-            between();
-            if (stats) write_stats(d, gen_off, best);
-        }
+    // Ranks 0 .. rounds-1 (rounds <= min(P, PGA_E_MAX)) into sh.ord and, with stats set,
+    // the statistics row gen_off: {best, mean of finite fitnesses (-inf if none),
+    // #-inf, argbest}; returns the best. ranked(): called once the ranks are known,
+    // before the statistics.
+    template <typename F>
+    __device__ Cand rank_and_stats(const InstDesc &d, int rounds, int gen_off, bool stats, F &&ranked) {
+        double sum, ninv;
+        ranked_once(rounds, sum, ninv);
+        ranked();
+        const Cand best{sh.best, sh.ord[0]};
+        if (stats) store_stats(d, gen_off, best, sum, ninv);
         return best;
-    }
-    // Statistics row gen_off: {best, mean of finite fitnesses (-inf if none), #-inf, argbest}.
-    __device__ void write_stats(const InstDesc &d, int gen_off, Cand best) {
-        double sum = 0.0, ninv = 0.0;
-#pragma unroll
-        for (int v = 0; v < CACHE; ++v) {
-            const int p = threadIdx.x + v * kRankThreads;
-            if (p >= P) break;
-            if (isfinite(fr[v])) sum += fr[v];
-            else ninv += 1.0;
-        }
-        for (int p = threadIdx.x + CACHE * kRankThreads; p < P; p += kRankThreads) {
-            const double fp = gld(f + p);
-            if (isfinite(fp)) sum += fp;
-            else ninv += 1.0;
-        }
-        store_stats(d, gen_off, best, sum, ninv);
     }
     __device__ void store_stats(const InstDesc &d, int gen_off, Cand best, double total, double inv) {
         block_sum2(total, inv);
@@ -363,9 +337,9 @@ __global__ __launch_bounds__(kRankThreads) void k_rank(Tables t, int gen_off, in
     }
     if (d.selection == PGA_SELECT_SUS)                     // the SUS rank kernel adds into these
         for (int p = threadIdx.x; p < P; p += kRankThreads) gst(d.sus_rank + p, 1);
-    const Cand best = rb.rank_and_stats(d, E > 1 ? E : 1, gen_off, d.stats != nullptr, [&](int r, Cand b) {
-        if (r < E && threadIdx.x == 0) d.elite[r] = b.i;
-    }, [] {});
+    const Cand best = rb.rank_and_stats(d, E > 1 ? E : 1, gen_off, d.stats != nullptr, [&] {
+        if ((int)threadIdx.x < E) gst(d.elite + threadIdx.x, sh.ord[threadIdx.x]);
+    });
     if (d.term && threadIdx.x == 0) term_update(d, st, best.f, final, gen_off == 0);
 }
 
@@ -512,6 +486,9 @@ __device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which) {
     return sus_pick(d, k, n, u, W);
 }
 
+typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));   // rows need not be aligned
+typedef int32_t gene4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // Ranking by the breed launch ("fold": no instance selects by SUS or can stop
 // early): workgroup k < n_inst ranks instance k (the RankBlock code and thread
 // count of the rank kernel, so the statistics are the same bits), copies its
@@ -532,32 +509,35 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
     if (d.term && threadIdx.x == 0) st = *d.term;
     const int32_t *__restrict__ src = d.pop[parity];
     int32_t *__restrict__ dst = d.pop[parity ^ 1];
-    // Up to four elites are copied after the ranking, their loads in flight
-    // together; more are copied as they are found.
-    constexpr int kQ = RankBlock<4>::kTop;
-    int eq[kQ] = {0, 0, 0, 0};
-    const Cand best = rb.rank_and_stats(d, E > 1 ? E : 1, gen_off, d.stats != nullptr, [&](int r, Cand b) {
-        if (r >= E) return;
-        if (E <= kQ) {
+    const Cand best = rb.rank_and_stats(d, E > 1 ? E : 1, gen_off, d.stats != nullptr, [&] {
+        // Wave w copies the elites w, w + 4, ..: four genes a lane, the loads of a whole row (N <=
+        // 1024) in flight together. (One gene a thread and four rows at a time: ten rows of 768
+        // genes were nine memory latencies, 9 us.)
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+        constexpr int kV = 4;
+        for (int r = wave; r < E; r += kRankWaves) {
+            const int32_t *__restrict__ e = src + (size_t)sh.ord[r] * N;
+            int32_t *__restrict__ o = dst + (size_t)r * N;
+            for (int j0 = 4 * lane; j0 < N; j0 += 4 * 64 * kV) {
+                gene4 v[kV];
 #pragma unroll
-            for (int q = 0; q < kQ; ++q)
-                if (q == r) eq[q] = b.i;
-            return;
-        }
-        const int32_t *__restrict__ e = src + (size_t)b.i * N;
-        int32_t *__restrict__ o = dst + (size_t)r * N;
-        for (int j = threadIdx.x; j < N; j += kRankThreads) o[j] = e[j];
-    }, [&] {
-        if (E <= kQ)
-            for (int j = threadIdx.x; j < N; j += kRankThreads) {
-                int32_t v[kQ];
+                for (int q = 0; q < kV; ++q) {
+                    const int j = j0 + 256 * q;
+                    if (j + 4 <= N) v[q] = *(const PGA_GLOBAL gene4 *)(e + j);
+                    else if (j < N) v[q] = gene4{gld(e + j), gld(e + min(j + 1, N - 1)), gld(e + min(j + 2, N - 1)), 0};
+                }
 #pragma unroll
-                for (int q = 0; q < kQ; ++q)
-                    if (q < E) v[q] = src[(size_t)eq[q] * N + j];
-#pragma unroll
-                for (int q = 0; q < kQ; ++q)
-                    if (q < E) dst[(size_t)q * N + j] = v[q];
+                for (int q = 0; q < kV; ++q) {
+                    const int j = j0 + 256 * q;
+                    if (j + 4 <= N) *(PGA_GLOBAL gene4 *)(o + j) = v[q];
+                    else {
+                        if (j < N) gst(o + j, v[q].x);
+                        if (j + 1 < N) gst(o + j + 1, v[q].y);
+                        if (j + 2 < N) gst(o + j + 2, v[q].z);
+                    }
+                }
             }
+        }
     });
     if (d.term && threadIdx.x == 0) {
         if (gen_off == 0) st.call_gens = 0;
@@ -580,7 +560,6 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
 // N ~ U{32..512} read two parents per child and write it, 430 MB in 133 us (3.2
 // TB/s; 198 us with a wave per slot and all draws in it). (Loading the next
 // pass's genes before the draw: 139 us, and no gain in small launches.)
-typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));
 __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold, BreedShape shape) {
     extern __shared__ __align__(16) uint32_t blds[];       // [parent A, B | crosses][chr], words [4 nq][chr]
     int wg = blockIdx.x;
