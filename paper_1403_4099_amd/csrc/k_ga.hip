@@ -500,6 +500,10 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
     const InstDesc &d = t.desc[k];
     const int P = d.P, E = d.E, N = d.N;
     if (P == 0 || (E == 0 && !d.term && !d.stats)) return;   // a padding slot, or nothing to rank
+    if (inst_stopped(d)) {                                 // by an earlier call: it stays as it is
+        if (gen_off == 0 && threadIdx.x == 0) gst(&d.term->call_gens, 0);
+        return;
+    }
     // This workgroup's chain of reductions is the longest path of the launch:
     // its waves issue ahead of the slot waves that share their SIMDs.
     __builtin_amdgcn_s_setprio(3);

@@ -50,3 +50,24 @@ def test_an_instance_breeds_the_same_in_launches_of_every_size(fill):
         pga.Context().evolve([filler, beside], 2, init=True)
         assert torch.equal(alone.pop, beside.pop) and torch.equal(alone.fitness, beside.fitness)
         assert torch.equal(alone.stats, beside.stats)
+
+
+@pytest.mark.parametrize("fill", [0, 4500], ids=["alone", "4k"])
+def test_a_stopped_instance_stays_as_it_is_without_a_stop_test(fill):
+    """Stopped by the termination test after an odd number of generations, then evolved by a call without
+    the test, whose breed launch does the ranking."""
+    say(f"stopped instance, then no stop test, beside {fill} slots")
+    C, _ = corr(40, T=64, seed=4)
+    Cf, _ = corr(9, T=64, seed=1)
+    ctx = pga.Context()
+    I = _inst(C, 50, 1, "tournament", stall_gens=1, tol=1e9)
+    ctx.evolve([I], 2, init=True)
+    st = I.term_state()
+    assert st["stopped"] == 1 and st["call_gens"] == 1
+    I.stall_gens = 0
+    before = [x.clone() for x in (I.pop, I.fitness, I.stats)]
+    others = [_inst(Cf, fill, 2, "tournament")] if fill else []
+    ctx.evolve(others + [I], 2, init=False)
+    for x, b in zip((I.pop, I.fitness, I.stats), before):
+        assert torch.equal(torch.nan_to_num(x.double(), nan=7.0), torch.nan_to_num(b.double(), nan=7.0))
+    assert I.term_state() == dict(st, call_gens=0)
