@@ -52,21 +52,30 @@ hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, in
 // workgroup barrier). Each lane keeps its B labels s_pj and B FP64 accumulators in
 // registers and walks the rows i < j of its column in chunks of 64 rows:
 //   - C_ij is loaded once per (wave, row), coalesced across the wave, and
-//     reused by B individuals; loads run one group of 4 rows ahead;
+//     reused by B individuals; loads run one group of 4 rows ahead, in two sets of
+//     registers that change roles (copied from one to the other, a copy waited for
+//     loads that had just gone out);
 //   - the row labels s_pi of the wave's B individuals are staged per chunk in
 //     a wave-private LDS buffer (transposed, so one 16-byte broadcast read
 //     serves 4 individuals), double-buffered: the next chunk's labels are
-//     fetched into registers while the current chunk is processed.
+//     fetched into registers while the current chunk is processed. An add block's labels
+//     are read into registers before the block above it.
 // Per (pair, individual): compare, masked FP64 add. Rows i >= j and rows
 // past N contribute C = 0, so every chunk runs all 64 rows without branches.
-// acc[b] += c on the lanes where row label r[b] equals lj[b], for the 8 or 16
-// individuals of a wave: each compare writes a lane mask to an SGPR pair, the
-// scalar unit narrows EXEC to it, and the FP64 add runs under that mask. Two
-// vector instructions per (pair, individual); the scalar ones issue alongside
-// other waves' vector work. Masks are made in two groups of 8, each group's
-// compares under the full EXEC, which is restored before the block ends.
-__device__ __forceinline__ void add_if_equal8(double *acc, const int *r, const int *lj, double c) {
-    uint64_t m[8], sv;
+// Bound by vector issue: 17.3 vector instructions per row of 8 individuals, 72 cycles of a SIMD at
+// their own rate with many waves; planted partitions at N = 1024, P = 4096 (4 waves per SIMD), 217 us
+// with the reads next to their uses and 8 masks, 176.6 us now. Tried without gain: row labels by scalar
+// loads (a line per individual: 312 us two rows at a time, 214 us 16 rows at a time, against 217),
+// a select of the value's high word instead of EXEC (275 us).
+// acc[b] += c on the lanes where the row label of individual b equals lj[b], for two rows of 8
+// individuals (row 0 first) or one row of 16: 16 compares under the full EXEC write 16 lane
+// masks to SGPR pairs (0 on inactive lanes), then each FP64 add runs with its mask as EXEC, which
+// is restored before the block ends. Two vector instructions per (pair, individual); the scalar ones
+// issue alongside other waves' vector work. 16 masks, because a switch between the two runs costs
+// most where few waves share a SIMD: cycles per 8 pairs with 4 / 8 waves, 95 / 79 with 8 masks,
+// 78 / 72 with 16 (64 of them the 16 vector instructions).
+__device__ __forceinline__ void add_if_equal8(double *acc, const int *r0, const int *r1, const int *lj, double c0, double c1) {
+    uint64_t m[16], sv;
     asm volatile(
         "s_mov_b64 %[sv], exec\n\t"
         "v_cmp_eq_u32_e64 %[m0], %[r0], %[l0]\n\t"
@@ -77,30 +86,55 @@ __device__ __forceinline__ void add_if_equal8(double *acc, const int *r, const i
         "v_cmp_eq_u32_e64 %[m5], %[r5], %[l5]\n\t"
         "v_cmp_eq_u32_e64 %[m6], %[r6], %[l6]\n\t"
         "v_cmp_eq_u32_e64 %[m7], %[r7], %[l7]\n\t"
-        "s_and_b64 exec, %[sv], %[m0]\n\t"
-        "v_add_f64 %[a0], %[a0], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m1]\n\t"
-        "v_add_f64 %[a1], %[a1], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m2]\n\t"
-        "v_add_f64 %[a2], %[a2], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m3]\n\t"
-        "v_add_f64 %[a3], %[a3], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m4]\n\t"
-        "v_add_f64 %[a4], %[a4], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m5]\n\t"
-        "v_add_f64 %[a5], %[a5], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m6]\n\t"
-        "v_add_f64 %[a6], %[a6], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m7]\n\t"
-        "v_add_f64 %[a7], %[a7], %[c]\n\t"
+        "v_cmp_eq_u32_e64 %[m8], %[r8], %[l0]\n\t"
+        "v_cmp_eq_u32_e64 %[m9], %[r9], %[l1]\n\t"
+        "v_cmp_eq_u32_e64 %[m10], %[r10], %[l2]\n\t"
+        "v_cmp_eq_u32_e64 %[m11], %[r11], %[l3]\n\t"
+        "v_cmp_eq_u32_e64 %[m12], %[r12], %[l4]\n\t"
+        "v_cmp_eq_u32_e64 %[m13], %[r13], %[l5]\n\t"
+        "v_cmp_eq_u32_e64 %[m14], %[r14], %[l6]\n\t"
+        "v_cmp_eq_u32_e64 %[m15], %[r15], %[l7]\n\t"
+        "s_mov_b64 exec, %[m0]\n\t"
+        "v_add_f64 %[a0], %[a0], %[c0]\n\t"
+        "s_mov_b64 exec, %[m1]\n\t"
+        "v_add_f64 %[a1], %[a1], %[c0]\n\t"
+        "s_mov_b64 exec, %[m2]\n\t"
+        "v_add_f64 %[a2], %[a2], %[c0]\n\t"
+        "s_mov_b64 exec, %[m3]\n\t"
+        "v_add_f64 %[a3], %[a3], %[c0]\n\t"
+        "s_mov_b64 exec, %[m4]\n\t"
+        "v_add_f64 %[a4], %[a4], %[c0]\n\t"
+        "s_mov_b64 exec, %[m5]\n\t"
+        "v_add_f64 %[a5], %[a5], %[c0]\n\t"
+        "s_mov_b64 exec, %[m6]\n\t"
+        "v_add_f64 %[a6], %[a6], %[c0]\n\t"
+        "s_mov_b64 exec, %[m7]\n\t"
+        "v_add_f64 %[a7], %[a7], %[c0]\n\t"
+        "s_mov_b64 exec, %[m8]\n\t"
+        "v_add_f64 %[a0], %[a0], %[c1]\n\t"
+        "s_mov_b64 exec, %[m9]\n\t"
+        "v_add_f64 %[a1], %[a1], %[c1]\n\t"
+        "s_mov_b64 exec, %[m10]\n\t"
+        "v_add_f64 %[a2], %[a2], %[c1]\n\t"
+        "s_mov_b64 exec, %[m11]\n\t"
+        "v_add_f64 %[a3], %[a3], %[c1]\n\t"
+        "s_mov_b64 exec, %[m12]\n\t"
+        "v_add_f64 %[a4], %[a4], %[c1]\n\t"
+        "s_mov_b64 exec, %[m13]\n\t"
+        "v_add_f64 %[a5], %[a5], %[c1]\n\t"
+        "s_mov_b64 exec, %[m14]\n\t"
+        "v_add_f64 %[a6], %[a6], %[c1]\n\t"
+        "s_mov_b64 exec, %[m15]\n\t"
+        "v_add_f64 %[a7], %[a7], %[c1]\n\t"
         "s_mov_b64 exec, %[sv]"
-        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]), [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [m0] "=&s"(m[0]), [m1] "=&s"(m[1]), [m2] "=&s"(m[2]), [m3] "=&s"(m[3]), [m4] "=&s"(m[4]), [m5] "=&s"(m[5]), [m6] "=&s"(m[6]), [m7] "=&s"(m[7]), [sv] "=&s"(sv)
-        : [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]), [r4] "v"(r[4]), [r5] "v"(r[5]), [r6] "v"(r[6]), [r7] "v"(r[7]), [l0] "v"(lj[0]), [l1] "v"(lj[1]), [l2] "v"(lj[2]), [l3] "v"(lj[3]), [l4] "v"(lj[4]), [l5] "v"(lj[5]), [l6] "v"(lj[6]), [l7] "v"(lj[7]), [c] "v"(c)
-        : "scc");
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]), [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]),
+          [m0] "=&s"(m[0]), [m1] "=&s"(m[1]), [m2] "=&s"(m[2]), [m3] "=&s"(m[3]), [m4] "=&s"(m[4]), [m5] "=&s"(m[5]), [m6] "=&s"(m[6]), [m7] "=&s"(m[7]), [m8] "=&s"(m[8]), [m9] "=&s"(m[9]), [m10] "=&s"(m[10]), [m11] "=&s"(m[11]), [m12] "=&s"(m[12]), [m13] "=&s"(m[13]), [m14] "=&s"(m[14]), [m15] "=&s"(m[15]), [sv] "=&s"(sv)
+        : [r0] "v"(r0[0]), [r1] "v"(r0[1]), [r2] "v"(r0[2]), [r3] "v"(r0[3]), [r4] "v"(r0[4]), [r5] "v"(r0[5]), [r6] "v"(r0[6]), [r7] "v"(r0[7]), [r8] "v"(r1[0]), [r9] "v"(r1[1]), [r10] "v"(r1[2]), [r11] "v"(r1[3]), [r12] "v"(r1[4]), [r13] "v"(r1[5]), [r14] "v"(r1[6]), [r15] "v"(r1[7]),
+          [l0] "v"(lj[0]), [l1] "v"(lj[1]), [l2] "v"(lj[2]), [l3] "v"(lj[3]), [l4] "v"(lj[4]), [l5] "v"(lj[5]), [l6] "v"(lj[6]), [l7] "v"(lj[7]), [c0] "v"(c0), [c1] "v"(c1));
 }
 
 __device__ __forceinline__ void add_if_equal16(double *acc, const int *r, const int *lj, double c) {
-    uint64_t m[8], sv;
+    uint64_t m[16], sv;
     asm volatile(
         "s_mov_b64 %[sv], exec\n\t"
         "v_cmp_eq_u32_e64 %[m0], %[r0], %[l0]\n\t"
@@ -111,56 +145,54 @@ __device__ __forceinline__ void add_if_equal16(double *acc, const int *r, const 
         "v_cmp_eq_u32_e64 %[m5], %[r5], %[l5]\n\t"
         "v_cmp_eq_u32_e64 %[m6], %[r6], %[l6]\n\t"
         "v_cmp_eq_u32_e64 %[m7], %[r7], %[l7]\n\t"
-        "s_and_b64 exec, %[sv], %[m0]\n\t"
-        "v_add_f64 %[a0], %[a0], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m1]\n\t"
-        "v_add_f64 %[a1], %[a1], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m2]\n\t"
-        "v_add_f64 %[a2], %[a2], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m3]\n\t"
-        "v_add_f64 %[a3], %[a3], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m4]\n\t"
-        "v_add_f64 %[a4], %[a4], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m5]\n\t"
-        "v_add_f64 %[a5], %[a5], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m6]\n\t"
-        "v_add_f64 %[a6], %[a6], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m7]\n\t"
-        "v_add_f64 %[a7], %[a7], %[c]\n\t"
-        "s_mov_b64 exec, %[sv]\n\t"
-        "v_cmp_eq_u32_e64 %[m0], %[r8], %[l8]\n\t"
-        "v_cmp_eq_u32_e64 %[m1], %[r9], %[l9]\n\t"
-        "v_cmp_eq_u32_e64 %[m2], %[r10], %[l10]\n\t"
-        "v_cmp_eq_u32_e64 %[m3], %[r11], %[l11]\n\t"
-        "v_cmp_eq_u32_e64 %[m4], %[r12], %[l12]\n\t"
-        "v_cmp_eq_u32_e64 %[m5], %[r13], %[l13]\n\t"
-        "v_cmp_eq_u32_e64 %[m6], %[r14], %[l14]\n\t"
-        "v_cmp_eq_u32_e64 %[m7], %[r15], %[l15]\n\t"
-        "s_and_b64 exec, %[sv], %[m0]\n\t"
-        "v_add_f64 %[a8], %[a8], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m1]\n\t"
-        "v_add_f64 %[a9], %[a9], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m2]\n\t"
-        "v_add_f64 %[a10], %[a10], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m3]\n\t"
-        "v_add_f64 %[a11], %[a11], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m4]\n\t"
-        "v_add_f64 %[a12], %[a12], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m5]\n\t"
-        "v_add_f64 %[a13], %[a13], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m6]\n\t"
-        "v_add_f64 %[a14], %[a14], %[c]\n\t"
-        "s_and_b64 exec, %[sv], %[m7]\n\t"
-        "v_add_f64 %[a15], %[a15], %[c]\n\t"
+        "v_cmp_eq_u32_e64 %[m8], %[r8], %[l8]\n\t"
+        "v_cmp_eq_u32_e64 %[m9], %[r9], %[l9]\n\t"
+        "v_cmp_eq_u32_e64 %[m10], %[r10], %[l10]\n\t"
+        "v_cmp_eq_u32_e64 %[m11], %[r11], %[l11]\n\t"
+        "v_cmp_eq_u32_e64 %[m12], %[r12], %[l12]\n\t"
+        "v_cmp_eq_u32_e64 %[m13], %[r13], %[l13]\n\t"
+        "v_cmp_eq_u32_e64 %[m14], %[r14], %[l14]\n\t"
+        "v_cmp_eq_u32_e64 %[m15], %[r15], %[l15]\n\t"
+        "s_mov_b64 exec, %[m0]\n\t"
+        "v_add_f64 %[a0], %[a0], %[c0]\n\t"
+        "s_mov_b64 exec, %[m1]\n\t"
+        "v_add_f64 %[a1], %[a1], %[c0]\n\t"
+        "s_mov_b64 exec, %[m2]\n\t"
+        "v_add_f64 %[a2], %[a2], %[c0]\n\t"
+        "s_mov_b64 exec, %[m3]\n\t"
+        "v_add_f64 %[a3], %[a3], %[c0]\n\t"
+        "s_mov_b64 exec, %[m4]\n\t"
+        "v_add_f64 %[a4], %[a4], %[c0]\n\t"
+        "s_mov_b64 exec, %[m5]\n\t"
+        "v_add_f64 %[a5], %[a5], %[c0]\n\t"
+        "s_mov_b64 exec, %[m6]\n\t"
+        "v_add_f64 %[a6], %[a6], %[c0]\n\t"
+        "s_mov_b64 exec, %[m7]\n\t"
+        "v_add_f64 %[a7], %[a7], %[c0]\n\t"
+        "s_mov_b64 exec, %[m8]\n\t"
+        "v_add_f64 %[a8], %[a8], %[c0]\n\t"
+        "s_mov_b64 exec, %[m9]\n\t"
+        "v_add_f64 %[a9], %[a9], %[c0]\n\t"
+        "s_mov_b64 exec, %[m10]\n\t"
+        "v_add_f64 %[a10], %[a10], %[c0]\n\t"
+        "s_mov_b64 exec, %[m11]\n\t"
+        "v_add_f64 %[a11], %[a11], %[c0]\n\t"
+        "s_mov_b64 exec, %[m12]\n\t"
+        "v_add_f64 %[a12], %[a12], %[c0]\n\t"
+        "s_mov_b64 exec, %[m13]\n\t"
+        "v_add_f64 %[a13], %[a13], %[c0]\n\t"
+        "s_mov_b64 exec, %[m14]\n\t"
+        "v_add_f64 %[a14], %[a14], %[c0]\n\t"
+        "s_mov_b64 exec, %[m15]\n\t"
+        "v_add_f64 %[a15], %[a15], %[c0]\n\t"
         "s_mov_b64 exec, %[sv]"
-        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]), [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [a8] "+v"(acc[8]), [a9] "+v"(acc[9]), [a10] "+v"(acc[10]), [a11] "+v"(acc[11]), [a12] "+v"(acc[12]), [a13] "+v"(acc[13]), [a14] "+v"(acc[14]), [a15] "+v"(acc[15]), [m0] "=&s"(m[0]), [m1] "=&s"(m[1]), [m2] "=&s"(m[2]), [m3] "=&s"(m[3]), [m4] "=&s"(m[4]), [m5] "=&s"(m[5]), [m6] "=&s"(m[6]), [m7] "=&s"(m[7]), [sv] "=&s"(sv)
-        : [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]), [r4] "v"(r[4]), [r5] "v"(r[5]), [r6] "v"(r[6]), [r7] "v"(r[7]), [r8] "v"(r[8]), [r9] "v"(r[9]), [r10] "v"(r[10]), [r11] "v"(r[11]), [r12] "v"(r[12]), [r13] "v"(r[13]), [r14] "v"(r[14]), [r15] "v"(r[15]), [l0] "v"(lj[0]), [l1] "v"(lj[1]), [l2] "v"(lj[2]), [l3] "v"(lj[3]), [l4] "v"(lj[4]), [l5] "v"(lj[5]), [l6] "v"(lj[6]), [l7] "v"(lj[7]), [l8] "v"(lj[8]), [l9] "v"(lj[9]), [l10] "v"(lj[10]), [l11] "v"(lj[11]), [l12] "v"(lj[12]), [l13] "v"(lj[13]), [l14] "v"(lj[14]), [l15] "v"(lj[15]), [c] "v"(c)
-        : "scc");
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1]), [a2] "+v"(acc[2]), [a3] "+v"(acc[3]), [a4] "+v"(acc[4]), [a5] "+v"(acc[5]), [a6] "+v"(acc[6]), [a7] "+v"(acc[7]), [a8] "+v"(acc[8]), [a9] "+v"(acc[9]), [a10] "+v"(acc[10]), [a11] "+v"(acc[11]), [a12] "+v"(acc[12]), [a13] "+v"(acc[13]), [a14] "+v"(acc[14]), [a15] "+v"(acc[15]),
+          [m0] "=&s"(m[0]), [m1] "=&s"(m[1]), [m2] "=&s"(m[2]), [m3] "=&s"(m[3]), [m4] "=&s"(m[4]), [m5] "=&s"(m[5]), [m6] "=&s"(m[6]), [m7] "=&s"(m[7]), [m8] "=&s"(m[8]), [m9] "=&s"(m[9]), [m10] "=&s"(m[10]), [m11] "=&s"(m[11]), [m12] "=&s"(m[12]), [m13] "=&s"(m[13]), [m14] "=&s"(m[14]), [m15] "=&s"(m[15]), [sv] "=&s"(sv)
+        : [r0] "v"(r[0]), [r1] "v"(r[1]), [r2] "v"(r[2]), [r3] "v"(r[3]), [r4] "v"(r[4]), [r5] "v"(r[5]), [r6] "v"(r[6]), [r7] "v"(r[7]), [r8] "v"(r[8]), [r9] "v"(r[9]), [r10] "v"(r[10]), [r11] "v"(r[11]), [r12] "v"(r[12]), [r13] "v"(r[13]), [r14] "v"(r[14]), [r15] "v"(r[15]),
+          [l0] "v"(lj[0]), [l1] "v"(lj[1]), [l2] "v"(lj[2]), [l3] "v"(lj[3]), [l4] "v"(lj[4]), [l5] "v"(lj[5]), [l6] "v"(lj[6]), [l7] "v"(lj[7]), [l8] "v"(lj[8]), [l9] "v"(lj[9]), [l10] "v"(lj[10]), [l11] "v"(lj[11]), [l12] "v"(lj[12]), [l13] "v"(lj[13]), [l14] "v"(lj[14]), [l15] "v"(lj[15]), [c0] "v"(c));
 }
 
-__device__ __forceinline__ double fp64_c(const double *__restrict__ C, int N, int i, int j) {
-    return (i < j && j < N) ? gld(C + (size_t)i * N + j) : 0.0;
-}
+constexpr int kFp64Ahead = 4;                        // rows whose C loads go out together: two or four add blocks
 
 template <int B>
 __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int order) {
@@ -181,11 +213,11 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
     const int lane = threadIdx.x & 63;
     const int pbase = pb * (kFp64Waves * B) + wave * B;
-    if (d.route) {                                   // wave-uniform: the waves share no barrier
-        int any = 0;
+    if (pbase >= P) return;                          // wave-uniform: the waves share no barrier
+    if (d.route) {
+        int any = 0;                                 // the loads together: no test between them
 #pragma unroll
-        for (int b = 0; b < B; ++b)
-            if (pbase + b < P) any |= gld(d.route + pbase + b);
+        for (int b = 0; b < B; ++b) any |= gld(d.route + min(pbase + b, P - 1));
         if (!any) return;
     }
     const int32_t *__restrict__ labels = d.pop[parity];
@@ -206,6 +238,10 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             lab_s[wave][buf][lane][q] = make_int4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
     };
 
+    // The four waves of a SIMD have equal work but, left to themselves, the oldest issues first and
+    // the youngest ends alone, at half the rate (they lived 74% of the launch on average): the
+    // highest priority goes round by wave slot, a chunk each (86%; 188.7 -> 176.6 us at N = 1024, P = 4096).
+    const int slot = __builtin_amdgcn_s_getreg((3 << 11) | 4);   // HW_ID.WAVE_ID
     // The triangle is folded: column blocks n_jb-1-jp (jp + 1 ... n_jb chunks of rows) and
     // jp are done by the same workgroup, so every workgroup has n_jb + 1 chunks of work.
     for (int half = 0; half < 2; ++half) {
@@ -230,19 +266,28 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
         __builtin_amdgcn_wave_barrier();                 // previous block's reads of buffer 0 are done
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         store_labels(0, nxt);
-        // Chunks before the last hold rows i < 64 jb <= j (and i < N) only, so their C
-        // loads need no test; lanes past N read column N - 1 and are never stored.
-        // Those loads go through a buffer descriptor over C: the lane's column offset
-        // stays in one register and the row offset is a scalar, so a load costs no
-        // vector address arithmetic.
+        // C loads go through a buffer descriptor over C: the lane's column offset stays in one
+        // register and the row offset is a scalar, so a load costs no vector address arithmetic;
+        // rows past N are out of its range and read 0. Lanes past N read column N - 1 and are
+        // never stored. Chunks before the last hold rows i < 64 jb <= j only, so their values
+        // need no test.
         const int jc = jok ? j : N - 1;
         const uint32_t jc_off = 8u * (uint32_t)jc;
+        auto load_c = [&](double *c, int i) {
+#pragma unroll
+            for (int q = 0; q < kFp64Ahead; ++q)
+                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)(i + q) * (uint32_t)N, 0));
+        };
+        double ca[kFp64Ahead], cb[kFp64Ahead];
+        load_c(ca, 0);
         auto chunk = [&](auto checked_tag, int ch) {
             constexpr bool checked = decltype(checked_tag)::value;
-            auto cload = [&](int i) -> double {
-                if constexpr (checked) return fp64_c(C, N, i, j);
-                else return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)i * (uint32_t)N, 0));
-            };
+            switch ((ch + slot) & 3) {
+            case 0: __builtin_amdgcn_s_setprio(0); break;
+            case 1: __builtin_amdgcn_s_setprio(1); break;
+            case 2: __builtin_amdgcn_s_setprio(2); break;
+            default: __builtin_amdgcn_s_setprio(3); break;
+            }
             const int i0 = ch * 64;
             const int buf = ch & 1;
             if (ch + 1 < nchunks) fetch_labels(i0 + 64, nxt);   // in flight during this chunk
@@ -250,32 +295,45 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-            double cq[4];
+            constexpr int kRows = 16 / B;                    // of one add block
+            int ra[kRows][B], rb[kRows][B];
+            auto labels_of = [&](int *rl, int r) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) cq[q] = cload(i0 + q);
-            for (int r = 0; r < 64; r += 4) {
-                double cur[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) cur[q] = cq[q];
-                if (r + 4 < 64) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) cq[q] = cload(i0 + r + 4 + q);
+                for (int u = 0; u < B / 4; ++u) {
+                    const int4 v = lab_s[wave][buf][r & 63][u];
+                    rl[4 * u + 0] = v.x;
+                    rl[4 * u + 1] = v.y;
+                    rl[4 * u + 2] = v.z;
+                    rl[4 * u + 3] = v.w;
                 }
+            };
+            // rows r .. r + kFp64Ahead - 1 with values c, the labels of the first kRows in rl; the
+            // C loads of the next rows go out before them, the label reads of a block's rows before
+            // the block above it (the barriers keep the compiler from moving a read next to its use)
+            auto rows = [&](int r, double *c, double *cn) {
+                load_c(cn, i0 + r + kFp64Ahead);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const double c = cur[q];
-                    int rl[B];
+                for (int q = 0; q < kFp64Ahead; q += kRows) {
+                    int(*cur)[B] = q / kRows & 1 ? rb : ra, (*next)[B] = q / kRows & 1 ? ra : rb;
 #pragma unroll
-                    for (int u = 0; u < B / 4; ++u) {
-                        const int4 v = lab_s[wave][buf][r + q][u];
-                        rl[4 * u + 0] = v.x;
-                        rl[4 * u + 1] = v.y;
-                        rl[4 * u + 2] = v.z;
-                        rl[4 * u + 3] = v.w;
+                    for (int u = 0; u < kRows; ++u) labels_of(next[u], r + q + kRows + u);
+                    __builtin_amdgcn_sched_barrier(0);
+                    double cq[kRows];
+#pragma unroll
+                    for (int u = 0; u < kRows; ++u) {
+                        cq[u] = c[q + u];
+                        if constexpr (checked) cq[u] = i0 + r + q + u < j ? cq[u] : 0.0;
                     }
-                    if constexpr (B == 16) add_if_equal16(acc, rl, lj, c);
-                    else add_if_equal8(acc, rl, lj, c);
+                    if constexpr (B == 16) add_if_equal16(acc, cur[0], lj, cq[0]);
+                    else add_if_equal8(acc, cur[0], cur[1], lj, cq[0], cq[1]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+            };
+#pragma unroll
+            for (int u = 0; u < kRows; ++u) labels_of(ra[u], u);
+            for (int r = 0; r < 64; r += 2 * kFp64Ahead) {
+                rows(r, ca, cb);
+                rows(r + kFp64Ahead, cb, ca);
             }
             if (ch + 1 < nchunks) store_labels(buf ^ 1, nxt);
         };
