@@ -43,11 +43,10 @@
 // times 2^125 (a workspace copy made once per call); every product is then
 // exactly the split part, as with a one-hot of 1.0.
 //
-// A is loaded once per (wave, chunk), one chunk ahead, by direct
-// memory-to-LDS loads into a two-slot ring per wave (no registers hold it in
-// flight; the column kernel addresses them through buffer descriptors, the
-// packed kernel through global addresses), and reused by every individual or
-// column group. FP32
+// A is loaded once per (wave, chunk), one chunk ahead (the column kernel: into
+// registers, through buffer descriptors; the packed kernel: by direct
+// memory-to-LDS loads into a two-slot ring per wave, through global addresses),
+// and reused by every individual or column group. FP32
 // accumulation is flushed into FP64 at every 512-row boundary (no FP32 partial
 // sum spans more than 512 rows). Both kernels give the same sums bit for bit:
 // a stock's column holds the same one-hot values in either, and its FP32
@@ -96,13 +95,10 @@ __host__ __device__ constexpr int mfma_pos(int b) {
 // LDS of one workgroup (dynamic): row codes, kMfmaRowCodes 16-bit words (the
 // code shifted into bits 8..15), as dwords [row pair][mfma_pos(b)] holding the
 // rows 2q (low half) and 2q + 1 of individual b; then the label -> code
-// tables [B][cstride] (bytes, cstride >= N); then each wave's ring of
-// kMfmaASlots A slots, 2 KB each (the 16 x 32 hi tile, then the lo tile, in
-// lane order), filled by direct buffer-to-LDS loads one chunk ahead.
+// tables [B][cstride] (bytes, cstride >= N).
 struct MfmaLdsCols {
     uint32_t *rows;
     uint8_t *code;
-    unsigned char *aring;
     int cstride;
 };
 
@@ -170,31 +166,21 @@ __device__ __forceinline__ void mfma_block_cols(const InstDesc &d, int jb, int p
     // multiple of 32 and jt0 a multiple of 16), so the loads need no guard. The
     // scaled copies are tile-major (a_tile_offset): the wave's 16 x 32 A block is
     // 1 KB of consecutive bytes in lane order.
-    // Chunk i0's A goes to ring slot ((i0 - c0) / 32) % kMfmaASlots of this wave:
-    // a direct buffer-to-LDS load puts lane l's 16 bytes at slot + 16 l, exactly
-    // where the same lane reads them back. The loads address the scaled copies
-    // through buffer descriptors: the lane's byte offset (16 l) stays in one
-    // register and the chunk's offset is a scalar, so moving to the next chunk
-    // costs no vector instruction.
+    // A goes straight to registers, and the row codes with it, one chunk ahead in two
+    // sets that change roles: a lane reads back its own 16 bytes only, and through a ring
+    // in LDS every chunk began with the latency of those reads and of the row codes' (N =
+    // 1024, P = 4096: the call 175 -> 171 us). The loads address the scaled copies
+    // through buffer descriptors: the lane's byte offset (16 l) stays in one register
+    // and the chunk's offset is a scalar, so moving to the next chunk costs no vector
+    // instruction.
     const size_t a_row = (size_t)(jt0 >> 4) * (size_t)(ld >> 5);
-    unsigned char *const my_ring = s.aring + (size_t)wave * kMfmaASlots * 2048;
-    auto slot_of = [&](int i0, int c0) { return my_ring + (size_t)(((i0 - c0) >> 5) % kMfmaASlots) * 2048; };
     const int a_bytes = 2 * ld * ld;                          // each scaled copy: ld x ld bf16
     const __amdgpu_buffer_rsrc_t hs_r = __builtin_amdgcn_make_buffer_rsrc((void *)hs, (short)0, a_bytes, kBufWord3);
     const __amdgpu_buffer_rsrc_t ls_r = __builtin_amdgcn_make_buffer_rsrc((void *)ls, (short)0, a_bytes, kBufWord3);
     const uint32_t lane_off = 16u * (uint32_t)lane;
-    auto load_a = [&](int i0, int c0) {
-        const uint32_t tile_off = (uint32_t)((a_row + (size_t)(i0 >> 5)) * 1024);   // uniform
-        unsigned char *sl = slot_of(i0, c0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(hs_r, (__attribute__((address_space(3))) void *)sl, 16, lane_off,
-                                                 tile_off, 0, 0);
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(ls_r, (__attribute__((address_space(3))) void *)(sl + 1024), 16,
-                                                 lane_off, tile_off, 0, 0);
-    };
-    auto read_a = [&](int i0, int c0, uint4 &ah, uint4 &al) {
-        const unsigned char *sl = slot_of(i0, c0);
-        ah = *(const uint4 *)(sl + 16 * lane);
-        al = *(const uint4 *)(sl + 1024 + 16 * lane);
+    struct Chunk {
+        pga_u32x4 ah, al;
+        uint32_t R[B / 4];
     };
     // Lane t of row group g reads, into R[k], rows i0 + 8g + 2(t%4), +1 of individual 4k + t/4.
     auto read_r = [&](int i0, int c0, uint32_t (&R)[B / 4]) {
@@ -213,7 +199,7 @@ __device__ __forceinline__ void mfma_block_cols(const InstDesc &d, int jb, int p
             R[3] = q4.w;
         }
     };
-    auto chunk = [&](auto masked_tag, int i0, int c0, uint4 ah, uint4 al, const uint32_t (&R)[B / 4]) {
+    auto chunk = [&](auto masked_tag, int i0, int c0, const pga_u32x4 &ah, const pga_u32x4 &al, const uint32_t (&R)[B / 4]) {
         constexpr bool masked = decltype(masked_tag)::value;
         const int ik = i0 + 8 * g;                            // first of this lane's 8 rows
         uint32_t m[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
@@ -255,17 +241,31 @@ __device__ __forceinline__ void mfma_block_cols(const InstDesc &d, int jb, int p
         });
         if (((i0 + 32) % kMfmaFlushRows) == 0) flush();
     };
-    // Chunks [i0, end) of one kind. A chunk first reads its A and row codes from
-    // LDS (its A was loaded during the previous chunk), then starts the load of
-    // the next chunk's A into the other slot, then computes.
-    auto run = [&](auto masked_tag, int &i0, int end, int cend, int c0) {
-        for (; i0 < end; i0 += 32) {
-            uint4 ah, al;
-            read_a(i0, c0, ah, al);
-            uint32_t R[B / 4];
-            read_r(i0, c0, R);
-            if (i0 + 32 < cend) load_a(i0 + 32, c0);
-            chunk(masked_tag, i0, c0, ah, al, R);
+    auto load = [&](Chunk &x, int i0, int c0) {
+        const uint32_t tile_off = (uint32_t)((a_row + (size_t)(i0 >> 5)) * 1024);   // uniform
+        x.ah = __builtin_amdgcn_raw_buffer_load_b128(hs_r, lane_off, tile_off, 0);
+        x.al = __builtin_amdgcn_raw_buffer_load_b128(ls_r, lane_off, tile_off, 0);
+        read_r(i0, c0, x.R);
+    };
+    // Chunks [i0, end) of one kind, cur holding the first: the loads of a chunk's A and
+    // row codes go out before the chunk above it.
+    auto run = [&](auto masked_tag, Chunk &cur, int &i0, int end, int last, int c0) {
+        Chunk next;
+        while (i0 < end) {
+            load(next, min(i0 + 32, last), c0);
+            __builtin_amdgcn_sched_barrier(0);
+            chunk(masked_tag, i0, c0, cur.ah, cur.al, cur.R);
+            __builtin_amdgcn_sched_barrier(0);
+            i0 += 32;
+            if (i0 >= end) {
+                cur = next;
+                break;
+            }
+            load(cur, min(i0 + 32, last), c0);
+            __builtin_amdgcn_sched_barrier(0);
+            chunk(masked_tag, i0, c0, next.ah, next.al, next.R);
+            __builtin_amdgcn_sched_barrier(0);
+            i0 += 32;
         }
     };
 
@@ -320,11 +320,13 @@ __device__ __forceinline__ void mfma_block_cols(const InstDesc &d, int jb, int p
         __syncthreads();
         const int cend = min(c0 + RC, my_iend);
         if (c0 < cend) {
-            load_a(c0, c0);
+            Chunk cur;
             int i0 = c0;
+            const int last = c0 + ((cend - c0 - 1) & ~31);      // loaded again behind itself, unused
+            load(cur, c0, c0);
             const int uend = min(cend, max(c0, i_diag));        // chunks entirely below the diagonal
-            run(std::false_type{}, i0, uend, cend, c0);
-            run(std::true_type{}, i0, cend, cend, c0);
+            run(std::false_type{}, cur, i0, uend, last, c0);
+            run(std::true_type{}, cur, i0, cend, last, c0);
         }
         __syncthreads();
     }
@@ -994,7 +996,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
             mfma_block_lut<B>(d, jp, pb, parity, lds, cstride);
         }
     } else {
-        const MfmaLdsCols s{(uint32_t *)lds, code, lds + mfma_lds_ring_off(B, cstride, KIND), cstride};
+        const MfmaLdsCols s{(uint32_t *)lds, code, cstride};
         mfma_block_cols<B>(d, n_jb - 1 - jp, pb, parity, s);
         if (jp != n_jb - 1 - jp) {
             clear_codes();

@@ -130,7 +130,7 @@ inline int32_t pair_tiles(int32_t N, int32_t P, const Variant &v) {
     return fold_pairs(N, 64) * ceil_div(P, per);
 }
 inline size_t mfma_code_stride(int max_n) { return ((size_t)max_n + 15) / 16 * 16; }
-constexpr int kMfmaASlots = 2;                     // A ring slots per wave (2 KB each) in the MFMA kernel
+constexpr int kMfmaASlots = 2;                     // A ring slots per wave (2 KB each) in the packed kernel
 // Rows of row codes staged per pass and individual by the packed kernel (a
 // multiple of 512), and the per-individual stride of its staged codes in 16-bit
 // words (16 bytes of padding).
@@ -139,7 +139,7 @@ __host__ __device__ constexpr int mfma_row_stride(int ipg) { return mfma_rows(ip
 // LDS of the MFMA kernels.
 // Column and packed kernels: row codes (the column kernel: kMfmaRowCodes words
 // for all individuals; the packed kernel: [ipg][stride]), label -> code tables,
-// A rings, and for the packed kernel 1 KB per wave of scratch.
+// and for the packed kernel A rings and 1 KB per wave of scratch.
 // LUT kernel, at fixed offsets: the one-hot table (256 x 16 bytes), two
 // buffers of row masks (16 KB each: [chunk][ipg][64 codes][4 row groups]
 // 16-bit words of lut_rows(ipg) rows, one pass), then the label -> code tables.
@@ -163,7 +163,8 @@ __host__ __device__ constexpr size_t mfma_lds_scratch_off(int ipg, int cstride, 
 inline size_t mfma_lds_bytes(int ipg, int max_n, int kind) {
     const int cstride = (int)mfma_code_stride(max_n);
     if (kind == kKindLut) return kLutCodeOff + (size_t)ipg * cstride;
-    return mfma_lds_scratch_off(ipg, cstride, kind) + (kind == kKindPacked ? (size_t)kMfmaWaves * 1024 : 0);
+    return kind == kKindPacked ? mfma_lds_scratch_off(ipg, cstride, kind) + (size_t)kMfmaWaves * 1024
+                               : mfma_lds_ring_off(ipg, cstride, kind);
 }
 static_assert(mfma_lds_code_off(4, kKindPacked) % 256 == 0 && mfma_lds_code_off(8, kKindPacked) % 256 == 0 &&
                   mfma_lds_code_off(16, kKindPacked) % 256 == 0 && mfma_lds_code_off(8, kKindCols) % 256 == 0 &&
