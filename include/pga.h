@@ -358,7 +358,8 @@ int pga_best(const double *fitness, const int32_t *labels, int32_t P, int32_t N,
  * elapsed milliseconds and launch count for kernel id
  *   0 pair-sum FP64, 1 pair-sum BF16x2 MFMA, 2 finish (n_s, c_s, L_c),
  *   3 rank/stats, 4 breed, 5 correlate, 6 split, 7 init, 8 SUS ranks and
- *   weights, 9 EWMA correlation, 10 cluster-pair fitness, 11 the labels with
+ *   weights (up to 4096 individuals an instance: rank/stats and parents
+ *   too), 9 EWMA correlation, 10 cluster-pair fitness, 11 the labels with
  *   n_s >= 2 (BF16x2 form, before its pair-sum). */
 int pga_timing_enable(int on);
 int pga_timing_reset(void);

@@ -10,6 +10,8 @@
 // gives the same bits alone or inside a batch and across resumes.
 #include "pga_internal.hpp"
 
+#include <type_traits>
+
 #include <math.h>
 
 namespace pga {
@@ -126,6 +128,15 @@ struct RankLds {
     int ord[PGA_E_MAX];                                    // the ranking
     double best;
 };
+
+__device__ __forceinline__ void stats_row(const InstDesc &d, int gen_off, Cand best, int P, double total, double inv) {
+    double *row = d.stats + 4 * (size_t)gen_off;
+    const double nfin = (double)P - inv;
+    row[0] = best.f;
+    row[1] = nfin > 0.0 ? total / nfin : -INFINITY;
+    row[2] = inv;
+    row[3] = (double)best.i;
+}
 
 template <int CACHE>
 struct RankBlock {
@@ -277,14 +288,7 @@ struct RankBlock {
     }
     __device__ void store_stats(const InstDesc &d, int gen_off, Cand best, double total, double inv) {
         block_sum2(total, inv);
-        if (threadIdx.x == 0) {
-            double *row = d.stats + 4 * (size_t)gen_off;
-            const double nfin = (double)P - inv;
-            row[0] = best.f;
-            row[1] = nfin > 0.0 ? total / nfin : -INFINITY;
-            row[2] = inv;
-            row[3] = (double)best.i;
-        }
+        if (threadIdx.x == 0) stats_row(d, gen_off, best, P, total, inv);
     }
 };
 
@@ -365,6 +369,7 @@ __device__ __forceinline__ int tournament2(const double *f, int a, int b) {
 
 // ---------------------------------------------------------------------------
 // Stochastic universal sampling after rank scaling (PGA_SELECT_SUS).
+// P <= 4096: the rank kernel of the launch does it all (k_rank_sus below). Larger:
 //   k_sus_rank:   rank_p = 1 + #{q : q ranks before p}; workgroup (x, y, inst)
 //                 compares individuals [256x, 256x + 256) with [256y, 256y + 256)
 //                 and adds its integer counts atomically (exact, order-free);
@@ -390,6 +395,33 @@ __global__ __launch_bounds__(256) void k_sus_rank(Tables t) {
     for (int r = 0; r < nq; ++r) cnt += ranks_before(fq[r], q0 + r, fp, p) ? 1 : 0;
     if (cnt) atomicAdd(d.sus_rank + p, cnt);
 }
+
+// The permutation of [0, n) that pairs SUS parents: a Feistel network on two halves of h bits, walked
+// until the image is below n. f(R, round): its round function, before the mask to h bits.
+__device__ __forceinline__ int shuffle_bits(uint32_t n) {
+    int h = 1;
+    while (((uint64_t)1 << (2 * h)) < (uint64_t)n) ++h;
+    return h;
+}
+template <typename F>
+__device__ __forceinline__ uint32_t feistel(uint32_t x, int h, F &&f) {
+    const uint32_t mask = (1u << h) - 1u;
+    uint32_t L = x >> h, R = x & mask;
+    for (uint32_t round = 0; round < 4; ++round) {
+        const uint32_t t = R;
+        R = L ^ (f(R, round) & mask);
+        L = t;
+    }
+    return (L << h) | R;
+}
+
+// u = floor(w0 W / 2^32) of the pointers floor((u + k W) / n).
+__device__ __forceinline__ uint64_t sus_offset(const InstDesc &d, uint32_t gen, uint64_t W) {
+    const uint32_t w0 = draw(0u, 0xFFFFFFFFu, gen, kTagSus, d.inst_id, d.seed).x;
+    return __umul64hi((uint64_t)w0 << 32, W);
+}
+// The parents, two per child, where the rank kernel lists them: in the prefix's place (2 (P - E) words of 2 P).
+__device__ __forceinline__ int32_t *sus_parents(const InstDesc &d) { return (int32_t *)d.sus_cum; }
 
 __device__ __forceinline__ uint64_t isqrt_u48(uint64_t x) {
     uint64_t y = (uint64_t)sqrt((double)x);                 // within one of the exact root
@@ -435,6 +467,310 @@ __global__ __launch_bounds__(1024) void k_sus_prefix(Tables t) {
     }
 }
 
+// ---- ranking and SUS of one instance by one workgroup -------------------------------------------
+// A fitness as a key that sorts ascending where ranks_before sorts (higher fitness first, +0 and -0 equal).
+__device__ __forceinline__ uint64_t rank_key(double f) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, f + 0.0);
+    return ~(b >> 63 ? ~b : b ^ (uint64_t)1 << 63);
+}
+__device__ __forceinline__ bool key_finite(uint64_t key) {
+    const uint64_t u = ~key;
+    return isfinite(__builtin_bit_cast(double, u >> 63 ? u ^ (uint64_t)1 << 63 : ~u));
+}
+// isqrt_u48(2^48 / r): the FP64 quotient's floor is exact (2^48 / r is a whole number, or at least 1 / r
+// below the next one, and half a unit in its last place is at most 2^-5 / r).
+__device__ __forceinline__ uint64_t sus_weight(int r) { return isqrt_u48((uint64_t)(0x1p48 / (double)r)); }
+
+// Rank kernel of the launches that select by SUS with P <= 1024 V: what k_rank, k_sus_rank and
+// k_sus_prefix do together, and the pointers' individuals with it. A bitonic sort of (key, index)
+// by 1024 threads, V elements each (element e in register e % V of thread e / V): partners up to 32
+// lanes away come by DPP and lane swaps, farther ones through LDS (10 of 55 steps at P = 1024).
+// Then, by sorted position, the elites and the weights (into LDS by individual); the inclusive prefix
+// cum of the weights in index order; for each individual p the number of pointers before the end of its
+// segment, ks(p): pointer k lies at floor((u + k W) / n), and cum(p) > floor(x) for a whole cum(p) is
+// cum(p) > x, so ks(p) = ceil((n cum(p) - u) / W) (n cum < 2^13 2^36); and each child's parents, the first
+// individuals p with ks(p) > k by a search in LDS, k the shuffled pointer. The shuffle's round function has 4 2^h
+// values (h <= 7): one draw per thread here, against 8 draws and more per parent in the breed kernel. The
+// statistics are those of RankBlock: 256 threads, the same order of additions.
+// 128 instances of P = 1000: three launches of 45 us (29 of them to count all pairs) and 36 us of breeding,
+// which drew the shuffle and searched the prefix in memory, against one of 20 us and 19 us (with 512
+// or 256 threads of 2 or 4 elements the whole run took 1.03 or 1.13 times as long). By phase, in cycles of 43 000: the sort 16 400, the
+// parents 8 400, the shuffle 5 400, loads and weights 5 000.
+constexpr int kSusHalfBits = 7;                              // of the pairing's halves, n <= 2 kSusSortMax
+static_assert((1 << 2 * kSusHalfBits) >= 2 * kSusSortMax && kSusHalfBits <= 8, "a byte per value");
+
+struct SusElem {
+    uint64_t key;
+    uint32_t idx;
+};
+
+// Lanes where (a.key, a.idx) < (b.key, b.idx): the borrow of their difference. (Written as compares it is
+// five, and four scalar instructions.)
+__device__ __forceinline__ uint64_t sus_less(const SusElem &a, const SusElem &b) {
+    uint64_t m;
+    uint32_t t;
+    asm("v_sub_co_u32_e32 %[t], vcc, %[ai], %[bi]\n\t"
+        "v_subb_co_u32_e32 %[t], vcc, %[al], %[bl], vcc\n\t"
+        "v_subb_co_u32_e32 %[t], vcc, %[ah], %[bh], vcc\n\t"
+        "s_mov_b64 %[m], vcc"
+        : [m] "=s"(m), [t] "=&v"(t)
+        : [ai] "v"(a.idx), [bi] "v"(b.idx), [al] "v"((uint32_t)a.key), [bl] "v"((uint32_t)b.key),
+          [ah] "v"((uint32_t)(a.key >> 32)), [bh] "v"((uint32_t)(b.key >> 32))
+        : "vcc");
+    return m;
+}
+__device__ __forceinline__ SusElem sus_select(uint64_t lanes, const SusElem &a, const SusElem &b) {   // a on `lanes`
+    const bool s = __builtin_amdgcn_inverse_ballot_w64(lanes);
+    return SusElem{s ? a.key : b.key, s ? a.idx : b.idx};
+}
+template <typename F>
+__device__ __forceinline__ SusElem sus_each(const SusElem &x, F &&f) {
+    return SusElem{(uint64_t)f((uint32_t)(x.key >> 32)) << 32 | f((uint32_t)x.key), f(x.idx)};
+}
+
+// One step with lane l ^ J; up: lanes whose run ascends.
+template <int J, int V>
+__device__ __forceinline__ void sus_step(SusElem (&x)[V], uint64_t up) {
+    constexpr uint64_t kUpper = J == 1    ? 0xAAAAAAAAAAAAAAAA
+                                : J == 2  ? 0xCCCCCCCCCCCCCCCC
+                                : J == 4  ? 0xF0F0F0F0F0F0F0F0
+                                : J == 8  ? 0xFF00FF00FF00FF00
+                                : J == 16 ? 0xFFFF0000FFFF0000
+                                          : 0xFFFFFFFF00000000;      // the upper lane of each pair
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        if constexpr (J >= 16) {
+            // a swap of x with itself: the lower lane's element and the upper lane's, in both
+            uint32_t lo[3], hi[3];
+            const uint32_t w[3] = {(uint32_t)x[v].key, (uint32_t)(x[v].key >> 32), x[v].idx};
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                const auto r = J == 16 ? __builtin_amdgcn_permlane16_swap(w[q], w[q], false, false)
+                                       : __builtin_amdgcn_permlane32_swap(w[q], w[q], false, false);
+                lo[q] = r[0];
+                hi[q] = r[1];
+            }
+            const SusElem L{(uint64_t)lo[1] << 32 | lo[0], lo[2]}, U{(uint64_t)hi[1] << 32 | hi[0], hi[2]};
+            x[v] = sus_select(~(sus_less(U, L) ^ up) ^ kUpper, U, L);
+        } else {
+            const SusElem y = sus_each(x[v], [](uint32_t z) {
+                auto mov = [](uint32_t q, auto ctrl) {
+                    return (uint32_t)__builtin_amdgcn_mov_dpp((int)q, decltype(ctrl)::value, 0xF, 0xF, true);
+                };
+                if constexpr (J == 1) return mov(z, std::integral_constant<int, kQuad1>{});
+                else if constexpr (J == 2) return mov(z, std::integral_constant<int, kQuad2>{});
+                else if constexpr (J == 4)                   // half mirror: l ^ 7, quads reversed: l ^ 3
+                    return mov(mov(z, std::integral_constant<int, 0x141>{}), std::integral_constant<int, 0x1B>{});
+                else return mov(z, std::integral_constant<int, kRor8>{});
+            });
+            x[v] = sus_select(~(sus_less(y, x[v]) ^ up ^ kUpper), y, x[v]);
+        }
+    }
+}
+
+template <int T, int V>
+__global__ __launch_bounds__(T) void k_rank_sus(Tables t, int gen_off) {
+    __shared__ uint64_t key_s[T * V];                        // sort; then the weights by individual; then the shuffle
+    __shared__ uint32_t idx_s[T * V];                        // sort; then ks by individual
+    __shared__ uint64_t wsum[T / 64];
+    __shared__ double wf[kRankWaves];
+    __shared__ int wi[kRankWaves];
+    __shared__ uint8_t round_s[4 << kSusHalfBits];           // the pairing's round function: [round][right half]
+    __shared__ int first;
+    const InstDesc &d = t.desc[blockIdx.x];
+    if (d.P == 0) return;                                    // a padding slot of a capacity-sized launch
+    const int P = d.P, E = d.E, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const double *__restrict__ f = d.fitness;
+    SusElem x[V];
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int p = V * tid + v;
+        x[v] = SusElem{p < P ? rank_key(gld(f + p)) : ~(uint64_t)0, (uint32_t)p};
+    }
+    const bool sus = d.selection == PGA_SELECT_SUS;
+    const uint32_t n = 2u * (uint32_t)(P - E), gen = d.gen0 + (uint32_t)gen_off;
+    const int h = shuffle_bits(n);
+    if (sus)
+        for (int e = tid; e < 4 << h; e += T)
+            round_s[e] = (uint8_t)draw((uint32_t)e & ((1u << h) - 1u), (uint32_t)e >> h, gen, kTagShuf, d.inst_id, d.seed).x;
+    pga_term_state st{};
+    if (d.term) {
+        const bool stopped = inst_stopped(d);
+        if (tid == 0) st = *d.term;
+        __syncthreads();                                     // every thread has read the flag
+        if (gen_off == 0 && tid == 0) {
+            gst(&d.term->call_gens, 0);
+            st.call_gens = 0;
+        }
+        if (stopped) return;
+    }
+    if (d.stats && tid < kRankThreads) {                     // whole waves
+        double sum = 0.0, ninv = 0.0;
+        for (int p = tid; p < P; p += kRankThreads) {
+            const double fp = gld(f + p);
+            if (isfinite(fp)) sum += fp;
+            else ninv += 1.0;
+        }
+        sum = group_sum<64>(sum);
+        ninv = group_sum<64>(ninv);
+        if (lane == 0) {
+            wf[wave] = sum;
+            wi[wave] = (int)ninv;
+        }
+    }
+
+    int n2 = 64 * V;
+    while (n2 < P) n2 *= 2;
+    const bool busy = (tid & ~63) * V < n2;                  // per wave
+    for (int k = 2; k <= n2; k *= 2) {
+        const uint64_t up = __builtin_amdgcn_ballot_w64(((V * tid) & k) == 0);   // (k < V: by register, below)
+        for (int j = k / 2; j >= 64 * V; j /= 2) {           // uniform over the workgroup
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                key_s[v * T + tid] = x[v].key;
+                idx_s[v * T + tid] = x[v].idx;
+            }
+            __syncthreads();
+            const int q = tid ^ (j / V);
+            const uint64_t upper = tid & (j / V) ? ~(uint64_t)0 : 0;      // per wave
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const SusElem y{key_s[v * T + q], idx_s[v * T + q]};
+                x[v] = sus_select(~(sus_less(y, x[v]) ^ up ^ upper), y, x[v]);
+            }
+            __syncthreads();
+        }
+        if (!busy) continue;
+        if (k > 32 * V) sus_step<32>(x, up);
+        if (k > 16 * V) sus_step<16>(x, up);
+        if (k > 8 * V) sus_step<8>(x, up);
+        if (k > 4 * V) sus_step<4>(x, up);
+        if (k > 2 * V) sus_step<2>(x, up);
+        if (k > V) sus_step<1>(x, up);
+#pragma unroll
+        for (int j = V / 2; j > 0; j /= 2) {
+            if (k <= j) continue;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                if (v & j) continue;
+                const uint64_t up_v = k < V ? (v & k) == 0 ? ~(uint64_t)0 : 0 : up;
+                const SusElem a = x[v], b = x[v ^ j];
+                const uint64_t swap = ~(sus_less(b, a) ^ up_v);
+                x[v] = sus_select(swap, b, a);
+                x[v ^ j] = sus_select(swap, a, b);
+            }
+        }
+    }
+    __syncthreads();                                         // (n2 <= 64 V: no barrier above)
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int r = V * tid + v;                           // its rank - 1
+        const int i = (int)x[v].idx;
+        if (r >= P) continue;
+        if (r < E) gst(d.elite + r, i);
+        if (r == 0) first = i;
+        if (sus) key_s[i] = key_finite(x[v].key) ? sus_weight(r + 1) : 0;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const double best = gld(f + first);
+        if (d.stats) {
+            double total = 0.0, inv = 0.0;
+            for (int w = 0; w < kRankWaves; ++w) {
+                total += wf[w];
+                inv += (double)wi[w];
+            }
+            stats_row(d, gen_off, Cand{best, first}, P, total, inv);
+        }
+        if (d.term) term_update(d, st, best, 0, gen_off == 0);
+    }
+    if (!sus) return;
+
+    uint64_t cum[V];
+    uint64_t w = 0;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int p = V * tid + v;
+        if (p < P) w += key_s[p];
+        cum[v] = w;
+    }
+    uint64_t inc = w;                                        // inclusive scan over the wave
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) wsum[wave] = inc;
+    __syncthreads();
+    uint64_t before = inc - w, W = 0;
+#pragma unroll
+    for (int v = 0; v < T / 64; ++v) {
+        if (v < wave) before += wsum[v];
+        W += wsum[v];
+    }
+    const bool uniform = W == 0;                             // every fitness is -inf: every weight 1
+    if (uniform) W = (uint64_t)P;
+    const uint64_t u = sus_offset(d, gen, W);
+    const double per = 1.0 / (double)W;
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        const int p = V * tid + v;
+        if (p >= P) continue;
+        const uint64_t a = (uint64_t)n * (uniform ? (uint64_t)p + 1 : before + cum[v]);
+        // floor((a - u) / W) by FP64 within one, then exactly; then the ceiling
+        const uint64_t num = a <= u ? 0 : a - u;
+        uint32_t q = (uint32_t)((double)num * per);
+        int64_t r = (int64_t)(num - q * W);
+        if (r < 0) {
+            --q;
+            r += (int64_t)W;
+        } else if (r >= (int64_t)W) {
+            ++q;
+            r -= (int64_t)W;
+        }
+        idx_s[p] = q + (r > 0 ? 1u : 0u);
+    }
+    // The Feistel network's image of every number of 2h bits (the weights have been read): 4 rounds here,
+    // one read per turn of the cycle walk.
+    uint16_t *const shuffle_s = (uint16_t *)key_s;
+    static_assert(sizeof(key_s) >= sizeof(uint16_t) << (V * T > 2048 ? 14 : 12), "2h = 12 bits up to n = 4096");
+#pragma unroll 4
+    for (int e = tid; e < 1 << 2 * h; e += T)
+        shuffle_s[e] = (uint16_t)feistel((uint32_t)e, h, [&](uint32_t R, uint32_t round) { return (uint32_t)round_s[round << h | R]; });
+    __syncthreads();
+    int32_t *__restrict__ parents = sus_parents(d);
+    for (uint32_t i0 = tid; i0 < n; i0 += 2 * T) {           // two at a time: chains of LDS reads
+        uint32_t x[2] = {i0, i0 + T < n ? i0 + T : i0};
+        x[0] = shuffle_s[x[0]];
+        x[1] = shuffle_s[x[1]];
+        while (x[0] >= n || x[1] >= n) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (x[q] >= n) x[q] = shuffle_s[x[q]];
+        }
+        int at[2] = {0, 0};
+        for (int s = n2 / 2; s > 0; s /= 2) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+                if (at[q] + s <= P && idx_s[at[q] + s - 1] <= x[q]) at[q] += s;
+        }
+        gst(parents + i0, at[0]);
+        if (i0 + T < n) gst(parents + i0 + T, at[1]);
+    }
+}
+
+hipError_t launch_rank_sus(Tables t, int max_p, int gen_off, hipStream_t s) {
+    if (max_p <= 1024)
+        hipLaunchKernelGGL((k_rank_sus<1024, 1024 / 1024>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
+    else if (max_p <= 2048)
+        hipLaunchKernelGGL((k_rank_sus<1024, 2>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
+    else if (max_p <= kSusSortMax)
+        hipLaunchKernelGGL((k_rank_sus<1024, 4>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
 hipError_t launch_sus(Tables t, int max_p, hipStream_t s) {
     if (t.n_inst <= 0 || max_p <= 0) return hipSuccess;
     const int nb = (max_p + 255) / 256;
@@ -443,23 +779,6 @@ hipError_t launch_sus(Tables t, int max_p, hipStream_t s) {
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_sus_prefix, dim3(t.n_inst), dim3(1024), 0, s, t);
     return hipGetLastError();
-}
-
-// Image of x under the Feistel permutation of [0, n) that pairs SUS parents.
-__device__ uint32_t shuffle_index(uint32_t x, uint32_t n, const InstDesc &d, uint32_t gen) {
-    int h = 1;
-    while (((uint64_t)1 << (2 * h)) < (uint64_t)n) ++h;
-    const uint32_t mask = (1u << h) - 1u;
-    do {
-        uint32_t L = x >> h, R = x & mask;
-        for (uint32_t round = 0; round < 4; ++round) {
-            const uint32_t t = R;
-            R = L ^ (draw(R, round, gen, kTagShuf, d.inst_id, d.seed).x & mask);
-            L = t;
-        }
-        x = (L << h) | R;
-    } while (x >= n);
-    return x;
 }
 
 // Individual whose SUS segment holds pointer k (smallest p with cum[p] > pos).
@@ -476,14 +795,18 @@ __device__ int sus_pick(const InstDesc &d, uint32_t k, uint32_t n, uint64_t u, u
 // Parent pair of child c (c >= E): two tournaments of two on draw (0, c, g,
 // SELECT), or, with SUS, the individuals under shuffled pointers 2(c - E) and
 // 2(c - E) + 1 (which = 0, 1).
-__device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which) {
+__device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which, int listed) {
     const int P = d.P, E = d.E;
     const uint32_t n = 2u * (uint32_t)(P - E);
+    const uint32_t x = 2u * (uint32_t)(c - E) + (uint32_t)which;
+    if (listed) return gld(sus_parents(d) + x);
+    const int h = shuffle_bits(n);
+    uint32_t k = x;
+    do {                                                     // until the image is one of [0, n)
+        k = feistel(k, h, [&](uint32_t R, uint32_t round) { return draw(R, round, gen, kTagShuf, d.inst_id, d.seed).x; });
+    } while (k >= n);
     const uint64_t W = gld(d.sus_cum + (P - 1));
-    const uint32_t w0 = draw(0u, 0xFFFFFFFFu, gen, kTagSus, d.inst_id, d.seed).x;
-    const uint64_t u = __umul64hi((uint64_t)w0 << 32, W);              // floor(w0 W / 2^32)
-    const uint32_t k = shuffle_index(2u * (uint32_t)(c - E) + (uint32_t)which, n, d, gen);
-    return sus_pick(d, k, n, u, W);
+    return sus_pick(d, k, n, sus_offset(d, gen, W), W);
 }
 
 typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));   // rows need not be aligned
@@ -564,7 +887,7 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
 // N ~ U{32..512} read two parents per child and write it, 430 MB in 133 us (3.2
 // TB/s; 198 us with a wave per slot and all draws in it). (Loading the next
 // pass's genes before the draw: 139 us, and no gain in small launches.)
-__global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold, BreedShape shape) {
+__global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold, int sus_listed, BreedShape shape) {
     extern __shared__ __align__(16) uint32_t blds[];       // [parent A, B | crosses][chr], words [4 nq][chr]
     int wg = blockIdx.x;
     if (fold) {
@@ -598,7 +921,7 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
         for (int x = tid / chr; x < kinds; x += 256 / chr) {
             if (c >= P || c < E) continue;
             if (sus && x < 2) {
-                par[x * chr + ci] = sus_parent(d, c, gen, x);
+                par[x * chr + ci] = sus_parent(d, c, gen, x, sus_listed);
                 continue;
             }
             const int y = sus ? x - 1 : x;                 // 0 parents, 1 cross, 2 + q: word q
@@ -661,7 +984,7 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
     }
 }
 
-hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int max_n,
+hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s) {
     const int grid = (fold ? t.n_inst : 0) + blocks;
     if (grid <= 0) return hipSuccess;
@@ -671,7 +994,7 @@ hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, i
         const int N = n < max_n ? n : max_n;
         words = std::max(words, (size_t)breed_split(N, b).chr * (3 + 4 * (size_t)((2 * N + 127) / 128)));
     }
-    hipLaunchKernelGGL(k_breed, dim3(grid), dim3(256), sizeof(uint32_t) * words, s, t, parity, gen_off, fold, b);
+    hipLaunchKernelGGL(k_breed, dim3(grid), dim3(256), sizeof(uint32_t) * words, s, t, parity, gen_off, fold, sus_listed, b);
     return hipGetLastError();
 }
 

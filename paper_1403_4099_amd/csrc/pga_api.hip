@@ -287,10 +287,15 @@ hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, in
         // Without SUS or an early stop, breeding needs the ranking only for the elite
         // slots, and the breed kernel does it itself (fold); otherwise rank first.
         const int fold = (!sh.sus && !sh.stop) ? 1 : 0;
-        if (!fold && (e = timed(3, s, [&] { return launch_rank(t, k, 0, s); })) != hipSuccess) return e;
-        if (sh.sus && (e = timed(8, s, [&] { return launch_sus(t, sh.max_p, s); })) != hipSuccess) return e;
+        const int sorted = (sh.sus && sh.max_p <= kSusSortMax) ? 1 : 0;
+        if (sorted) {
+            if ((e = timed(8, s, [&] { return launch_rank_sus(t, sh.max_p, k, s); })) != hipSuccess) return e;
+        } else {
+            if (!fold && (e = timed(3, s, [&] { return launch_rank(t, k, 0, s); })) != hipSuccess) return e;
+            if (sh.sus && (e = timed(8, s, [&] { return launch_sus(t, sh.max_p, s); })) != hipSuccess) return e;
+        }
         if ((e = timed(4, s, [&] {
-                 return launch_breed(t, sh.breeds, sh.breed, parity, k, fold, sh.max_n, s);
+                 return launch_breed(t, sh.breeds, sh.breed, parity, k, fold, sorted, sh.max_n, s);
              })) != hipSuccess)
             return e;
     }

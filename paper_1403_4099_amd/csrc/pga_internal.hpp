@@ -389,12 +389,14 @@ inline BreedShape breed_shape(int inds) {
     return BreedShape{inds >= 4096 ? 8 : 2, inds >= 16384 ? 8 : 1, 16};
 }
 inline int breed_blocks(int N, int P, const BreedShape &b) { return ceil_div(P, breed_split(N, b).chr); }
-hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int max_n,
+hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s);
 // Launches of at least kManyInds individuals (more than the chip holds at a
 // workgroup each) run the finish over the dense list; smaller ones a workgroup
 // per individual.
 constexpr int kManyInds = 8192;
+constexpr int kSusSortMax = 4096;                  // largest P of a launch whose rank kernel does the SUS: its LDS and registers
+hipError_t launch_rank_sus(Tables t, int max_p, int gen_off, hipStream_t s);
 hipError_t launch_sus(Tables t, int max_p, hipStream_t s);
 hipError_t launch_copy_back(Tables t, int total_inds, int G, hipStream_t s);
 // Records a hipError_t for pga_last_hip_error() on this thread.
