@@ -16,38 +16,52 @@
 
 namespace pga {
 
+typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));   // rows need not be aligned
+typedef int32_t gene4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // ---------------------------------------------------------------------------
 // Initial population: gene i of individual p is scale_u32(word i%4 of draw
-// (i/4, p, gen0, INIT), N). One workgroup per individual.
-__global__ __launch_bounds__(256) void k_init(Tables t) {
-    const int g = blockIdx.x;
-    if (g >= t.inds[t.n_inst]) return;                     // the grid may exceed the total (capacity-sized graph)
-    const int k = find_inst(t.inds, t.n_inst, g);
+// (i/4, p, gen0, INIT), N). The breed launch's split: a workgroup makes the slots [c0, c0 + chr)
+// of one instance, gl lanes each (a workgroup per individual took 113 us for 128 000 of N = 18,
+// five of its lanes at work; 14.6 us).
+__global__ __launch_bounds__(256) void k_init(Tables t, BreedShape shape) {
+    const int wg = blockIdx.x;
+    if (wg >= t.breeds[t.n_inst]) return;                  // the grid may exceed the total (capacity-sized graph)
+    const int k = find_inst(t.breeds, t.n_inst, wg);
     const InstDesc &d = t.desc[k];
-    const int N = d.N;
-    const int p = g - t.inds[k];
-    if (p == 0 && threadIdx.x == 0 && d.term) {
+    const int N = d.N, tid = threadIdx.x;
+    const BreedSplit split = breed_split(N, shape);
+    const int c0 = (wg - t.breeds[k]) * split.chr, gl = tid & (split.gl - 1);
+    if (c0 == 0 && tid == 0 && d.term) {
         pga_term_state z;
         z.ref = -INFINITY;
         z.stall = z.stopped = z.gens = z.call_gens = 0;
         *d.term = z;
     }
-    int32_t *__restrict__ row = d.pop[0] + (size_t)p * N;
     const int nq = (N + 3) >> 2;
-    for (int q = threadIdx.x; q < nq; q += 256) {
-        const U4 w = draw((uint32_t)q, (uint32_t)p, d.gen0, kTagInit, d.inst_id, d.seed);
-        const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 4 * q + r;
-            if (i < N) row[i] = (int32_t)scale_u32(ws[r], (uint32_t)N);
+    for (int ci = tid / split.gl; ci < split.chr; ci += 256 / split.gl) {
+        const int p = c0 + ci;
+        if (p >= d.P) break;
+        int32_t *__restrict__ row = d.pop[0] + (size_t)p * N;
+        for (int q = gl; q < nq; q += split.gl) {
+            const U4 w = draw((uint32_t)q, (uint32_t)p, d.gen0, kTagInit, d.inst_id, d.seed);
+            const gene4 v = {(int32_t)scale_u32(w.x, (uint32_t)N), (int32_t)scale_u32(w.y, (uint32_t)N),
+                             (int32_t)scale_u32(w.z, (uint32_t)N), (int32_t)scale_u32(w.w, (uint32_t)N)};
+            const int i = 4 * q;
+            if (i + 4 <= N) {
+                *(PGA_GLOBAL gene4 *)(row + i) = v;
+            } else {
+                gst(row + i, v.x);
+                if (i + 1 < N) gst(row + i + 1, v.y);
+                if (i + 2 < N) gst(row + i + 2, v.z);
+            }
         }
     }
 }
 
-hipError_t launch_init(Tables t, int total_inds, hipStream_t s) {
-    if (total_inds <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_init, dim3(total_inds), dim3(256), 0, s, t);
+hipError_t launch_init(Tables t, int blocks, const BreedShape &b, hipStream_t s) {
+    if (blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, t, b);
     return hipGetLastError();
 }
 
@@ -809,9 +823,6 @@ __device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which, int
     return sus_pick(d, k, n, sus_offset(d, gen, W), W);
 }
 
-typedef int32_t gene2 __attribute__((ext_vector_type(2), aligned(4)));   // rows need not be aligned
-typedef int32_t gene4 __attribute__((ext_vector_type(4), aligned(4)));
-
 // Ranking by the breed launch ("fold": no instance selects by SUS or can stop
 // early): workgroup k < n_inst ranks instance k (the RankBlock code and thread
 // count of the rank kernel, so the statistics are the same bits), copies its
@@ -1001,23 +1012,33 @@ hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, i
 // After an odd number of bred generations the population sits in pop[1]; copy
 // it back so the caller always finds the result in the buffer it passed as
 // pop. Without a termination test every call breeds G generations.
-__global__ __launch_bounds__(256) void k_copy_back(Tables t, int G) {
-    const int g = blockIdx.x;
-    if (g >= t.inds[t.n_inst]) return;                     // the grid may exceed the total (capacity-sized graph)
-    const int k = find_inst(t.inds, t.n_inst, g);
+// A workgroup copies the rows of the slots that it would breed: one run of memory (a workgroup per row: 90 us
+// for 128 000 of N = 18 without a row to copy; 3.9 us).
+__global__ __launch_bounds__(256) void k_copy_back(Tables t, int G, BreedShape shape) {
+    const int wg = blockIdx.x;
+    if (wg >= t.breeds[t.n_inst]) return;                  // the grid may exceed the total (capacity-sized graph)
+    const int k = find_inst(t.breeds, t.n_inst, wg);
     const InstDesc &d = t.desc[k];
     const int bred = d.term ? gld(&d.term->call_gens) : G;
     if ((bred & 1) == 0) return;
-    const int N = d.N;
-    const int p = g - t.inds[k];
-    const int32_t *__restrict__ a = d.pop[1] + (size_t)p * N;
-    int32_t *__restrict__ b = d.pop[0] + (size_t)p * N;
-    for (int j = threadIdx.x; j < N; j += 256) b[j] = a[j];
+    const int N = d.N, chr = breed_split(N, shape).chr, c0 = (wg - t.breeds[k]) * chr;
+    const int len = min(chr, d.P - c0) * N;
+    const int32_t *__restrict__ a = d.pop[1] + (size_t)c0 * N;
+    int32_t *__restrict__ b = d.pop[0] + (size_t)c0 * N;
+    for (int j = 4 * threadIdx.x; j < len; j += 4 * 256) {
+        if (j + 4 <= len) {
+            *(PGA_GLOBAL gene4 *)(b + j) = *(const PGA_GLOBAL gene4 *)(a + j);
+        } else {
+            gst(b + j, gld(a + j));
+            if (j + 1 < len) gst(b + j + 1, gld(a + j + 1));
+            if (j + 2 < len) gst(b + j + 2, gld(a + j + 2));
+        }
+    }
 }
 
-hipError_t launch_copy_back(Tables t, int total_inds, int G, hipStream_t s) {
-    if (total_inds <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_copy_back, dim3(total_inds), dim3(256), 0, s, t, G);
+hipError_t launch_copy_back(Tables t, int blocks, const BreedShape &b, int G, hipStream_t s) {
+    if (blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_copy_back, dim3(blocks), dim3(256), 0, s, t, G, b);
     return hipGetLastError();
 }
 

@@ -302,7 +302,7 @@ hipError_t run_generations(const Tables &t, const Shape &sh, int form, int G, in
     const int parity = G & 1;
     if ((e = run_fitness(t, sh, form, parity, status, s)) != hipSuccess) return e;
     if ((e = timed(3, s, [&] { return launch_rank(t, G, 1, s); })) != hipSuccess) return e;
-    return launch_copy_back(t, sh.inds, G, s);
+    return launch_copy_back(t, sh.breeds, sh.breed, G, s);
 }
 
 }  // namespace
@@ -856,7 +856,7 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     Tables t = tables_at(ws, L, nb);
     if (form == PGA_FORM_BF16X2) HIP_TRY(launch_scale_split(t, split_ld(sh.max_n), s));
     if (sh.frac > 0.0) HIP_TRY(launch_diag(t, sh.max_n, s));
-    if (flags & PGA_EVOLVE_INIT) HIP_TRY(timed(7, s, [&] { return launch_init(t, sh.inds, s); }));
+    if (flags & PGA_EVOLVE_INIT) HIP_TRY(timed(7, s, [&] { return launch_init(t, sh.breeds, sh.breed, s); }));
 
     const bool eager = (flags & PGA_EVOLVE_EAGER) || timing_on();
     if (eager) {

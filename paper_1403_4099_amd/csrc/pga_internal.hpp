@@ -364,7 +364,7 @@ size_t eval_lds(int N);
 hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int parity, double frac, int listed, int form,
                        int32_t *status, hipStream_t s);
 
-hipError_t launch_init(Tables t, int total_inds, hipStream_t s);
+
 hipError_t launch_rank(Tables t, int gen_off, int final, hipStream_t s);
 // Shape of a breed launch: the most passes of a slot's lanes over its gene pairs (few in small
 // launches, whose time is a slot's chain of passes; many in large ones, where few lanes per
@@ -389,6 +389,7 @@ inline BreedShape breed_shape(int inds) {
     return BreedShape{inds >= 4096 ? 8 : 2, inds >= 16384 ? 8 : 1, 16};
 }
 inline int breed_blocks(int N, int P, const BreedShape &b) { return ceil_div(P, breed_split(N, b).chr); }
+hipError_t launch_init(Tables t, int blocks, const BreedShape &b, hipStream_t s);
 hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s);
 // Launches of at least kManyInds individuals (more than the chip holds at a
@@ -398,7 +399,7 @@ constexpr int kManyInds = 8192;
 constexpr int kSusSortMax = 4096;                  // largest P of a launch whose rank kernel does the SUS: its LDS and registers
 hipError_t launch_rank_sus(Tables t, int max_p, int gen_off, hipStream_t s);
 hipError_t launch_sus(Tables t, int max_p, hipStream_t s);
-hipError_t launch_copy_back(Tables t, int total_inds, int G, hipStream_t s);
+hipError_t launch_copy_back(Tables t, int blocks, const BreedShape &b, int G, hipStream_t s);
 // Records a hipError_t for pga_last_hip_error() on this thread.
 void note_hip_error(int e);
 
