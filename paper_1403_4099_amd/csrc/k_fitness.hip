@@ -267,16 +267,16 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         store_labels(0, nxt);
         // C loads go through a buffer descriptor over C: the lane's column offset stays in one
-        // register and the row offset is a scalar, so a load costs no vector address arithmetic;
-        // rows past N are out of its range and read 0. Lanes past N read column N - 1 and are
-        // never stored. Chunks before the last hold rows i < 64 jb <= j only, so their values
-        // need no test.
+        // register and the row offset is a scalar, so a load costs no vector address arithmetic.
+        // Rows past N read row N - 1 (the range check of a buffer leaves the scalar offset out) and
+        // lanes past N column N - 1; the former are >= j, the latter never stored. Chunks before the
+        // last hold rows i < 64 jb <= j only, so their values need no test.
         const int jc = jok ? j : N - 1;
         const uint32_t jc_off = 8u * (uint32_t)jc;
         auto load_c = [&](double *c, int i) {
 #pragma unroll
             for (int q = 0; q < kFp64Ahead; ++q)
-                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)(i + q) * (uint32_t)N, 0));
+                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)min(i + q, N - 1) * (uint32_t)N, 0));
         };
         double ca[kFp64Ahead], cb[kFp64Ahead];
         load_c(ca, 0);
