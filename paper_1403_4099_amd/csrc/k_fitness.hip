@@ -64,7 +64,7 @@ hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, in
 // past N contribute C = 0, so every chunk runs all 64 rows without branches.
 // Bound by vector issue: 17.3 vector instructions per row of 8 individuals, 72 cycles of a SIMD at
 // their own rate with many waves; planted partitions at N = 1024, P = 4096 (4 waves per SIMD), 217 us
-// with the reads next to their uses and 8 masks, 176.6 us now. Tried without gain: row labels by scalar
+// with the reads next to their uses and 8 masks, 173 us now. Tried without gain: row labels by scalar
 // loads (a line per individual: 312 us two rows at a time, 214 us 16 rows at a time, against 217),
 // a select of the value's high word instead of EXEC (275 us).
 // acc[b] += c on the lanes where the row label of individual b equals lj[b], for two rows of 8
@@ -273,13 +273,16 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
         // last hold rows i < 64 jb <= j only, so their values need no test.
         const int jc = jok ? j : N - 1;
         const uint32_t jc_off = 8u * (uint32_t)jc;
-        auto load_c = [&](double *c, int i) {
+        // (The clamp only where rows may be past N: in every load it cost 3%.)
+        auto load_c = [&](auto clamped, double *c, int i) {
 #pragma unroll
-            for (int q = 0; q < kFp64Ahead; ++q)
-                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)min(i + q, N - 1) * (uint32_t)N, 0));
+            for (int q = 0; q < kFp64Ahead; ++q) {
+                const int row = decltype(clamped)::value ? min(i + q, N - 1) : i + q;
+                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)row * (uint32_t)N, 0));
+            }
         };
         double ca[kFp64Ahead], cb[kFp64Ahead];
-        load_c(ca, 0);
+        load_c(std::true_type{}, ca, 0);
         auto chunk = [&](auto checked_tag, int ch) {
             constexpr bool checked = decltype(checked_tag)::value;
             switch ((ch + slot) & 3) {
@@ -310,8 +313,8 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             // rows r .. r + kFp64Ahead - 1 with values c, the labels of the first kRows in rl; the
             // C loads of the next rows go out before them, the label reads of a block's rows before
             // the block above it (the barriers keep the compiler from moving a read next to its use)
-            auto rows = [&](int r, double *c, double *cn) {
-                load_c(cn, i0 + r + kFp64Ahead);
+            auto rows = [&](auto clamped, int r, double *c, double *cn) {
+                load_c(clamped, cn, i0 + r + kFp64Ahead);
 #pragma unroll
                 for (int q = 0; q < kFp64Ahead; q += kRows) {
                     int(*cur)[B] = q / kRows & 1 ? rb : ra, (*next)[B] = q / kRows & 1 ? ra : rb;
@@ -331,10 +334,12 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             };
 #pragma unroll
             for (int u = 0; u < kRows; ++u) labels_of(ra[u], u);
-            for (int r = 0; r < 64; r += 2 * kFp64Ahead) {
-                rows(r, ca, cb);
-                rows(r + kFp64Ahead, cb, ca);
+            for (int r = 0; r < 64 - 2 * kFp64Ahead; r += 2 * kFp64Ahead) {
+                rows(checked_tag, r, ca, cb);
+                rows(checked_tag, r + kFp64Ahead, cb, ca);
             }
+            rows(checked_tag, 64 - 2 * kFp64Ahead, ca, cb);
+            rows(std::true_type{}, 64 - kFp64Ahead, cb, ca);           // loads rows of the next chunk
             if (ch + 1 < nchunks) store_labels(buf ^ 1, nxt);
         };
         for (int ch = 0; ch + 1 < nchunks; ++ch) chunk(std::false_type{}, ch);
