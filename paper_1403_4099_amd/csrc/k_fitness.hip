@@ -29,7 +29,7 @@ struct DescBlob {
 __global__ void k_write_desc(DescBlob b, InstDesc *dst, int32_t *prefix) {
     if (threadIdx.x == 0) *dst = b.d;
     if (threadIdx.x < 8) prefix[threadIdx.x] = b.prefix[threadIdx.x];
-    for (int i = threadIdx.x; i < kListCounters; i += blockDim.x) prefix[8 + i] = 0;
+    for (int i = threadIdx.x; i < kListCounters + kTileCounters; i += blockDim.x) prefix[8 + i] = 0;
 }
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix, hipStream_t s) {
@@ -194,26 +194,22 @@ __device__ __forceinline__ void add_if_equal16(double *acc, const int *r, const 
 
 constexpr int kFp64Ahead = 4;                        // rows whose C loads go out together: two or four add blocks
 
-template <int B>
+template <int B, bool LISTED>
 __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int order) {
     __shared__ int4 lab_s[kFp64Waves][2][64][B / 4];
 
     const int total = t.tiles[t.n_inst];                  // the grid may exceed it (capacity-sized graph)
     if ((int)blockIdx.x >= total) return;
-    const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
-    const int k = find_inst(t.tiles, t.n_inst, tile);
-    const InstDesc &d = t.desc[k];
-    if (inst_stopped(d)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
+    const int lane = threadIdx.x & 63;
+    auto work = [&](const InstDesc &d, int local) {        // the waves share no barrier
     const int N = d.N, P = d.P;
-    const int local = tile - t.tiles[k];
     const int n_jb = (N + kFp64Cols - 1) / kFp64Cols;
     const int n_pairs = (n_jb + 1) / 2;
     const TilePos tp = tile_pos(local, n_pairs, (P + kFp64Waves * B - 1) / (kFp64Waves * B), order);
     const int jp = tp.jp, pb = tp.pb;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
-    const int lane = threadIdx.x & 63;
     const int pbase = pb * (kFp64Waves * B) + wave * B;
-    if (pbase >= P) return;                          // wave-uniform: the waves share no barrier
+    if (pbase >= P) return;
     if (d.route) {
         int any = 0;                                 // the loads together: no test between them
 #pragma unroll
@@ -353,16 +349,66 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             }
         }
     }
+    };
+    if constexpr (LISTED) {
+        each_listed_tile(t, parity, total, [&](int tile) {
+            const int k = find_inst_const(t.tiles, t.n_inst, tile);
+            work(desc_const(t, k), tile - ((const PGA_CONST int32_t *)(uintptr_t)t.tiles)[k]);
+        });
+    } else {
+        const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
+        const int k = find_inst(t.tiles, t.n_inst, tile);
+        const InstDesc &d = t.desc[k];
+        if (inst_stopped(d)) return;
+        work(d, tile - t.tiles[k]);
+    }
 }
 
-hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, const Variant &v, hipStream_t s) {
+// The tiles with an individual of the pair-sum's, listed by XCD in tile order: a thread per tile, an append per wave.
+__global__ __launch_bounds__(256) void k_tiles(Tables t, int parity, int order, int per) {
+    const int total = t.tiles[t.n_inst], cap = tile_list_cap(total), span = (cap + 63) & ~63;
+    const int g = blockIdx.x * 256 + threadIdx.x, x = __builtin_amdgcn_readfirstlane(g / span), b = (g % span) * kXcds + x;
+    if (x >= kXcds) return;
+    bool active = false;
+    const int tile = order ? xcd_tile(min(b, total - 1), total) : b;
+    if (b < total) {
+        const int k = find_inst(t.tiles, t.n_inst, tile);
+        const InstDesc &d = t.desc[k];
+        if (!inst_stopped(d)) {
+            const int local = tile - t.tiles[k], n_pairs = ((d.N + 63) / 64 + 1) / 2;
+            const int p0 = tile_pos(local, n_pairs, (d.P + per - 1) / per, order).pb * per;
+            int any = 0;
+            for (int p = p0; p < p0 + per; p += 4)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) any |= gld(d.route + min(p + q, d.P - 1));
+            active = any != 0;
+        }
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(active);
+    if (!m) return;
+    const int lane = threadIdx.x & 63;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(tile_count(t, parity, x), __popcll(m));
+    at = __builtin_amdgcn_readfirstlane(at) + __popcll(m & (((uint64_t)1 << lane) - 1));
+    if (active) gst(t.tile_list + (size_t)x * cap + at, tile);
+}
+
+hipError_t launch_tiles(Tables t, int total_tiles, int parity, int order, int per, hipStream_t s) {
+    const int span = (total_tiles / kXcds + 1 + 63) & ~63;   // of the capacity: no less than the kernel's
+    hipLaunchKernelGGL(k_tiles, dim3((kXcds * span + 255) / 256), dim3(256), 0, s, t, parity, order, per);
+    return hipGetLastError();
+}
+
+hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, int listed, const Variant &v, hipStream_t s) {
     if (total_tiles <= 0) return hipSuccess;
-    if (v.ipg == 16)
-        hipLaunchKernelGGL(k_pairsum_fp64<16>, dim3(total_tiles), dim3(256), 0, s, t, parity, v.order);
-    else if (v.ipg == 8)
-        hipLaunchKernelGGL(k_pairsum_fp64<8>, dim3(total_tiles), dim3(256), 0, s, t, parity, v.order);
-    else
-        return hipErrorInvalidValue;
+    if (v.ipg != 16 && v.ipg != 8) return hipErrorInvalidValue;
+    if (listed) {
+        const hipError_t e = launch_tiles(t, total_tiles, parity, v.order, kFp64Waves * v.ipg, s);
+        if (e != hipSuccess) return e;
+    }
+    auto kernel = listed ? (v.ipg == 16 ? k_pairsum_fp64<16, true> : k_pairsum_fp64<8, true>)
+                         : (v.ipg == 16 ? k_pairsum_fp64<16, false> : k_pairsum_fp64<8, false>);
+    hipLaunchKernelGGL(kernel, dim3(listed ? kTileListGrid : total_tiles), dim3(256), 0, s, t, parity, v.order);
     return hipGetLastError();
 }
 
@@ -1204,6 +1250,10 @@ __global__ __launch_bounds__(256, 8) void k_eval(Tables t, int parity, double fr
     const int b = blockIdx.x;
     if (listed && b == 0)
         for (int i = threadIdx.x; i < kListSlices; i += 256) gst(list_count(t, parity ^ 1, i), 0);
+    if (b == 0 && threadIdx.x < kXcds) {             // the next evaluation's tile lists
+        gst(tile_count(t, parity ^ 1, threadIdx.x), 0);
+        gst(tile_next(t, parity ^ 1, threadIdx.x), 0);
+    }
     if (b >= t.evals[t.n_inst]) return;              // the grid may exceed the total (capacity-sized graph)
     // Workgroups go to the XCDs in turn; runs of kEvalRun consecutive ones are given to one XCD, so
     // that it reads the C of few instances at a time (256 instances, N ~ U{32..512}: 334 us without,

@@ -942,29 +942,18 @@ __device__ __forceinline__ void mfma_block_packed(const InstDesc &d, int jb, int
 
 // The triangle is folded: column blocks n_jb-1-jp and jp share a workgroup, so every
 // workgroup processes the same number of row chunks.
-template <int B, int KIND>
+template <int B, int KIND, bool LISTED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     KIND == kKindLut ? (B == 8 ? 2 : 3) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
                                                                                      int order, int cstride) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int total = t.tiles[t.n_inst];                  // the grid may exceed it (capacity-sized graph)
     if ((int)blockIdx.x >= total) return;
-    const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
-    const int k = find_inst(t.tiles, t.n_inst, tile);
-    const InstDesc &d = t.desc[k];
-    if (inst_stopped(d)) return;                              // uniform over the workgroup
-    const int local = tile - t.tiles[k];
+    auto work = [&](const InstDesc &d, int local) {
     const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
     const int n_pairs = (n_jb + 1) / 2;
     const TilePos tp = tile_pos(local, n_pairs, (d.P + B - 1) / B, order);
     const int jp = tp.jp, pb = tp.pb;
-    if (d.route) {                                            // uniform: skip batches the cluster-pair
-        int any = 0;                                          // kernel evaluated entirely
-#pragma unroll
-        for (int b = 0; b < B; ++b)
-            if (pb * B + b < d.P) any |= gld(d.route + pb * B + b);
-        if (!any) return;
-    }
     // Label -> code tables: every entry set to kCodeNone (B tables of cstride bytes,
     // one contiguous, 16-byte aligned region; cstride >= N is a multiple of 16). The
     // column and packed blocks leave their entries set, and the tables are cleared
@@ -1004,6 +993,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
             mfma_block_cols<B>(d, jp, pb, parity, s);
         }
     }
+    };
+    if constexpr (LISTED) {
+        each_listed_tile(t, parity, total, [&](int tile) {
+            const int k = find_inst_const(t.tiles, t.n_inst, tile);
+            work(desc_const(t, k), tile - ((const PGA_CONST int32_t *)(uintptr_t)t.tiles)[k]);
+        });
+    } else {
+        const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
+        const int k = find_inst(t.tiles, t.n_inst, tile);
+        const InstDesc &d = t.desc[k];
+        if (inst_stopped(d)) return;                          // uniform over the workgroup
+        const int local = tile - t.tiles[k], n_pairs = ((d.N + kMfmaCols - 1) / kMfmaCols + 1) / 2;
+        const int pb = tile_pos(local, n_pairs, (d.P + B - 1) / B, order).pb;
+        if (d.route) {                                        // uniform: skip batches the cluster-pair
+            int any = 0;                                      // kernel evaluated entirely
+#pragma unroll
+            for (int b = 0; b < B; ++b)
+                if (pb * B + b < d.P) any |= gld(d.route + pb * B + b);
+            if (!any) return;
+        }
+        work(d, local);
+    }
 }
 
 // The LUT kernel addresses its table by absolute LDS address, which requires
@@ -1015,41 +1026,48 @@ bool mfma_static_lds_ok() {
     } else {
         static const bool ok = [] {
             hipFuncAttributes a{};
-            return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_pairsum_mfma<B, KIND>)) == hipSuccess &&
+            return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_pairsum_mfma<B, KIND, false>)) == hipSuccess &&
                    a.sharedSizeBytes == 0;
         }();
         return ok;
     }
 }
 
-template <int KIND>
-hipError_t launch_mfma_b(Tables t, int total_tiles, int parity, int ipg, int order, int cstride, size_t lds,
-                         hipStream_t s) {
-    if (ipg == 8) {
-        if (!mfma_static_lds_ok<8, KIND>()) return hipErrorInvalidKernelFile;
-        hipLaunchKernelGGL((k_pairsum_mfma<8, KIND>), dim3(total_tiles), dim3(256), lds, s, t, parity, order, cstride);
-    } else if (ipg == 4) {
-        if (!mfma_static_lds_ok<4, KIND>()) return hipErrorInvalidKernelFile;
-        hipLaunchKernelGGL((k_pairsum_mfma<4, KIND>), dim3(total_tiles), dim3(256), lds, s, t, parity, order, cstride);
-    } else if (ipg == 16 && KIND != kKindLut) {               // the LUT kernel has no 16-individual form
-        if constexpr (KIND != kKindLut)
-            hipLaunchKernelGGL((k_pairsum_mfma<16, KIND>), dim3(total_tiles), dim3(256), lds, s, t, parity, order,
+template <int B, int KIND>
+hipError_t launch_mfma(Tables t, int total_tiles, int parity, int listed, int order, int cstride, size_t lds, hipStream_t s) {
+    if (!mfma_static_lds_ok<B, KIND>()) return hipErrorInvalidKernelFile;
+    if constexpr (KIND == kKindCols)
+        if (listed && lds + 256 <= (size_t)kMaxLdsBytes) {    // (the listed kernel has a word of its own)
+            const hipError_t e = launch_tiles(t, total_tiles, parity, order, B, s);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, true>), dim3(kTileListGrid), dim3(256), lds, s, t, parity, order,
                                cstride);
-    } else {
-        return hipErrorInvalidValue;
-    }
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, false>), dim3(total_tiles), dim3(256), lds, s, t, parity, order, cstride);
     return hipGetLastError();
 }
 
-hipError_t launch_pairsum_mfma(Tables t, int total_tiles, int parity, const Variant &v, int max_n,
+template <int KIND>
+hipError_t launch_mfma_b(Tables t, int total_tiles, int parity, int listed, int ipg, int order, int cstride, size_t lds,
+                         hipStream_t s) {
+    if (ipg == 8) return launch_mfma<8, KIND>(t, total_tiles, parity, listed, order, cstride, lds, s);
+    if (ipg == 4) return launch_mfma<4, KIND>(t, total_tiles, parity, listed, order, cstride, lds, s);
+    if constexpr (KIND != kKindLut)                           // the LUT kernel has no 16-individual form
+        if (ipg == 16) return launch_mfma<16, KIND>(t, total_tiles, parity, listed, order, cstride, lds, s);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_pairsum_mfma(Tables t, int total_tiles, int parity, int listed, const Variant &v, int max_n,
                                hipStream_t s) {
     if (total_tiles <= 0) return hipSuccess;
     if (!variant_ok(v, max_n)) return hipErrorInvalidValue;
     const int cstride = (int)mfma_code_stride(max_n);
     const size_t lds = mfma_lds_bytes(v.ipg, max_n, v.kind);
-    if (v.kind == kKindPacked) return launch_mfma_b<kKindPacked>(t, total_tiles, parity, v.ipg, v.order, cstride, lds, s);
-    if (v.kind == kKindLut) return launch_mfma_b<kKindLut>(t, total_tiles, parity, v.ipg, v.order, cstride, lds, s);
-    return launch_mfma_b<kKindCols>(t, total_tiles, parity, v.ipg, v.order, cstride, lds, s);
+    if (v.kind == kKindPacked)
+        return launch_mfma_b<kKindPacked>(t, total_tiles, parity, listed, v.ipg, v.order, cstride, lds, s);
+    if (v.kind == kKindLut) return launch_mfma_b<kKindLut>(t, total_tiles, parity, listed, v.ipg, v.order, cstride, lds, s);
+    return launch_mfma_b<kKindCols>(t, total_tiles, parity, listed, v.ipg, v.order, cstride, lds, s);
 }
 
 // ---- scaled split parts ----------------------------------------------------------

@@ -182,7 +182,7 @@ int bucket(int x) {
 // offset that depends on n alone, so a captured graph serves every mix of n
 // slots; the per-instance regions are reached through the descriptors.
 struct Layout {
-    size_t desc_off, pre_off, inst_off, list_off;
+    size_t desc_off, pre_off, inst_off, list_off, tile_off;   // tile_off 0: no tile list
     std::vector<size_t> wsum_off, elite_off, hs_off, ls_off, rank_off, cum_off, route_off, diag_off, ns2_off;
     size_t total;
 };
@@ -191,11 +191,19 @@ Layout make_layout(const int32_t *Ns, const int32_t *Ps, int n, int form, const 
     Layout L;
     L.desc_off = 0;
     L.pre_off = align_up(sizeof(InstDesc) * (size_t)n, 256);
-    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (4 * ((size_t)n + 1) + (size_t)kListCounters), 256);
+    L.inst_off = align_up(L.pre_off + sizeof(int32_t) * (4 * ((size_t)n + 1) + (size_t)(kListCounters + kTileCounters)), 256);
     L.list_off = L.inst_off;
     int sum_p = 0;
     for (int k = 0; k < n; ++k) sum_p += Ps[k];
     size_t off = align_up(L.list_off + sizeof(int32_t) * list_words((bucket(sum_p) + 3) / 4), 256);
+    // Tile lists: of the variant with the most tiles (4 individuals each, or 8 a wave).
+    int64_t tiles = 0;
+    for (int k = 0; k < n; ++k) tiles += (int64_t)fold_pairs(Ns[k], 64) * ceil_div(Ps[k], form == PGA_FORM_FP64 ? kFp64Waves * 8 : 4);
+    L.tile_off = 0;
+    if (tiles > kTileListMin) {
+        L.tile_off = off;
+        off = align_up(off + sizeof(int32_t) * kXcds * ((size_t)tiles / kXcds + 1), 256);
+    }
     for (int k = 0; k < n; ++k) {
         L.wsum_off.push_back(off);
         off = align_up(off + sizeof(double) * (size_t)Ns[k] * (size_t)Ps[k], 256);
@@ -234,6 +242,7 @@ Tables tables_at(void *ws, const Layout &L, int n) {
     t.breeds = t.tiles + 3 * (n + 1);
     t.sq = (int32_t *)(b + L.pre_off) + 4 * (n + 1);
     t.sq_list = (int32_t *)(b + L.list_off);
+    t.tile_list = L.tile_off ? (int32_t *)(b + L.tile_off) : nullptr;
     t.n_inst = n;
     return t;
 }
@@ -266,13 +275,14 @@ hipError_t run_fitness(const Tables &t, const Shape &sh, int form, int parity, i
         // with every N <= 64 no individual is left to the pair-sum and the finish
         if (e != hipSuccess || sh.max_n <= kRouteAllPairsMaxN) return e;
     }
+    const int tile_listed = sh.frac > 0.0 && t.tile_list && sh.tiles > kTileListMin ? 1 : 0;
     if (form == PGA_FORM_FP64) {
-        e = timed(0, s, [&] { return launch_pairsum_fp64(t, sh.tiles, parity, sh.v, s); });
+        e = timed(0, s, [&] { return launch_pairsum_fp64(t, sh.tiles, parity, tile_listed, sh.v, s); });
     } else {
         if (sh.v.kind == kKindPacked &&
             (e = timed(11, s, [&] { return launch_nsmask(t, sh.inds, sh.max_n, parity, s); })) != hipSuccess)
             return e;
-        e = timed(1, s, [&] { return launch_pairsum_mfma(t, sh.tiles, parity, sh.v, sh.max_n, s); });
+        e = timed(1, s, [&] { return launch_pairsum_mfma(t, sh.tiles, parity, tile_listed, sh.v, sh.max_n, s); });
     }
     if (e != hipSuccess) return e;
     return timed(2, s, [&] { return launch_finish(t, sh.inds, sh.max_n, parity, listed, status, s); });
@@ -777,7 +787,7 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     int32_t *pf = (int32_t *)(hb + L.pre_off);
     int32_t *pi = pf + (nb + 1), *pe = pi + (nb + 1), *pb = pe + (nb + 1);
     pf[0] = pi[0] = pe[0] = pb[0] = 0;
-    memset(pb + (nb + 1), 0, sizeof(int32_t) * kListCounters);     // the dense lists start empty
+    memset(pb + (nb + 1), 0, sizeof(int32_t) * (kListCounters + kTileCounters));     // the lists start empty
     Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0, BreedShape{0, 0, 0}, 0};
     int total_p = 0;
     for (int k = 0; k < n_inst; ++k) {

@@ -50,12 +50,12 @@ struct Tables {
     const int32_t *breeds;      // prefix of breed workgroups (of the launch's BreedShape)
     int32_t *sq;                // dense list counters (see list_count)
     int32_t *sq_list;           // dense list entries (see list_entry)
+    int32_t *tile_list;         // pair-sum tiles to do (see tile_count); null in a workspace without room for them
     int32_t n_inst;
 };
 
 // Workgroups of one launch are handed to the eight XCDs in turn (workgroup i
 // to XCD i mod 8), each XCD with its own L2.
-constexpr int kXcds = 8;
 
 // Dense list. With the cluster-pair route on, a large launch's cluster-pair
 // kernel lists the individuals that it leaves to the pair-sum and the finish, so
@@ -66,6 +66,11 @@ constexpr int kXcds = 8;
 // evaluation before it used.
 constexpr int kListSlices = 1024;
 constexpr int kListCounters = 2 * kListSlices;     // [parity][slice]
+// Tile lists, one per XCD: counters [parity][XCD], a line each for the entries and for the next to take,
+// behind the dense list's.
+constexpr int kXcds = 8;
+constexpr int kTileCounterStride = 32;
+constexpr int kTileCounters = 2 * kXcds * 2 * kTileCounterStride;
 // Slices in use for a launch of n_wg groups of four individuals (group i's go to
 // slice i mod slices; one slice per group up to kListSlices, so the list launches
 // of a small population are no larger than a workgroup per individual), and
@@ -315,6 +320,74 @@ __device__ __forceinline__ bool inst_stopped(const InstDesc &d) {
     return d.term != nullptr && gld(&d.term->stopped) != 0;
 }
 
+// Tile lists of launches with more than kTileListMin pair-sum tiles: k_tiles lists the tiles that hold an
+// individual of the pair-sum's, and kTileListGrid workgroups take them one by one, each from its XCD's list
+// first (the tiles that share C and labels stay on one XCD). Where the cluster-pair kernel has most
+// individuals, a workgroup per tile only to find that out took 83 us for the 79 000 tiles of 256 instances of N ~
+// U{32..512}, P = 512; the two launches take 29 us there. (Without a list, 8 tiles a workgroup: 47 us, but
+// 5 to 12% slower where every tile is to do.) Where every tile is to do the list costs 2% (15 000 tiles of N ~ 700),
+// so smaller launches, which have less to gain, keep a workgroup per tile.
+__device__ __forceinline__ int32_t *tile_count(const Tables &t, int parity, int xcd) {
+    return t.sq + kListCounters + (parity * kXcds + xcd) * 2 * kTileCounterStride;
+}
+__device__ __forceinline__ int32_t *tile_next(const Tables &t, int parity, int xcd) {
+    return tile_count(t, parity, xcd) + kTileCounterStride;
+}
+__device__ __forceinline__ int tile_list_cap(int total) { return total / kXcds + 1; }
+
+// Descriptors and prefixes do not change during a launch; through the constant address space their loads
+// stay scalar in a loop that stores (as vector loads they put every address made from them into
+// vector registers: 1.1 to 1.4 times the pair-sums' time).
+#define PGA_CONST __attribute__((address_space(4)))
+__device__ __forceinline__ const InstDesc &desc_const(const Tables &t, int k) {
+    return *(const InstDesc *)(const PGA_CONST InstDesc *)(uintptr_t)(t.desc + k);
+}
+__device__ __forceinline__ int find_inst_const(const int32_t *prefix, int n, int t) {
+    return find_inst((const int32_t *)(const PGA_CONST int32_t *)(uintptr_t)prefix, n, t);
+}
+
+// work(tile) for every listed tile, by the whole workgroup. Only thread 0 looks at what changes during the
+// launch (the next tile to take) and hands its tile to the others. While more than two tiles a workgroup are left
+// it takes one ahead, so that the two latencies of a tile pass behind the work (48 instances of N ~ 145, every
+// tile to do: 7.4 ms for 10 generations against 8.4); near the end a tile taken ahead would wait for a busy
+// workgroup (256 instances, few tiles: 34 us a launch against 23).
+template <typename F>
+__device__ __forceinline__ void each_listed_tile(const Tables &t, int parity, int total, F &&work) {
+    __shared__ int taken[2];
+    const int cap = tile_list_cap(total);
+    for (int o = 0; o < kXcds; ++o) {
+        const int x = ((int)blockIdx.x + o) % kXcds;
+        const int n = __builtin_amdgcn_readfirstlane(gld(tile_count(t, parity, x)));   // the same in every wave
+        if (n == 0) continue;
+        const int32_t *list = t.tile_list + (size_t)x * cap;
+        int32_t *next = tile_next(t, parity, x);
+        __syncthreads();                                   // taken is free
+        const int margin = 2 * (int)gridDim.x / kXcds;
+        auto take = [&] { return gld(next) >= n ? n : atomicAdd(next, 1); };   // (an old value of next: the sum is >= n)
+        auto take_ahead = [&](int i) { return i + margin < n ? atomicAdd(next, 1) : -1; };   // -1: not yet
+        auto tile_of = [&](int i) { return i < n ? gld(list + i) : -1; };
+        int ahead = -1;                                    // thread 0's
+        if (threadIdx.x == 0) {
+            const int i = take();
+            taken[0] = tile_of(i);
+            ahead = take_ahead(i);
+        }
+        for (int k = 0;; ++k) {
+            __syncthreads();                               // taken[k & 1] is there, the other one and the work's LDS free
+            const int tile = __builtin_amdgcn_readfirstlane(taken[k & 1]);
+            if (tile < 0) break;
+            int after = -1;
+            const bool have = ahead >= 0;
+            if (threadIdx.x == 0 && have) {
+                after = tile_of(ahead);
+                ahead = take_ahead(ahead);
+            }
+            work(tile);
+            if (threadIdx.x == 0) taken[(k + 1) & 1] = have ? after : tile_of(take());
+        }
+    }
+}
+
 // Total order used for ranking, elites and tournaments: higher fitness first,
 // then lower index. -inf compares equal to -inf, so ties among invalid
 // individuals also go to the lower index.
@@ -349,8 +422,8 @@ hipError_t launch_ewma(const double *R, int N, int T, int64_t ld, double lam, in
                        double *C, uint16_t *hi, uint16_t *lo, double *ws, double *part, int32_t *status, hipStream_t s);
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix2, hipStream_t s);
-hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, const Variant &v, hipStream_t s);
-hipError_t launch_pairsum_mfma(Tables t, int total_tiles, int parity, const Variant &v, int max_n,
+hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, int listed, const Variant &v, hipStream_t s);
+hipError_t launch_pairsum_mfma(Tables t, int total_tiles, int parity, int listed, const Variant &v, int max_n,
                                hipStream_t s);
 hipError_t launch_scale_split(Tables t, int max_ld, hipStream_t s);
 hipError_t launch_nsmask(Tables t, int total_inds, int max_n, int parity, hipStream_t s);
@@ -390,6 +463,10 @@ inline BreedShape breed_shape(int inds) {
 }
 inline int breed_blocks(int N, int P, const BreedShape &b) { return ceil_div(P, breed_split(N, b).chr); }
 hipError_t launch_init(Tables t, int blocks, const BreedShape &b, hipStream_t s);
+constexpr int kTileListMin = 16384, kTileListGrid = 1024;   // grid: four workgroups a CU, what their registers allow
+// (a value of bucket(), so that launches of one captured shape agree on it)
+// Lists the tiles of the launch; per = individuals of a tile.
+hipError_t launch_tiles(Tables t, int total_tiles, int parity, int order, int per, hipStream_t s);
 hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s);
 // Launches of at least kManyInds individuals (more than the chip holds at a
