@@ -198,7 +198,7 @@ template <int B, bool LISTED>
 __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int order) {
     __shared__ int4 lab_s[kFp64Waves][2][64][B / 4];
 
-    const int total = t.tiles[t.n_inst];                  // the grid may exceed it (capacity-sized graph)
+    const int total = const_at(t.tiles, t.n_inst);                  // the grid may exceed it (capacity-sized graph)
     if ((int)blockIdx.x >= total) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
     const int lane = threadIdx.x & 63;
@@ -352,30 +352,30 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
     };
     if constexpr (LISTED) {
         each_listed_tile(t, parity, total, [&](int tile) {
-            const int k = find_inst_const(t.tiles, t.n_inst, tile);
-            work(desc_const(t, k), tile - ((const PGA_CONST int32_t *)(uintptr_t)t.tiles)[k]);
+            const int k = find_inst(t.tiles, t.n_inst, tile);
+            work(const_at(t.desc, k), tile - const_at(t.tiles, k));
         });
     } else {
         const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
         const int k = find_inst(t.tiles, t.n_inst, tile);
-        const InstDesc &d = t.desc[k];
+        const InstDesc &d = const_at(t.desc, k);
         if (inst_stopped(d)) return;
-        work(d, tile - t.tiles[k]);
+        work(d, tile - const_at(t.tiles, k));
     }
 }
 
 // The tiles with an individual of the pair-sum's, listed by XCD in tile order: a thread per tile, an append per wave.
 __global__ __launch_bounds__(256) void k_tiles(Tables t, int parity, int order, int per) {
-    const int total = t.tiles[t.n_inst], cap = tile_list_cap(total), span = (cap + 63) & ~63;
+    const int total = const_at(t.tiles, t.n_inst), cap = tile_list_cap(total), span = (cap + 63) & ~63;
     const int g = blockIdx.x * 256 + threadIdx.x, x = __builtin_amdgcn_readfirstlane(g / span), b = (g % span) * kXcds + x;
     if (x >= kXcds) return;
     bool active = false;
     const int tile = order ? xcd_tile(min(b, total - 1), total) : b;
     if (b < total) {
         const int k = find_inst(t.tiles, t.n_inst, tile);
-        const InstDesc &d = t.desc[k];
+        const InstDesc &d = const_at(t.desc, k);
         if (!inst_stopped(d)) {
-            const int local = tile - t.tiles[k], n_pairs = ((d.N + 63) / 64 + 1) / 2;
+            const int local = tile - const_at(t.tiles, k), n_pairs = ((d.N + 63) / 64 + 1) / 2;
             const int p0 = tile_pos(local, n_pairs, (d.P + per - 1) / per, order).pb * per;
             int any = 0;
             for (int p = p0; p < p0 + per; p += 4)
@@ -552,7 +552,7 @@ __device__ __forceinline__ void finish_terms(const InstDesc &d, int p, int N, co
 __device__ __forceinline__ void finish_one(const Tables &t, int k, int p, int max_n, int parity, int32_t *status,
                                            unsigned char *smem) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, tid = threadIdx.x;
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     if (inst_stopped(d)) return;                     // uniform over the workgroup
     const int N = d.N;
     if (d.route && gld(d.route + p) == 0) return;    // evaluated by the cluster-pair kernel
@@ -655,9 +655,9 @@ __device__ __forceinline__ void finish_one(const Tables &t, int k, int p, int ma
 __global__ __launch_bounds__(kFinThreads) void k_finish(Tables t, int max_n, int parity, int32_t *status) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int g = blockIdx.x;
-    if (g >= t.inds[t.n_inst]) return;               // the grid may exceed the total (capacity-sized graph)
+    if (g >= const_at(t.inds, t.n_inst)) return;               // the grid may exceed the total (capacity-sized graph)
     const int k = find_inst(t.inds, t.n_inst, g);
-    finish_one(t, k, g - t.inds[k], max_n, parity, status, smem);
+    finish_one(t, k, g - const_at(t.inds, k), max_n, parity, status, smem);
 }
 
 // Listed (cluster-pair route on, large launches): per slice of this parity's
@@ -776,7 +776,7 @@ __device__ __forceinline__ void to_dense(const Tables &t, const InstDesc &d, int
                                          int slices, int cap) {
     gst(d.route + p, 1);
     if (!listed) return;
-    const int slice = ((t.inds[k] + p) >> 2) % slices;
+    const int slice = ((const_at(t.inds, k) + p) >> 2) % slices;
     int32_t *e = list_entry(t, slice, cap, atomicAdd(list_count(t, parity, slice), 1));
     gst(e, p);
     gst(e + 1, k);
@@ -1254,18 +1254,18 @@ __global__ __launch_bounds__(256, 8) void k_eval(Tables t, int parity, double fr
         gst(tile_count(t, parity ^ 1, threadIdx.x), 0);
         gst(tile_next(t, parity ^ 1, threadIdx.x), 0);
     }
-    if (b >= t.evals[t.n_inst]) return;              // the grid may exceed the total (capacity-sized graph)
+    if (b >= const_at(t.evals, t.n_inst)) return;              // the grid may exceed the total (capacity-sized graph)
     // Workgroups go to the XCDs in turn; runs of kEvalRun consecutive ones are given to one XCD, so
     // that it reads the C of few instances at a time (256 instances, N ~ U{32..512}: 334 us without,
     // 290 with runs of 128 to 512; a run of an eighth of the launch is less even).
-    const int total = t.evals[t.n_inst], run8 = b / (kXcds * kEvalRun), in8 = b % (kXcds * kEvalRun);
+    const int total = const_at(t.evals, t.n_inst), run8 = b / (kXcds * kEvalRun), in8 = b % (kXcds * kEvalRun);
     const int bb = (run8 + 1) * kXcds * kEvalRun > total
                        ? b
                        : run8 * kXcds * kEvalRun + in8 % kXcds * kEvalRun + in8 / kXcds;
     const int k = find_inst(t.evals, t.n_inst, bb);
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     if (inst_stopped(d)) return;
-    const int N = d.N, local = bb - t.evals[k];
+    const int N = d.N, local = bb - const_at(t.evals, k);
     if (N <= 32) eval_pairs<16, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
     else if (N <= 64) eval_pairs<32, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
     else if (N <= 512) eval_pairs<64, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
@@ -1288,7 +1288,7 @@ hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int par
 // Contiguous copy of the diagonal of every instance's C (one workgroup per
 // instance, blockIdx.y), and diag[N] = 1 if every C_jj is 1, else 0.
 __global__ __launch_bounds__(256) void k_diag(Tables t) {
-    const InstDesc &d = t.desc[blockIdx.y];
+    const InstDesc &d = const_at(t.desc, blockIdx.y);
     if (!d.diag || d.P == 0) return;                 // uniform
     int ones = 1;
     for (int j = threadIdx.x; j < d.N; j += 256) {

@@ -26,12 +26,12 @@ typedef int32_t gene4 __attribute__((ext_vector_type(4), aligned(4)));
 // five of its lanes at work; 14.6 us).
 __global__ __launch_bounds__(256) void k_init(Tables t, BreedShape shape) {
     const int wg = blockIdx.x;
-    if (wg >= t.breeds[t.n_inst]) return;                  // the grid may exceed the total (capacity-sized graph)
+    if (wg >= const_at(t.breeds, t.n_inst)) return;                  // the grid may exceed the total (capacity-sized graph)
     const int k = find_inst(t.breeds, t.n_inst, wg);
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     const int N = d.N, tid = threadIdx.x;
     const BreedSplit split = breed_split(N, shape);
-    const int c0 = (wg - t.breeds[k]) * split.chr, gl = tid & (split.gl - 1);
+    const int c0 = (wg - const_at(t.breeds, k)) * split.chr, gl = tid & (split.gl - 1);
     if (c0 == 0 && tid == 0 && d.term) {
         pga_term_state z;
         z.ref = -INFINITY;
@@ -335,7 +335,7 @@ __device__ void term_update(const InstDesc &d, pga_term_state st, double b, int 
 
 __global__ __launch_bounds__(kRankThreads) void k_rank(Tables t, int gen_off, int final) {
     __shared__ RankLds sh;
-    const InstDesc &d = t.desc[blockIdx.x];
+    const InstDesc &d = const_at(t.desc, blockIdx.x);
     if (d.P == 0) return;                                  // a padding slot of a capacity-sized launch
     const int P = d.P, E = d.E;
     // The fitness values, the stop flag and (thread 0) the termination state are
@@ -394,7 +394,7 @@ __device__ __forceinline__ int tournament2(const double *f, int a, int b) {
 //                 segment holds it; child E + j uses pointers pi(2j), pi(2j+1).
 __global__ __launch_bounds__(256) void k_sus_rank(Tables t) {
     __shared__ double fq[256];
-    const InstDesc &d = t.desc[blockIdx.z];
+    const InstDesc &d = const_at(t.desc, blockIdx.z);
     if (d.P == 0 || d.selection != PGA_SELECT_SUS || inst_stopped(d)) return;
     const int P = d.P;
     const int p0 = blockIdx.x * 256, q0 = blockIdx.y * 256;
@@ -447,7 +447,7 @@ __device__ __forceinline__ uint64_t isqrt_u48(uint64_t x) {
 __global__ __launch_bounds__(1024) void k_sus_prefix(Tables t) {
     __shared__ uint64_t wsum[16];
     __shared__ uint64_t carry_s;
-    const InstDesc &d = t.desc[blockIdx.x];
+    const InstDesc &d = const_at(t.desc, blockIdx.x);
     if (d.P == 0 || d.selection != PGA_SELECT_SUS || inst_stopped(d)) return;
     const int P = d.P;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -591,7 +591,7 @@ __global__ __launch_bounds__(T) void k_rank_sus(Tables t, int gen_off) {
     __shared__ int wi[kRankWaves];
     __shared__ uint8_t round_s[4 << kSusHalfBits];           // the pairing's round function: [round][right half]
     __shared__ int first;
-    const InstDesc &d = t.desc[blockIdx.x];
+    const InstDesc &d = const_at(t.desc, blockIdx.x);
     if (d.P == 0) return;                                    // a padding slot of a capacity-sized launch
     const int P = d.P, E = d.E, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const double *__restrict__ f = d.fitness;
@@ -831,7 +831,7 @@ __device__ int sus_parent(const InstDesc &d, int c, uint32_t gen, int which, int
 // (tournaments): no rank launch between fitness and breeding.
 __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, int gen_off) {
     __shared__ RankLds sh;
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     const int P = d.P, E = d.E, N = d.N;
     if (P == 0 || (E == 0 && !d.term && !d.stats)) return;   // a padding slot, or nothing to rank
     if (inst_stopped(d)) {                                 // by an earlier call: it stays as it is
@@ -908,17 +908,17 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
         }
         wg -= t.n_inst;
     }
-    const int total = t.breeds[t.n_inst];
+    const int total = const_at(t.breeds, t.n_inst);
     if (wg >= total) return;                               // the grid may exceed the total (capacity-sized graph)
     // runs of workgroups of up to 512 children on one XCD: its L2 holds their instance's parents
     const int run = shape.run, run8 = wg / (kXcds * run), in8 = wg % (kXcds * run);
     if ((run8 + 1) * kXcds * run <= total) wg = run8 * kXcds * run + in8 % kXcds * run + in8 / kXcds;
     const int k = find_inst(t.breeds, t.n_inst, wg);
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     if (inst_stopped(d)) return;                           // set by this generation's rank
     const int N = d.N, P = d.P, E = d.E, tid = threadIdx.x;
     const BreedSplit split = breed_split(N, shape);
-    const int chr = split.chr, gl_n = split.gl, c0 = (wg - t.breeds[k]) * chr;
+    const int chr = split.chr, gl_n = split.gl, c0 = (wg - const_at(t.breeds, k)) * chr;
     const int32_t *__restrict__ src = d.pop[parity];
     const uint32_t gen = d.gen0 + (uint32_t)gen_off;
     const bool sus = d.selection == PGA_SELECT_SUS;
@@ -1016,12 +1016,12 @@ hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, i
 // for 128 000 of N = 18 without a row to copy; 3.9 us).
 __global__ __launch_bounds__(256) void k_copy_back(Tables t, int G, BreedShape shape) {
     const int wg = blockIdx.x;
-    if (wg >= t.breeds[t.n_inst]) return;                  // the grid may exceed the total (capacity-sized graph)
+    if (wg >= const_at(t.breeds, t.n_inst)) return;                  // the grid may exceed the total (capacity-sized graph)
     const int k = find_inst(t.breeds, t.n_inst, wg);
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     const int bred = d.term ? gld(&d.term->call_gens) : G;
     if ((bred & 1) == 0) return;
-    const int N = d.N, chr = breed_split(N, shape).chr, c0 = (wg - t.breeds[k]) * chr;
+    const int N = d.N, chr = breed_split(N, shape).chr, c0 = (wg - const_at(t.breeds, k)) * chr;
     const int len = min(chr, d.P - c0) * N;
     const int32_t *__restrict__ a = d.pop[1] + (size_t)c0 * N;
     int32_t *__restrict__ b = d.pop[0] + (size_t)c0 * N;

@@ -618,11 +618,11 @@ __device__ __forceinline__ void mfma_block_lut(const InstDesc &d, int jb, int pb
 __global__ __launch_bounds__(256) void k_nsmask(Tables t, int parity) {
     extern __shared__ int ns_cnt[];
     const int gi = blockIdx.x;
-    if (gi >= t.inds[t.n_inst]) return;
+    if (gi >= const_at(t.inds, t.n_inst)) return;
     const int k = find_inst(t.inds, t.n_inst, gi);
-    const InstDesc &d = t.desc[k];
+    const InstDesc &d = const_at(t.desc, k);
     if (!d.ns2 || inst_stopped(d)) return;                    // uniform
-    const int p = gi - t.inds[k];
+    const int p = gi - const_at(t.inds, k);
     if (d.route && gld(d.route + p) == 0) return;
     const int N = d.N;
     const int32_t *lab = d.pop[parity] + (size_t)p * N;
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     KIND == kKindLut ? (B == 8 ? 2 : 3) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
                                                                                      int order, int cstride) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int total = t.tiles[t.n_inst];                  // the grid may exceed it (capacity-sized graph)
+    const int total = const_at(t.tiles, t.n_inst);                  // the grid may exceed it (capacity-sized graph)
     if ((int)blockIdx.x >= total) return;
     auto work = [&](const InstDesc &d, int local) {
     const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
@@ -996,15 +996,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     };
     if constexpr (LISTED) {
         each_listed_tile(t, parity, total, [&](int tile) {
-            const int k = find_inst_const(t.tiles, t.n_inst, tile);
-            work(desc_const(t, k), tile - ((const PGA_CONST int32_t *)(uintptr_t)t.tiles)[k]);
+            const int k = find_inst(t.tiles, t.n_inst, tile);
+            work(const_at(t.desc, k), tile - const_at(t.tiles, k));
         });
     } else {
         const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
         const int k = find_inst(t.tiles, t.n_inst, tile);
-        const InstDesc &d = t.desc[k];
+        const InstDesc &d = const_at(t.desc, k);
         if (inst_stopped(d)) return;                          // uniform over the workgroup
-        const int local = tile - t.tiles[k], n_pairs = ((d.N + kMfmaCols - 1) / kMfmaCols + 1) / 2;
+        const int local = tile - const_at(t.tiles, k), n_pairs = ((d.N + kMfmaCols - 1) / kMfmaCols + 1) / 2;
         const int pb = tile_pos(local, n_pairs, (d.P + B - 1) / B, order).pb;
         if (d.route) {                                        // uniform: skip batches the cluster-pair
             int any = 0;                                      // kernel evaluated entirely
@@ -1085,7 +1085,7 @@ __device__ __forceinline__ uint32_t scale2(uint32_t w) {
 }
 
 __global__ __launch_bounds__(256) void k_scale_split(Tables t) {
-    const InstDesc &d = t.desc[blockIdx.y];
+    const InstDesc &d = const_at(t.desc, blockIdx.y);
     if (d.P == 0) return;                                     // a padding slot of a capacity-sized launch
     const size_t n8 = (size_t)d.ld_h * d.ld_h / 8;            // ld is a multiple of 32
     const size_t ld = (size_t)d.ld_h;

@@ -305,12 +305,22 @@ __device__ __forceinline__ uint4 gld_u4(const void *p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// Descriptors and prefixes do not change during a launch. Through the constant address space their loads are
+// scalar also behind a store (of which the compiler cannot tell that it leaves them alone): as vector loads the
+// lookup of a workgroup's instance and descriptor was a chain of up to a dozen memory latencies in
+// the cluster-pair kernel, and put the pair-sums' addresses into vector registers.
+#define PGA_CONST __attribute__((address_space(4)))
+template <typename T>
+__device__ __forceinline__ const T &const_at(const T *p, int i) {
+    return *(const T *)(const PGA_CONST T *)(uintptr_t)(p + i);
+}
+
 // Instance lookup: largest k with prefix[k] <= t (prefix is exclusive, n + 1 entries).
 __device__ __forceinline__ int find_inst(const int32_t *prefix, int n, int t) {
     int lo = 0, hi = n - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (prefix[mid] <= t) lo = mid; else hi = mid - 1;
+        if (const_at(prefix, mid) <= t) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -334,17 +344,6 @@ __device__ __forceinline__ int32_t *tile_next(const Tables &t, int parity, int x
     return tile_count(t, parity, xcd) + kTileCounterStride;
 }
 __device__ __forceinline__ int tile_list_cap(int total) { return total / kXcds + 1; }
-
-// Descriptors and prefixes do not change during a launch; through the constant address space their loads
-// stay scalar in a loop that stores (as vector loads they put every address made from them into
-// vector registers: 1.1 to 1.4 times the pair-sums' time).
-#define PGA_CONST __attribute__((address_space(4)))
-__device__ __forceinline__ const InstDesc &desc_const(const Tables &t, int k) {
-    return *(const InstDesc *)(const PGA_CONST InstDesc *)(uintptr_t)(t.desc + k);
-}
-__device__ __forceinline__ int find_inst_const(const int32_t *prefix, int n, int t) {
-    return find_inst((const int32_t *)(const PGA_CONST int32_t *)(uintptr_t)prefix, n, t);
-}
 
 // work(tile) for every listed tile, by the whole workgroup. Only thread 0 looks at what changes during the
 // launch (the next tile to take) and hands its tile to the others. While more than two tiles a workgroup are left
