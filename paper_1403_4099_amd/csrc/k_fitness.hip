@@ -901,7 +901,7 @@ __device__ __attribute__((noinline)) void dense_small(const InstDesc &d, int p, 
 template <int GL, int SL>
 __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, int k, int local, int parity,
                                            double frac, int listed, int slices, int cap, int form, int32_t *status,
-                                           unsigned char *smem) {
+                                           unsigned char *smem, int32_t stopped) {
     constexpr bool kBlock = GL == 256;
     constexpr int WL = kBlock ? 64 : GL;             // lanes that vote together
     constexpr int NW = kBlock ? 4 : 1;               // such sets per individual
@@ -947,6 +947,7 @@ __device__ __forceinline__ void eval_pairs(const Tables &t, const InstDesc &d, i
         lr[u] = j < N ? (uint32_t)gld(lab + j) : 0u;
     }
     const bool ones = gld(d.diag + N) == 1.0;        // every C_jj is 1 (uniform)
+    if (flag_stops(d, stopped)) return;              // uniform over the workgroup
     bool badl = false;
 #pragma unroll
     for (int u = 0; u < SL; ++u) {
@@ -1264,16 +1265,16 @@ __global__ __launch_bounds__(256, 8) void k_eval(Tables t, int parity, double fr
                        : run8 * kXcds * kEvalRun + in8 % kXcds * kEvalRun + in8 / kXcds;
     const int k = find_inst(t.evals, t.n_inst, bb);
     const InstDesc &d = const_at(t.desc, k);
-    if (inst_stopped(d)) return;
+    const int32_t stopped = stop_flag(d, t);         // tested behind the label loads
     const int N = d.N, local = bb - const_at(t.evals, k);
-    if (N <= 32) eval_pairs<16, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
-    else if (N <= 64) eval_pairs<32, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
-    else if (N <= 512) eval_pairs<64, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+    if (N <= 32) eval_pairs<16, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem, stopped);
+    else if (N <= 64) eval_pairs<32, 2>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem, stopped);
+    else if (N <= 512) eval_pairs<64, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem, stopped);
     else if (N <= kSparseMaxN)
-        eval_pairs<256, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem);
+        eval_pairs<256, 8>(t, d, k, local, parity, frac, listed, slices, cap, form, status, smem, stopped);
     else {
         const int p = 256 * local + threadIdx.x;
-        if (p < d.P) to_dense(t, d, k, p, parity, listed, slices, cap);
+        if (p < d.P && !flag_stops(d, stopped)) to_dense(t, d, k, p, parity, listed, slices, cap);
     }
 }
 

@@ -915,7 +915,7 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
     if ((run8 + 1) * kXcds * run <= total) wg = run8 * kXcds * run + in8 % kXcds * run + in8 / kXcds;
     const int k = find_inst(t.breeds, t.n_inst, wg);
     const InstDesc &d = const_at(t.desc, k);
-    if (inst_stopped(d)) return;                           // set by this generation's rank
+    const int32_t stopped = stop_flag(d, t);               // set by this generation's rank; tested before the genes
     const int N = d.N, P = d.P, E = d.E, tid = threadIdx.x;
     const BreedSplit split = breed_split(N, shape);
     const int chr = split.chr, gl_n = split.gl, c0 = (wg - const_at(t.breeds, k)) * chr;
@@ -953,6 +953,7 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
             }
         }
     }
+    if (flag_stops(d, stopped)) return;                    // uniform over the workgroup
     __syncthreads();
 
     const int gl = tid & (gl_n - 1), npair = (N + 1) >> 1;

@@ -387,6 +387,18 @@ __device__ __forceinline__ void each_listed_tile(const Tables &t, int parity, in
     }
 }
 
+// The same, to be tested later: the load goes out here, and the test waits for it (by readfirstlane; a load
+// from an address that the compiler knows to be uniform is waited for at once). A memory latency less at
+// the start of every workgroup.
+__device__ __forceinline__ int32_t stop_flag(const InstDesc &d, const Tables &t) {
+    int z = 0;
+    asm("" : "+v"(z));
+    return gld((d.term ? &d.term->stopped : (const int32_t *)t.desc) + z);   // (without a state: any word)
+}
+__device__ __forceinline__ bool flag_stops(const InstDesc &d, int32_t flag) {
+    return d.term && __builtin_amdgcn_readfirstlane(flag) != 0;
+}
+
 // Total order used for ranking, elites and tournaments: higher fitness first,
 // then lower index. -inf compares equal to -inf, so ties among invalid
 // individuals also go to the lower index.
