@@ -19,30 +19,11 @@
 namespace pga {
 
 // ---------------------------------------------------------------------------
-// Descriptor upload for single-instance calls: the descriptor and prefix
-// tables travel as kernel arguments, so no host buffer has to outlive the call.
-struct DescBlob {
-    InstDesc d;
-    int32_t prefix[8];   // {0, tiles}, {0, P}, {0, evaluation blocks}, {0, 0}; the list counters follow, zeroed
-};
-
-__global__ void k_write_desc(DescBlob b, InstDesc *dst, int32_t *prefix) {
-    if (threadIdx.x == 0) *dst = b.d;
-    if (threadIdx.x < 8) prefix[threadIdx.x] = b.prefix[threadIdx.x];
-    for (int i = threadIdx.x; i < kListCounters + kTileCounters; i += blockDim.x) prefix[8 + i] = 0;
-}
+// Descriptor upload alone (the tuner's next variant).
+__global__ __launch_bounds__(256) void k_write_desc(DescBlob b, InstDesc *dst, int32_t *prefix) { write_desc(b, dst, prefix); }
 
 hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, int32_t *prefix, hipStream_t s) {
-    DescBlob b;
-    b.d = d;
-    b.prefix[0] = 0;
-    b.prefix[1] = tiles;
-    b.prefix[2] = 0;
-    b.prefix[3] = d.P;
-    b.prefix[4] = 0;
-    b.prefix[5] = eval_blocks(d.N, d.P);
-    b.prefix[6] = b.prefix[7] = 0;
-    hipLaunchKernelGGL(k_write_desc, dim3(1), dim3(256), 0, s, b, dst, prefix);
+    hipLaunchKernelGGL(k_write_desc, dim3(1), dim3(256), 0, s, DescBlob::of(d, tiles), dst, prefix);
     return hipGetLastError();
 }
 
@@ -1283,27 +1264,6 @@ hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int par
     if (blocks <= 0) return hipSuccess;
     const int n_wg = (total_inds + 3) / 4, slices = list_slices(n_wg), cap = list_slice_cap(n_wg);
     hipLaunchKernelGGL(k_eval, dim3(blocks), dim3(256), lds, s, t, parity, frac, listed, slices, cap, form, status);
-    return hipGetLastError();
-}
-
-// Contiguous copy of the diagonal of every instance's C (one workgroup per
-// instance, blockIdx.y), and diag[N] = 1 if every C_jj is 1, else 0.
-__global__ __launch_bounds__(256) void k_diag(Tables t) {
-    const InstDesc &d = const_at(t.desc, blockIdx.y);
-    if (!d.diag || d.P == 0) return;                 // uniform
-    int ones = 1;
-    for (int j = threadIdx.x; j < d.N; j += 256) {
-        const double c = gld(d.C + (size_t)j * d.N + j);
-        gst(d.diag + j, c);
-        ones &= c == 1.0 ? 1 : 0;
-    }
-    const int all = __syncthreads_and(ones);
-    if (threadIdx.x == 0) gst(d.diag + d.N, all ? 1.0 : 0.0);
-}
-
-hipError_t launch_diag(Tables t, int max_n, hipStream_t s) {
-    if (t.n_inst <= 0 || max_n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_diag, dim3(1, t.n_inst), dim3(256), 0, s, t);
     return hipGetLastError();
 }
 

@@ -1084,12 +1084,10 @@ __device__ __forceinline__ uint32_t scale2(uint32_t w) {
     return (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xFFFF0000u);
 }
 
-__global__ __launch_bounds__(256) void k_scale_split(Tables t) {
-    const InstDesc &d = const_at(t.desc, blockIdx.y);
-    if (d.P == 0) return;                                     // a padding slot of a capacity-sized launch
+__device__ __forceinline__ void scale_split(const InstDesc &d, int block, int blocks) {
     const size_t n8 = (size_t)d.ld_h * d.ld_h / 8;            // ld is a multiple of 32
     const size_t ld = (size_t)d.ld_h;
-    for (size_t v = (size_t)blockIdx.x * 256 + threadIdx.x; v < n8; v += (size_t)gridDim.x * 256) {
+    for (size_t v = (size_t)block * 256 + threadIdx.x; v < n8; v += (size_t)blocks * 256) {
         const size_t row = 8 * v / ld, col = 8 * v % ld;   // 8 consecutive columns of one row
         const size_t dst = ((row >> 4) * (ld >> 5) + (col >> 5)) * 512 + ((((col & 31) >> 3) << 4) + (row & 15)) * 8;
         const uint4 h = gld_u4(d.hi + 8 * v);
@@ -1101,11 +1099,46 @@ __global__ __launch_bounds__(256) void k_scale_split(Tables t) {
     }
 }
 
-hipError_t launch_scale_split(Tables t, int max_ld, hipStream_t s) {
-    if (t.n_inst <= 0 || max_ld <= 0) return hipSuccess;
-    const size_t n8 = (size_t)max_ld * max_ld / 8;
-    const int gx = (int)std::min<size_t>((n8 + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_scale_split, dim3(gx, t.n_inst), dim3(256), 0, s, t);
+// Contiguous copy of the diagonal of C, and diag[N] = 1 if every C_jj is 1, else 0; by one workgroup.
+__device__ __forceinline__ void copy_diag(const InstDesc &d) {
+    int ones = 1;
+    for (int j = threadIdx.x; j < d.N; j += 256) {
+        const double c = gld(d.C + (size_t)j * d.N + j);
+        gst(d.diag + j, c);
+        ones &= c == 1.0 ? 1 : 0;
+    }
+    const int all = __syncthreads_and(ones);
+    if (threadIdx.x == 0) gst(d.diag + d.N, all ? 1.0 : 0.0);
+}
+
+// What an evaluation needs of an instance (blockIdx.y) beside its labels, in one launch: the scaled split parts
+// (workgroups below `splits`), the diagonal (the next one) and, in a single-instance call, the descriptor
+// and prefix tables, which travel as kernel arguments so that no host buffer has to outlive the call (the last).
+// As launches of their own they were a quarter of a small call: N = 333, P = 777, BF16x2, descriptors twice, split
+// and diagonal 2.0 + 3.4 + 2.0 + 2.1 us and three gaps of the call's 40; this
+// launch takes 3.6 and the call 33.
+template <bool SINGLE>
+__global__ __launch_bounds__(256) void k_prep(Tables t, DescBlob b, InstDesc *dst, int32_t *prefix, int splits) {
+    const InstDesc &d = SINGLE ? b.d : const_at(t.desc, blockIdx.y);
+    if (d.P == 0) return;                                     // a padding slot of a capacity-sized launch
+    if ((int)blockIdx.x < splits) scale_split(d, blockIdx.x, splits);
+    else if ((int)blockIdx.x == splits) {
+        if (d.diag) copy_diag(d);
+    } else {
+        write_desc(b, dst, prefix);
+    }
+}
+
+hipError_t launch_prep(const Tables &t, const InstDesc *single, int32_t tiles, int max_ld, hipStream_t s) {
+    if (t.n_inst <= 0) return hipSuccess;
+    const size_t n8 = (size_t)max_ld * max_ld / 8;            // max_ld 0: no split parts
+    const int splits = (int)std::min<size_t>((n8 + 255) / 256, 1024);
+    if (single)
+        hipLaunchKernelGGL(k_prep<true>, dim3(splits + 2), dim3(256), 0, s, t, DescBlob::of(*single, tiles),
+                           (InstDesc *)t.desc, (int32_t *)t.tiles, splits);
+    else
+        hipLaunchKernelGGL(k_prep<false>, dim3(splits + 1, t.n_inst), dim3(256), 0, s, t, DescBlob{}, (InstDesc *)nullptr,
+                           (int32_t *)nullptr, splits);
     return hipGetLastError();
 }
 

@@ -471,7 +471,7 @@ size_t pga_fitness_ws_bytes(int32_t N, int32_t P, int32_t form) {
 }
 
 namespace {
-// Checks, descriptor and (BF16x2) scaled split for a single-instance fitness
+// Checks, descriptor, diagonal and (BF16x2) scaled split for a single-instance fitness
 // launch; run_fitness then evaluates labels into `fitness`.
 int prepare_single(const double *C, const uint16_t *C_hi, const uint16_t *C_lo, int32_t N,
                    const int32_t *labels, int32_t P, int32_t form, double *fitness, int32_t *n_s,
@@ -520,11 +520,10 @@ int prepare_single(const double *C, const uint16_t *C_hi, const uint16_t *C_lo, 
     sh->frac = frac;
     sh->evals = eval_blocks(N, P);
     sh->lds = eval_lds(N);
+    sh->v = variant_at(form, pick_variant(form, N, P));
+    sh->tiles = dense_tiles(N, P, sh->v, frac);
     *dd = d;
-    if (form == PGA_FORM_BF16X2) {
-        HIP_TRY(launch_write_desc(d, 0, (InstDesc *)t->desc, (int32_t *)t->tiles, s));
-        HIP_TRY(launch_scale_split(*t, d.ld_h, s));
-    }
+    HIP_TRY(launch_prep(*t, &d, sh->tiles, form == PGA_FORM_BF16X2 ? d.ld_h : 0, s));
     return PGA_OK;
 }
 
@@ -559,8 +558,6 @@ int fitness_call(const double *C, const uint16_t *C_hi, const uint16_t *C_lo, in
     const int rc = prepare_single(C, C_hi, C_lo, N, labels, P, form, fitness, n_s, c_s, ws, ws_bytes, s,
                                   &t, &sh, &d, route_frac());
     if (rc != PGA_OK || P == 0) return rc;
-    HIP_TRY(use_variant(d, t, form, pick_variant(form, N, P), &sh, s));
-    if (sh.frac > 0.0) HIP_TRY(launch_diag(t, N, s));
     HIP_TRY(run_fitness(t, sh, form, 0, status, s));
     return PGA_OK;
 }
@@ -864,8 +861,8 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     ctx->upload_pending = true;
 
     Tables t = tables_at(ws, L, nb);
-    if (form == PGA_FORM_BF16X2) HIP_TRY(launch_scale_split(t, split_ld(sh.max_n), s));
-    if (sh.frac > 0.0) HIP_TRY(launch_diag(t, sh.max_n, s));
+    if (form == PGA_FORM_BF16X2 || sh.frac > 0.0)
+        HIP_TRY(launch_prep(t, nullptr, 0, form == PGA_FORM_BF16X2 ? split_ld(sh.max_n) : 0, s));
     if (flags & PGA_EVOLVE_INIT) HIP_TRY(timed(7, s, [&] { return launch_init(t, sh.breeds, sh.breed, s); }));
 
     const bool eager = (flags & PGA_EVOLVE_EAGER) || timing_on();

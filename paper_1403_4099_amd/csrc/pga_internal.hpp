@@ -436,13 +436,31 @@ hipError_t launch_write_desc(const InstDesc &d, int32_t tiles, InstDesc *dst, in
 hipError_t launch_pairsum_fp64(Tables t, int total_tiles, int parity, int listed, const Variant &v, hipStream_t s);
 hipError_t launch_pairsum_mfma(Tables t, int total_tiles, int parity, int listed, const Variant &v, int max_n,
                                hipStream_t s);
-hipError_t launch_scale_split(Tables t, int max_ld, hipStream_t s);
 hipError_t launch_nsmask(Tables t, int total_inds, int max_n, int parity, hipStream_t s);
 // listed: evaluate the dense list of this parity (cluster-pair route on), else every individual.
 hipError_t launch_finish(Tables t, int total_inds, int max_n, int parity, int listed, int32_t *status, hipStream_t s);
-hipError_t launch_diag(Tables t, int max_n, hipStream_t s);
 // Cluster-pair workgroups of an instance, and the LDS of one of them.
 int eval_blocks(int N, int P);
+// The tables of a single-instance call, as a kernel argument.
+struct DescBlob {
+    InstDesc d;
+    int32_t prefix[8];   // {0, tiles}, {0, P}, {0, evaluation blocks}, {0, 0}; the list counters follow, zeroed
+    static DescBlob of(const InstDesc &d, int32_t tiles) {
+        DescBlob b{};
+        b.d = d;
+        b.prefix[1] = tiles;
+        b.prefix[3] = d.P;
+        b.prefix[5] = eval_blocks(d.N, d.P);
+        return b;
+    }
+};
+__device__ __forceinline__ void write_desc(const DescBlob &b, InstDesc *dst, int32_t *prefix) {   // one workgroup
+    if (threadIdx.x == 0) *dst = b.d;
+    if (threadIdx.x < 8) prefix[threadIdx.x] = b.prefix[threadIdx.x];
+    for (int i = threadIdx.x; i < kListCounters + kTileCounters; i += blockDim.x) prefix[8 + i] = 0;
+}
+// Split parts (max_ld > 0), diagonals and, single != null, the tables of a call.
+hipError_t launch_prep(const Tables &t, const InstDesc *single, int32_t tiles, int max_ld, hipStream_t s);
 size_t eval_lds(int N);
 // listed: fill the dense list (kManyInds individuals or more).
 hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int parity, double frac, int listed, int form,
