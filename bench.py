@@ -150,7 +150,7 @@ def batched_run(n_inst, form, generations=200, reps=2, tune_table=None):
         byts += I.P * 4.0 * I.N + 8.0 * float(on.sum()) + 8.0 * float(wp[on].sum()) + 8.0 * I.N
     ach = byts / t_cp / 1e9
     roof = {"bound": "hbm", "achieved": ach, "peak": PEAK_HBM, "unit": "GB/s", "frac": ach / PEAK_HBM,
-            "traffic": None, "kernel": "k_route + k_sparse_wave", "avg_launch_us": 1e6 * t_cp,
+            "traffic": None, "kernel": "k_eval", "avg_launch_us": 1e6 * t_cp,
             "listed_share": listed / Ps,
             "work_per_launch": "every individual's labels (4N B), and for those within the pair limit the "
                                "fitness (8 B) and their within-cluster C entries (8 B each); each instance's "
@@ -515,7 +515,7 @@ def route_section(args, forms, results, insts, timed, step, pop0, route_default,
     route["roofline"] = {"bound": "hbm", "achieved": ach, "peak": PEAK_HBM, "unit": "GB/s", "frac": ach / PEAK_HBM,
                          "traffic": recorded_traffic(os.path.join(ROOT, "paper_1403_4099_amd", "csrc",
                                                                   "k_fitness.hip"), N, P, -1),
-                         "kernel": "k_sparse", "avg_launch_us": 1e6 * t_route,
+                         "kernel": "k_eval", "avg_launch_us": 1e6 * t_route,
                          "work_per_launch": "labels (4N B), within-cluster C entries (8 B each, "
                                             f"{float(wp0.mean()):.0f} pairs per individual), fitness, diagonal "
                                             "once, on the random generation-0 population"}
