@@ -179,8 +179,8 @@ template <int B, bool LISTED>
 __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int order) {
     __shared__ int4 lab_s[kFp64Waves][2][64][B / 4];
 
-    const int total = const_at(t.tiles, t.n_inst);                  // the grid may exceed it (capacity-sized graph)
-    if ((int)blockIdx.x >= total) return;
+    const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
+    if (none_dense(t, parity) | ((int)blockIdx.x >= total)) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
     const int lane = threadIdx.x & 63;
     auto work = [&](const InstDesc &d, int local) {        // the waves share no barrier
@@ -347,6 +347,7 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
 
 // The tiles with an individual of the pair-sum's, listed by XCD in tile order: a thread per tile, an append per wave.
 __global__ __launch_bounds__(256) void k_tiles(Tables t, int parity, int order, int per) {
+    if (none_dense(t, parity)) return;
     const int total = const_at(t.tiles, t.n_inst), cap = tile_list_cap(total), span = (cap + 63) & ~63;
     const int g = blockIdx.x * 256 + threadIdx.x, x = __builtin_amdgcn_readfirstlane(g / span), b = (g % span) * kXcds + x;
     if (x >= kXcds) return;
@@ -636,7 +637,7 @@ __device__ __forceinline__ void finish_one(const Tables &t, int k, int p, int ma
 __global__ __launch_bounds__(kFinThreads) void k_finish(Tables t, int max_n, int parity, int32_t *status) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int g = blockIdx.x;
-    if (g >= const_at(t.inds, t.n_inst)) return;               // the grid may exceed the total (capacity-sized graph)
+    if (none_dense(t, parity) | (g >= const_at(t.inds, t.n_inst))) return;               // the grid may exceed the total (capacity-sized graph)
     const int k = find_inst(t.inds, t.n_inst, g);
     finish_one(t, k, g - const_at(t.inds, k), max_n, parity, status, smem);
 }
@@ -756,6 +757,7 @@ __device__ __forceinline__ unsigned long long fixed_pt(double c, int sc) {
 __device__ __forceinline__ void to_dense(const Tables &t, const InstDesc &d, int k, int p, int parity, int listed,
                                          int slices, int cap) {
     gst(d.route + p, 1);
+    gst(any_dense(t, parity), 1);
     if (!listed) return;
     const int slice = ((const_at(t.inds, k) + p) >> 2) % slices;
     int32_t *e = list_entry(t, slice, cap, atomicAdd(list_count(t, parity, slice), 1));
@@ -1235,6 +1237,7 @@ __global__ __launch_bounds__(256, 8) void k_eval(Tables t, int parity, double fr
     if (b == 0 && threadIdx.x < kXcds) {             // the next evaluation's tile lists
         gst(tile_count(t, parity ^ 1, threadIdx.x), 0);
         gst(tile_next(t, parity ^ 1, threadIdx.x), 0);
+        if (threadIdx.x == 0) gst(any_dense(t, parity ^ 1), 0);
     }
     if (b >= const_at(t.evals, t.n_inst)) return;              // the grid may exceed the total (capacity-sized graph)
     // Workgroups go to the XCDs in turn; runs of kEvalRun consecutive ones are given to one XCD, so

@@ -947,8 +947,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     KIND == kKindLut ? (B == 8 ? 2 : 3) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
                                                                                      int order, int cstride) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int total = const_at(t.tiles, t.n_inst);                  // the grid may exceed it (capacity-sized graph)
-    if ((int)blockIdx.x >= total) return;
+    const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
+    if (none_dense(t, parity) | ((int)blockIdx.x >= total)) return;
     auto work = [&](const InstDesc &d, int local) {
     const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
     const int n_pairs = (n_jb + 1) / 2;

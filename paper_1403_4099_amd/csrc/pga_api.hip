@@ -244,6 +244,7 @@ Tables tables_at(void *ws, const Layout &L, int n) {
     t.sq_list = (int32_t *)(b + L.list_off);
     t.tile_list = L.tile_off ? (int32_t *)(b + L.tile_off) : nullptr;
     t.n_inst = n;
+    t.routed = 0;
     return t;
 }
 
@@ -265,8 +266,9 @@ int dense_tiles(int N, int P, const Variant &v, double frac) {
     return frac > 0.0 && N <= kRouteAllPairsMaxN ? 0 : pair_tiles(N, P, v);
 }
 
-hipError_t run_fitness(const Tables &t, const Shape &sh, int form, int parity, int32_t *status, hipStream_t s) {
+hipError_t run_fitness(Tables t, const Shape &sh, int form, int parity, int32_t *status, hipStream_t s) {
     hipError_t e;
+    t.routed = sh.frac > 0.0 ? 1 : 0;
     const int listed = sh.frac > 0.0 && sh.inds >= kManyInds ? 1 : 0;
     if (sh.frac > 0.0) {
         e = timed(10, s, [&] {
