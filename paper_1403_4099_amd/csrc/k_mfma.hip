@@ -942,13 +942,17 @@ __device__ __forceinline__ void mfma_block_packed(const InstDesc &d, int jb, int
 
 // The triangle is folded: column blocks n_jb-1-jp and jp share a workgroup, so every
 // workgroup processes the same number of row chunks.
-template <int B, int KIND, bool LISTED>
+// MODE: a tile per workgroup, the listed tiles, or a tile's column block per workgroup (kSplitTiles).
+enum { kTilePlain, kTileListed, kTileSplit };
+template <int B, int KIND, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     KIND == kKindLut ? (B == 8 ? 2 : 3) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
                                                                                      int order, int cstride) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
-    if (none_dense(t, parity) | ((int)blockIdx.x >= total)) return;
+    const int first = MODE == kTileSplit && (int)blockIdx.x >= total ? 1 : 0;   // the tile's blocks: long, short
+    const int end = MODE == kTileSplit ? first + 1 : 2, wg = (int)blockIdx.x - (MODE == kTileSplit ? first * total : 0);
+    if (none_dense(t, parity) | (wg >= total)) return;
     auto work = [&](const InstDesc &d, int local) {
     const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
     const int n_pairs = (n_jb + 1) / 2;
@@ -986,21 +990,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
         }
     } else {
         const MfmaLdsCols s{(uint32_t *)lds, code, cstride};
-        mfma_block_cols<B>(d, n_jb - 1 - jp, pb, parity, s);
-        if (jp != n_jb - 1 - jp) {
-            clear_codes();
-            __syncthreads();
+        if (!first) mfma_block_cols<B>(d, n_jb - 1 - jp, pb, parity, s);
+        if (end == 2 && jp != n_jb - 1 - jp) {
+            if (!first) {
+                clear_codes();
+                __syncthreads();
+            }
             mfma_block_cols<B>(d, jp, pb, parity, s);
         }
     }
     };
-    if constexpr (LISTED) {
+    if constexpr (MODE == kTileListed) {
         each_listed_tile(t, parity, total, [&](int tile) {
             const int k = find_inst(t.tiles, t.n_inst, tile);
             work(const_at(t.desc, k), tile - const_at(t.tiles, k));
         });
     } else {
-        const int tile = order ? xcd_tile(blockIdx.x, total) : blockIdx.x;
+        const int tile = order ? xcd_tile(wg, total) : wg;
         const int k = find_inst(t.tiles, t.n_inst, tile);
         const InstDesc &d = const_at(t.desc, k);
         if (inst_stopped(d)) return;                          // uniform over the workgroup
@@ -1026,7 +1032,7 @@ bool mfma_static_lds_ok() {
     } else {
         static const bool ok = [] {
             hipFuncAttributes a{};
-            return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_pairsum_mfma<B, KIND, false>)) == hipSuccess &&
+            return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_pairsum_mfma<B, KIND, kTilePlain>)) == hipSuccess &&
                    a.sharedSizeBytes == 0;
         }();
         return ok;
@@ -1040,11 +1046,17 @@ hipError_t launch_mfma(Tables t, int total_tiles, int parity, int listed, int or
         if (listed && lds + 256 <= (size_t)kMaxLdsBytes) {    // (the listed kernel has a word of its own)
             const hipError_t e = launch_tiles(t, total_tiles, parity, order, B, s);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, true>), dim3(kTileListGrid), dim3(256), lds, s, t, parity, order,
+            hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, kTileListed>), dim3(kTileListGrid), dim3(256), lds, s, t, parity, order,
                                cstride);
             return hipGetLastError();
         }
-    hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, false>), dim3(total_tiles), dim3(256), lds, s, t, parity, order, cstride);
+    if constexpr (KIND == kKindCols)
+        if (total_tiles <= kSplitTiles) {
+            hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, kTileSplit>), dim3(2 * total_tiles), dim3(256), lds, s, t, parity, order,
+                               cstride);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL((k_pairsum_mfma<B, KIND, kTilePlain>), dim3(total_tiles), dim3(256), lds, s, t, parity, order, cstride);
     return hipGetLastError();
 }
 

@@ -505,6 +505,11 @@ constexpr int kTileListMin = 16384, kTileListGrid = 1024;   // grid: four workgr
 // (a value of bucket(), so that launches of one captured shape agree on it)
 // Lists the tiles of the launch; per = individuals of a tile.
 hipError_t launch_tiles(Tables t, int total_tiles, int parity, int order, int per, hipStream_t s);
+// An MFMA pair-sum launch of at most kSplitTiles tiles (two workgroups a CU) gives each of a tile's two column blocks
+// a workgroup, the long ones first: N = 333, P = 777 (294 tiles) 15 -> 12 us, the call 33.0 -> 29.4; N = P = 500
+// 47.8 -> 45.9. (The FP64 kernel gained 2 to 3% with few tiles and lost 3% near 512; a launch argument
+// instead of a kernel of its own cost the large launches 0.8%.)
+constexpr int kSplitTiles = 512;
 hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s);
 // Launches of at least kManyInds individuals (more than the chip holds at a
