@@ -111,8 +111,8 @@ CorrOut corr_out(double *C, int N, uint16_t *hi, uint16_t *lo) {
 
 // ---- Gram matrix on FP64 MFMA ----------------------------------------------------
 // G_ij = sum_t x_it x_jt over the upper triangle of 128 x 128 output tiles,
-// each tile's t range split into S slices (gram_split: about one workgroup per
-// CU), one workgroup per (tile, slice):
+// each tile's t range split into S slices (gram_split: at most one workgroup
+// per CU), one workgroup per (tile, slice):
 //   * the workgroup stages x of its 128 + 128 rows, 32 samples at a time, in
 //     LDS (two buffers: the next chunk's global loads are in flight while the
 //     current one is multiplied, 128 MFMAs per SIMD and chunk, enough to cover a
@@ -121,8 +121,9 @@ CorrOut corr_out(double *C, int N, uint16_t *hi, uint16_t *lo) {
 //   * wave w of eight owns the 32 x 64 part (w / 2, w % 2) of the tile: eight
 //     16 x 16 blocks, each accumulated by v_mfma_f64_16x16x4_f64 (lane l
 //     supplies A[l % 16][l / 16] and B[l / 16][l % 16]: row l % 16 of A and
-//     column l % 16 of B at the samples t0 + 8 (l / 16) + e, e = 0..7, one per
-//     MFMA, so both operands see the same t);
+//     column l % 16 of B at the samples t0 + 8 h + 2 (l / 16) + v, h = 0..3,
+//     v = 0, 1, one (h, v) per MFMA, so both operands see the same t, and a
+//     slice's last chunk stops after the last h that holds a sample);
 //   * the slice's 128 x 128 partial Gram goes to the workspace; a finish kernel
 //     (one workgroup per 32 x 32 block of a tile) adds the S slices in slice
 //     order (a fixed order: the result does not depend on timing), applies the
@@ -147,12 +148,14 @@ int gram_tiles(int N) {
 }
 
 // Slices per tile for a given N (upper bound) and, with T known, the slices used:
-// about 256 workgroups in all (one per CU), at most kGMaxSplit, and at least 64
-// samples per slice. (Two per CU measured slower: the doubled partial traffic
-// of the finish outweighs the second wave per SIMD.)
+// as many as keep all workgroups resident at once (one per CU: the LDS of one leaves
+// no room for a second), at most kGMaxSplit, and at least 64 samples per slice. One
+// slice more and a few workgroups start a second round, as long as the first:
+// a correlation call at N = 1307 (66 tiles), T = 2000 takes 151 us with 3 slices,
+// 205 with 4; at T = 295, where slices also end at a quarter of a chunk instead
+// of a whole one, the Gram takes 26 us against 42.
 int gram_split_max(int N) {
-    const int t = gram_tiles(N);
-    int S = (256 + t / 2) / t;
+    const int S = 256 / gram_tiles(N);
     return S < 1 ? 1 : (S > kGMaxSplit ? kGMaxSplit : S);
 }
 
@@ -185,7 +188,7 @@ __global__ __launch_bounds__(kGThreads) void k_gram_mfma(const double *X, int N,
     int ti, tj;
     gram_tile_ij(tile, nt, ti, tj);
     const int i0 = ti * kGT, j0 = tj * kGT;
-    const int per = ((T + S - 1) / S + kGK - 1) / kGK * kGK;  // samples per slice, whole chunks
+    const int per = ((T + S - 1) / S + 7) / 8 * 8;          // samples per slice, whole quarters of a chunk
     const int ts = slice * per;
     const int te = min(T, ts + per);
 
@@ -261,18 +264,18 @@ __global__ __launch_bounds__(kGThreads) void k_gram_mfma(const double *X, int N,
     // Two buffers of 32 samples, one barrier per chunk: the next chunk's loads are issued first, its
     // store comes before the last quarter of the MFMAs, so that the store's vector work of one
     // wave of a SIMD runs beside the MFMAs of the other. Each quarter's operands are read during
-    // the quarter before. (N = 1024, T = 4096: 105 us, against 114 with four waves and 16-sample
+    // the quarter before. (N = 1024, T = 4096: 104 us, against 114 with four waves and 16-sample
     // chunks; 63 us of it are the MFMAs at their rate, without store and loads it runs 96. Three
     // buffers of 16 samples with the operands read across the barrier: 105.)
     constexpr int kQ = kGK / 8;                              // sample pairs per lane and chunk
     gram_d2 xa[2][2], xb[2][4];
-    auto read = [&](int h, int buf) {                        // samples 2h, 2h + 1 of this lane's kGK / 4
+    auto read = [&](int h, int buf) {                        // this lane's two of the eight samples 8h..8h + 7
 #pragma unroll
         for (int a = 0; a < 2; ++a)
-            xa[h & 1][a] = *(const gram_d2 *)&sA[buf][(kGR * qr + 16 * a + m) * kGPad + kGK / 4 * kq + 2 * h];
+            xa[h & 1][a] = *(const gram_d2 *)&sA[buf][(kGR * qr + 16 * a + m) * kGPad + 8 * h + 2 * kq];
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-            xb[h & 1][b] = *(const gram_d2 *)&sB[buf][(kGC * qc + 16 * b + m) * kGPad + kGK / 4 * kq + 2 * h];
+            xb[h & 1][b] = *(const gram_d2 *)&sB[buf][(kGC * qc + 16 * b + m) * kGPad + 8 * h + 2 * kq];
     };
     auto mul = [&](int h) {
 #pragma unroll
@@ -288,19 +291,25 @@ __global__ __launch_bounds__(kGThreads) void k_gram_mfma(const double *X, int N,
         store(0);
     }
     __syncthreads();
-    int buf = 0;
-    for (int t0 = ts; t0 < te; t0 += kGK) {
-        const bool more = t0 + kGK < te;
-        if (more) load(t0 + kGK);
+    int buf = 0, t0 = ts;
+    for (; t0 + kGK < te; t0 += kGK) {
+        load(t0 + kGK);
         read(0, buf);
 #pragma unroll
         for (int h = 0; h < kQ; ++h) {
             if (h + 1 < kQ) read(h + 1, buf);
-            if (h + 1 == kQ && more) store(buf ^ 1);
+            if (h + 1 == kQ) store(buf ^ 1);
             mul(h);
         }
         __syncthreads();
         buf ^= 1;
+    }
+    read(0, buf);                                            // the last chunk: its quarters that hold samples
+#pragma unroll
+    for (int h = 0; h < kQ; ++h) {
+        if (t0 + 8 * h >= te) break;
+        if (h + 1 < kQ) read(h + 1, buf);
+        mul(h);
     }
     // Where each accumulator register sits in its 16 x 16 block is read off the hardware: one
     // MFMA with A[i][0] = i, B[0][j] = 1 (zero for k > 0) gives every register its row i, one with
