@@ -996,17 +996,19 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
     }
 }
 
+// The draws of every launch size, beside the ranking's, fit in LDS for every N the library takes.
+constexpr bool breed_layout_ok() {
+    for (int inds : {1, 4096, 16384, 65536})
+        if (breed_lds_bytes(PGA_N_MAX, breed_shape(inds)) + sizeof(RankLds) + 16 > (size_t)kMaxLdsBytes) return false;
+    return true;
+}
+static_assert(breed_layout_ok(), "breed LDS within the LDS limit");
+
 hipError_t launch_breed(Tables t, int blocks, const BreedShape &b, int parity, int gen_off, int fold, int sus_listed, int max_n,
                         hipStream_t s) {
     const int grid = (fold ? t.n_inst : 0) + blocks;
     if (grid <= 0) return hipSuccess;
-    // the shared draws of the largest split (slots fall as N rises, words rise)
-    size_t words = 0;
-    for (int n = 1; n < 2 * max_n; n *= 2) {
-        const int N = n < max_n ? n : max_n;
-        words = std::max(words, (size_t)breed_split(N, b).chr * (3 + 4 * (size_t)((2 * N + 127) / 128)));
-    }
-    hipLaunchKernelGGL(k_breed, dim3(grid), dim3(256), sizeof(uint32_t) * words, s, t, parity, gen_off, fold, sus_listed, b);
+    hipLaunchKernelGGL(k_breed, dim3(grid), dim3(256), breed_lds_bytes(max_n, b), s, t, parity, gen_off, fold, sus_listed, b);
     return hipGetLastError();
 }
 

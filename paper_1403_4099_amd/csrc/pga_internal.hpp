@@ -486,16 +486,32 @@ struct BreedShape {
 struct BreedSplit {
     int gl, chr;             // lanes per slot, slots per workgroup: powers of two, gl chr >= 256
 };
-__host__ __device__ inline BreedSplit breed_split(int N, const BreedShape &b) {
+__host__ __device__ constexpr BreedSplit breed_split(int N, const BreedShape &b) {
     const int npair = (N + 1) / 2;
     int gl = 16;
     while (gl < 256 && gl * b.passes < npair) gl *= 2;
     const int chr = 256 / gl > b.min_chr ? 256 / gl : b.min_chr;
     return BreedSplit{gl, chr};
 }
+// LDS of a breed workgroup of an instance of N stocks: per slot its two parents, whether it crosses, and four
+// crossover words per 128 genes.
+__host__ __device__ constexpr size_t breed_bytes(int N, const BreedShape &b) {
+    return sizeof(uint32_t) * (size_t)breed_split(N, b).chr * (3 + 4 * (size_t)((N + 127) / 128));
+}
+// The most over N = 1 .. max_n. The slots fall as N rises, the words rise: the largest is at the last N of one of the lane
+// counts, 2 gl passes, or at max_n. (Counted for 2 max_n stocks it was 66 304 bytes, beyond what a workgroup may
+// allocate, at 65 536 slots beside N = 4096; 33 536 are needed.)
+constexpr size_t breed_lds_bytes(int max_n, const BreedShape &b) {
+    size_t most = breed_bytes(max_n, b);
+    for (int gl = 16; gl < 256 && 2 * gl * b.passes < max_n; gl *= 2) {
+        const size_t x = breed_bytes(2 * gl * b.passes, b);
+        most = x > most ? x : most;
+    }
+    return most;
+}
 // (us per generation at 2, 4 and 8 passes: one instance of 4096 slots, N = 1024: 74, 72, 71; ten
 // instances of 1024, N of 64 to 1024: 215, 212, 215; 131 072 slots of N ~ U{32..512}: 576 at 8, 16 and 32)
-inline BreedShape breed_shape(int inds) {
+constexpr BreedShape breed_shape(int inds) {
     if (inds >= 65536) return BreedShape{16, 64, 8};
     return BreedShape{inds >= 4096 ? 8 : 2, inds >= 16384 ? 8 : 1, 16};
 }
