@@ -173,8 +173,6 @@ __device__ __forceinline__ void add_if_equal16(double *acc, const int *r, const 
           [l0] "v"(lj[0]), [l1] "v"(lj[1]), [l2] "v"(lj[2]), [l3] "v"(lj[3]), [l4] "v"(lj[4]), [l5] "v"(lj[5]), [l6] "v"(lj[6]), [l7] "v"(lj[7]), [l8] "v"(lj[8]), [l9] "v"(lj[9]), [l10] "v"(lj[10]), [l11] "v"(lj[11]), [l12] "v"(lj[12]), [l13] "v"(lj[13]), [l14] "v"(lj[14]), [l15] "v"(lj[15]), [c0] "v"(c));
 }
 
-constexpr int kFp64Ahead = 4;                        // rows whose C loads go out together: two or four add blocks
-
 template <int B, bool LISTED>
 __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int order) {
     __shared__ int4 lab_s[kFp64Waves][2][64][B / 4];
@@ -254,7 +252,7 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
         auto load_c = [&](auto clamped, double *c, int i) {
 #pragma unroll
             for (int q = 0; q < kFp64Ahead; ++q) {
-                const int row = decltype(clamped)::value ? min(i + q, N - 1) : i + q;
+                const int row = fp64_row(i + q, N, decltype(clamped)::value);
                 c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)row * (uint32_t)N, 0));
             }
         };
@@ -311,12 +309,14 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
             };
 #pragma unroll
             for (int u = 0; u < kRows; ++u) labels_of(ra[u], u);
+            constexpr std::bool_constant<fp64_clamps(checked, 64 - 2 * kFp64Ahead)> within{};   // groups 0 .. 64 - 2 kFp64Ahead
+            constexpr std::bool_constant<fp64_clamps(checked, 64 - kFp64Ahead)> next{};         // the last: rows of the next chunk
             for (int r = 0; r < 64 - 2 * kFp64Ahead; r += 2 * kFp64Ahead) {
-                rows(checked_tag, r, ca, cb);
-                rows(checked_tag, r + kFp64Ahead, cb, ca);
+                rows(within, r, ca, cb);
+                rows(within, r + kFp64Ahead, cb, ca);
             }
-            rows(checked_tag, 64 - 2 * kFp64Ahead, ca, cb);
-            rows(std::true_type{}, 64 - kFp64Ahead, cb, ca);           // loads rows of the next chunk
+            rows(within, 64 - 2 * kFp64Ahead, ca, cb);
+            rows(next, 64 - kFp64Ahead, cb, ca);
             if (ch + 1 < nchunks) store_labels(buf ^ 1, nxt);
         };
         for (int ch = 0; ch + 1 < nchunks; ++ch) chunk(std::false_type{}, ch);

@@ -90,6 +90,12 @@ __host__ __device__ constexpr size_t list_words(int n_wg) {
 // ---- geometry of the pair-sum kernels --------------------------------------
 constexpr int kFp64Waves = 4;                      // waves per workgroup, one column (stock) per lane
 constexpr int kFp64Cols = 64;                      // columns per workgroup
+constexpr int kFp64Ahead = 4;                      // rows whose C loads go out together: two or four add blocks
+// The FP64 pair-sum walks a column block's rows in chunks of 64, kFp64Ahead at a time: with rows r .. of a chunk go out the
+// loads of the kFp64Ahead rows behind them. They may be past N, where row N - 1 is loaded instead, in the
+// last chunk of a block and where they belong to the next chunk.
+__host__ __device__ constexpr bool fp64_clamps(bool last_chunk, int r) { return last_chunk || r + 2 * kFp64Ahead > 64; }
+__host__ __device__ constexpr int fp64_row(int i, int N, bool clamped) { return clamped && i > N - 1 ? N - 1 : i; }
 constexpr int kMfmaWaves = 4;                      // waves per workgroup, 16 columns each
 constexpr int kMfmaCols = 16 * kMfmaWaves;         // columns per workgroup
 constexpr int kMfmaRowCodes = 8192;                // row codes staged in LDS per workgroup (column kernel)

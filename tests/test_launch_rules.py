@@ -31,3 +31,13 @@ def test_breed_launches_ask_for_the_lds_that_their_largest_instance_uses(rules):
     for inds, n, asked, used in rows:
         assert asked == used, (inds, n)
         assert asked + 4096 <= MAX_LDS, (inds, n)          # 4096: the ranking's, beside it
+
+
+def test_the_fp64_row_walk_stays_inside_the_matrix(rules):
+    """Every load of the walk is inside C, and a row above the column (its value counts) is read itself."""
+    rows = [tuple(map(int, r)) for r in rules("fp64_rows")]
+    assert [r[0] for r in rows] == list(range(1, 4097))
+    for n, loads, outside, other in rows:
+        blocks = (n + 63) // 64
+        assert loads == 4 * blocks + 64 * blocks * (blocks + 1) // 2
+        assert outside == 0 and other == 0, n
