@@ -216,6 +216,12 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
     // The four waves of a SIMD have equal work but, left to themselves, the oldest issues first and
     // the youngest ends alone, at half the rate (they lived 74% of the launch on average): the
     // highest priority goes round by wave slot, a chunk each (86%; 188.7 -> 176.6 us at N = 1024, P = 4096).
+    // Not where the launch has more than one round of workgroups and the upper triangle of C (4 N^2 bytes) is larger
+    // than the L2s (N > 2896): the waves that turns keep out of step share fewer C rows there, and a young wave's end is
+    // covered by the next round. N = 4096, P = 4096: 2758 us with turns, 2286 without; N = 3584, P = 4672: 2199 / 1999;
+    // N = 3072, P = 4096: 1345 / 1317. Below, with more rounds, they win or lose up to 4% (N = 2560, P = 2464:
+    // 649 / 671; P = 4928: 1196 / 1185); within one round they win at every N (3584, P = 864: 414 / 460).
+    const bool turns = total <= kFp64Round || 4ll * N * N <= kL2Bytes;
     const int slot = __builtin_amdgcn_s_getreg((3 << 11) | 4);   // HW_ID.WAVE_ID
     // The triangle is folded: column blocks n_jb-1-jp (jp + 1 ... n_jb chunks of rows) and
     // jp are done by the same workgroup, so every workgroup has n_jb + 1 chunks of work.
@@ -260,11 +266,13 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
         load_c(std::true_type{}, ca, 0);
         auto chunk = [&](auto checked_tag, int ch) {
             constexpr bool checked = decltype(checked_tag)::value;
-            switch ((ch + slot) & 3) {
-            case 0: __builtin_amdgcn_s_setprio(0); break;
-            case 1: __builtin_amdgcn_s_setprio(1); break;
-            case 2: __builtin_amdgcn_s_setprio(2); break;
-            default: __builtin_amdgcn_s_setprio(3); break;
+            if (turns) {
+                switch ((ch + slot) & 3) {
+                case 0: __builtin_amdgcn_s_setprio(0); break;
+                case 1: __builtin_amdgcn_s_setprio(1); break;
+                case 2: __builtin_amdgcn_s_setprio(2); break;
+                default: __builtin_amdgcn_s_setprio(3); break;
+                }
             }
             const int i0 = ch * 64;
             const int buf = ch & 1;

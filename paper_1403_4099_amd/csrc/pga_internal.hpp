@@ -91,6 +91,8 @@ __host__ __device__ constexpr size_t list_words(int n_wg) {
 constexpr int kFp64Waves = 4;                      // waves per workgroup, one column (stock) per lane
 constexpr int kFp64Cols = 64;                      // columns per workgroup
 constexpr int kFp64Ahead = 4;                      // rows whose C loads go out together: two or four add blocks
+constexpr int kFp64Round = 1024;                   // workgroups resident at once: four a CU (registers)
+constexpr int64_t kL2Bytes = 8ll << 22;            // the eight XCDs' L2s, 4 MiB each
 // The FP64 pair-sum walks a column block's rows in chunks of 64, kFp64Ahead at a time: with rows r .. of a chunk go out the
 // loads of the kFp64Ahead rows behind them. They may be past N, where row N - 1 is loaded instead, in the
 // last chunk of a block and where they belong to the next chunk.
