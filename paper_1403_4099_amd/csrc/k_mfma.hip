@@ -944,9 +944,11 @@ __device__ __forceinline__ void mfma_block_packed(const InstDesc &d, int jb, int
 // workgroup processes the same number of row chunks.
 // MODE: a tile per workgroup, the listed tiles, or a tile's column block per workgroup (kSplitTiles).
 enum { kTilePlain, kTileListed, kTileSplit };
+// Waves per SIMD: four where the accumulators leave room for them. (The table kernel with 4 individuals, free to take
+// 132 registers, ran three: 213 us at N = 1024, P = 4096; 183 with four.)
 template <int B, int KIND, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
-    KIND == kKindLut ? (B == 8 ? 2 : 3) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
+    KIND == kKindLut ? (B == 8 ? 2 : 4) : (B == 16 ? 2 : 4)))) void k_pairsum_mfma(Tables t, int parity,
                                                                                      int order, int cstride) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
