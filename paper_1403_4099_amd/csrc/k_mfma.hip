@@ -1041,9 +1041,18 @@ bool mfma_static_lds_ok() {
     }
 }
 
+// Column kernel with 8 individuals: where the triangle of A, both parts 2 N^2 bytes, fills the L2s (N > 4032) and the
+// launch has many rounds, a third workgroup per CU reads past them more than it hides; the LDS asked for then
+// leaves room for two. (N = 4096, P = 4096: 2722 us with three, 2615 with two; P = 2048 1394 / 1353; with 4096
+// tiles, P = 1024, 685 / 701; at N = 4000 1230 / 1247 and 2389 / 2416.)
+constexpr int kMfmaThreeMaxN = 4032, kMfmaTwoTiles = 8192;
+constexpr size_t kMfmaTwoLds = kMaxLdsBytes - 256;
+
 template <int B, int KIND>
 hipError_t launch_mfma(Tables t, int total_tiles, int parity, int listed, int order, int cstride, size_t lds, hipStream_t s) {
     if (!mfma_static_lds_ok<B, KIND>()) return hipErrorInvalidKernelFile;
+    if (KIND == kKindCols && B == 8 && cstride > kMfmaThreeMaxN && total_tiles >= kMfmaTwoTiles)
+        lds = std::max(lds, kMfmaTwoLds);
     if constexpr (KIND == kKindCols)
         if (listed && lds + 256 <= (size_t)kMaxLdsBytes) {    // (the listed kernel has a word of its own)
             const hipError_t e = launch_tiles(t, total_tiles, parity, order, B, s);
