@@ -587,11 +587,20 @@ __global__ __launch_bounds__(kSmThreads) void k_corr_small(const double *R, int 
     }
 }
 
-// Where the small path ends (graph replays, with the split, us small / large path): one
-// workgroup per CU up to N = 352, where it wins to T = 4096 (18 x 4096: 32 / 52, 300 x 390: 9 / 28,
-// 300 x 4096: 40 / 58); above that a tile's rows are read N / 16 times from L2, which pays to
-// T = 1024 and N = 704 (512 x 390: 20 / 29, 512 x 1024: 29 / 34, 700 x 1024: 41 / 41, 1024 x 390: 50 / 40).
-bool corr_small(int N, int T) { return N <= 352 ? T <= 4096 : N <= 704 && T <= 1024; }
+// Where the small path ends (back-to-back calls, us small / large path). Its workgroups are as many as the 16 x 16 tiles of the
+// upper triangle (with the split, whose padding counts, so that C is the same bits without it); their time is that of the
+// rounds of one per CU, which read every row twice (the means first) from T = 257.
+// One round (N <= 352): ahead wherever measured (300 x 390 13 / 26, 300 x 4096 40 / 56, 300 x 8192 73 / 97);
+// the rule ends at T = 4096, the longest window of its first measurements. Two (448 x 1024 25 / 31, x 2048 45 / 40):
+// to T = 1024. Three (576 x 768 31 / 32, x 1024 38 / 35; 512 x 1024 37 / 31): to T = 768. Four (704 x 256 25 / 28,
+// x 390 33 / 32, x 1024 51 / 38): to T = 256. Five and more lose from 100 samples on (896 x 64 34 / 26).
+bool corr_small(int N, int T) {
+    const int nt = split_ld(N) / kSmTile, rounds = (nt * (nt + 1) / 2 + 255) / 256;
+    return rounds <= 1 ? T <= 4096 : rounds == 2 ? T <= 1024 : rounds == 3 ? T <= 768 : rounds == 4 && T <= 256;
+}
+// The EWMA's small path reads each row once and its large path has a launch more: N = 704, T = 1024 34 / 46 with the split
+// (608 x 390 21 / 37, 352 x 1024 20 / 37). Its limits are those of the first measurements.
+bool ewma_small(int N, int T) { return N <= 352 ? T <= 4096 : N <= 704 && T <= 1024; }
 
 hipError_t launch_corr(const double *R, int N, int T, int64_t ld, double *mu, double *ss, double *C, uint16_t *hi,
                        uint16_t *lo, double *part, int32_t *status, hipStream_t s) {
@@ -721,7 +730,7 @@ hipError_t launch_ewma(const double *R, int N, int T, int64_t ld, double lam, in
                        reset ? nullptr : S, m, sw, diag0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (corr_small(N, T)) {
+    if (ewma_small(N, T)) {
         const int nt = (o.ld + kSmTile - 1) / kSmTile;
         hipLaunchKernelGGL(k_corr_small<true>, dim3(nt * (nt + 1) / 2), dim3(kSmThreads), 0, s, R, N, T, ld, nt, o, w,
                            status);
