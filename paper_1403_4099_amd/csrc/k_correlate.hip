@@ -30,34 +30,35 @@ __device__ __forceinline__ double block_sum256(double v, double *red) {
     return r;
 }
 
-// Bound by the read of R. The first kStatCache samples of a thread stay in registers
-// between the two passes (all of a row up to T = 4096), so R is read once. The mean is taken
+// Bound by the read of R. The first CACHE samples of a thread stay in registers between the two passes (all of a row
+// up to T = 256 CACHE), so R is read once; the slots that a short row leaves empty cost their instructions, so it
+// has few (T = 40: N = 2048 6.3 us with 16 of them, 5.0 with one; N = 4096 9.5 and 7.2). The mean is taken
 // of the differences to the row's first sample, so a constant row has variance exactly 0.
-constexpr int kStatCache = 16;
+template <int CACHE>
 __global__ __launch_bounds__(256) void k_row_stats(const double *R, int T, int64_t ld, double *mu,
                                                    double *ss, int32_t *status) {
     __shared__ double red[4];
     const int i = blockIdx.x;
     const double *__restrict__ row = R + (size_t)i * ld;
     const double x0 = row[0];
-    double x[kStatCache];
+    double x[CACHE];
     double s = 0.0;
 #pragma unroll
-    for (int u = 0; u < kStatCache; ++u) {
+    for (int u = 0; u < CACHE; ++u) {
         const int t = threadIdx.x + 256 * u;
         x[u] = t < T ? row[t] : x0;
     }
 #pragma unroll
-    for (int u = 0; u < kStatCache; ++u) s += x[u] - x0;
-    for (int t = threadIdx.x + 256 * kStatCache; t < T; t += 256) s += row[t] - x0;
+    for (int u = 0; u < CACHE; ++u) s += x[u] - x0;
+    for (int t = threadIdx.x + 256 * CACHE; t < T; t += 256) s += row[t] - x0;
     const double m = x0 + block_sum256(s, red) / (double)T;
     double q = 0.0;
 #pragma unroll
-    for (int u = 0; u < kStatCache; ++u) {
+    for (int u = 0; u < CACHE; ++u) {
         const double d = threadIdx.x + 256 * u < T ? x[u] - m : 0.0;
         q = fma(d, d, q);
     }
-    for (int t = threadIdx.x + 256 * kStatCache; t < T; t += 256) {
+    for (int t = threadIdx.x + 256 * CACHE; t < T; t += 256) {
         const double d = row[t] - m;
         q = fma(d, d, q);
     }
@@ -612,7 +613,8 @@ hipError_t launch_corr(const double *R, int N, int T, int64_t ld, double *mu, do
         return hipGetLastError();
     }
     const int nt = (N + kGT - 1) / kGT, tiles = gram_tiles(N), S = gram_split(N, T);
-    hipLaunchKernelGGL(k_row_stats, dim3(N), dim3(256), 0, s, R, T, ld, mu, ss, status);
+    hipLaunchKernelGGL(T <= 256 ? k_row_stats<1> : T <= 1024 ? k_row_stats<4> : k_row_stats<16>, dim3(N), dim3(256), 0, s, R,
+                       T, ld, mu, ss, status);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gram_mfma<false>, dim3(tiles * S), dim3(kGThreads), 0, s, R, N, T, ld, mu, nullptr, nt, tiles,
