@@ -322,9 +322,14 @@ int pga_tune_load(const char *path);
  * Launch sizes are rounded up to one of four values per octave and the
  * instance list padded with empty slots, so a captured graph is replayed for
  * every later call whose instance count, totals of tiles and individuals,
- * largest N and largest P round to the same values (and with the same
- * workspace, status buffer, form, G, kernel variant and route limit); the
- * instances' descriptors are uploaded at each call.
+ * largest N and largest P round to the same values, as do its workgroups of
+ * the cluster-pair evaluation (one per 16, 8, 4 or 1 individuals, by N) and of
+ * the breeding and the evaluation's LDS (one value per octave up to 8192
+ * workgroups; one per number of workgroups that fit a CU), with the same
+ * workspace, status buffer, form, G, kernel variant, route limit and use of
+ * SUS and of the termination test. A context keeps up to 48 graphs and drops
+ * the least recently used; the instances' descriptors are uploaded at each
+ * call.
  * Random draws come from Philox4x32-10 with counter
  *   (block, individual or child, generation, tag | instance_id << 4),
  * tags INIT=0, SELECT=1, CROSSOVER=2, MUTATION=3, SUS=4, SHUFFLE=5, so a run is a pure

@@ -169,6 +169,25 @@ int bucket(int x) {
     return (x + u - 1) / u * u;
 }
 
+// Workgroups of the evaluation and of the breed launch. Their totals follow each instance's N more closely than those of
+// tiles and individuals, so up to 8192 they get one value per octave: mixes of instances that agree in the latter
+// mostly share a graph, and a few thousand workgroups that end at their first load pass beside the others.
+int bucket_workgroups(int x) {
+    if (x > 8192) return bucket(x);
+    int b = 1;
+    while (b < x) b *= 2;
+    return b;
+}
+
+// LDS of an evaluation workgroup, rounded up to the most that leaves the same number of workgroups per CU (eight at most: their
+// registers), for the same reason: seven values.
+size_t bucket_lds(size_t bytes) {
+    constexpr size_t kCuLds = 163840, kGranule = 1280;
+    for (size_t k = 8; k > 2; --k)
+        if (bytes <= kCuLds / k / kGranule * kGranule) return kCuLds / k / kGranule * kGranule;
+    return kMaxLdsBytes;
+}
+
 // ---- workspace layout ----------------------------------------------------------
 // [InstDesc x n][prefix tiles n+1][prefix inds n+1][prefix evals n+1][prefix breeds n+1]
 // [dense list counters kListCounters int32]
@@ -338,7 +357,7 @@ struct CachedGraph {
     hipGraphExec_t exec;
     uint64_t last_use;
 };
-constexpr int kMaxGraphs = 32;                       // captured graphs kept per context (least recently used go)
+constexpr int kMaxGraphs = 48;                       // captured graphs kept per context (least recently used go)
 
 struct pga_ctx {
     hipStream_t cap = nullptr;
@@ -854,9 +873,9 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
         pe[k + 1] = pe[k];
         pb[k + 1] = pb[k];
     }
-    sh.evals = bucket(pe[nb]);
-    sh.breeds = bucket(pb[nb]);
-    sh.lds = align_up(sh.lds, 2048);                 // part of a captured graph's key: few values
+    sh.evals = bucket_workgroups(pe[nb]);
+    sh.breeds = bucket_workgroups(pb[nb]);
+    sh.lds = bucket_lds(sh.lds);
     sh.tiles = bucket(pf[nb]);
     HIP_TRY(hipMemcpyAsync(ws, ctx->staging, head, hipMemcpyHostToDevice, s));
     HIP_TRY(hipEventRecord(ctx->upload_done, s));
