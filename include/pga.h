@@ -131,7 +131,7 @@ typedef struct {
 /* ---- context and errors ------------------------------------------------ */
 int pga_ctx_create(pga_ctx **out);
 int pga_ctx_destroy(pga_ctx *ctx);
-/* Number of captured graphs the context holds (at most 32; the least recently
+/* Number of captured graphs the context holds (at most 64; the least recently
  * launched is dropped to make room). PGA_ERR_ARG for a null context. */
 int pga_ctx_graphs(pga_ctx *ctx);
 const char *pga_strerror(int code);
@@ -327,7 +327,7 @@ int pga_tune_load(const char *path);
  * the breeding and the evaluation's LDS (one value per octave up to 8192
  * workgroups; one per number of workgroups that fit a CU), with the same
  * workspace, status buffer, form, G, kernel variant, route limit and use of
- * SUS and of the termination test. A context keeps up to 48 graphs and drops
+ * SUS and of the termination test. A context keeps up to 64 graphs and drops
  * the least recently used; the instances' descriptors are uploaded at each
  * call.
  * Random draws come from Philox4x32-10 with counter

@@ -357,7 +357,7 @@ struct CachedGraph {
     hipGraphExec_t exec;
     uint64_t last_use;
 };
-constexpr int kMaxGraphs = 48;                       // captured graphs kept per context (least recently used go)
+constexpr int kMaxGraphs = 64;                       // captured graphs kept per context (least recently used go)
 
 struct pga_ctx {
     hipStream_t cap = nullptr;
