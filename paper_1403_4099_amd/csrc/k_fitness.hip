@@ -178,166 +178,167 @@ __global__ __launch_bounds__(256) void k_pairsum_fp64(Tables t, int parity, int 
     __shared__ int4 lab_s[kFp64Waves][2][64][B / 4];
 
     const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
-    if (none_dense(t, parity) | ((int)blockIdx.x >= total)) return;
+    const bool none = none_dense(t, parity), past = (int)blockIdx.x >= total;   // one wait for both loads
+    if (none | past) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept scalar
     const int lane = threadIdx.x & 63;
     auto work = [&](const InstDesc &d, int local) {        // the waves share no barrier
-    const int N = d.N, P = d.P;
-    const int n_jb = (N + kFp64Cols - 1) / kFp64Cols;
-    const int n_pairs = (n_jb + 1) / 2;
-    const TilePos tp = tile_pos(local, n_pairs, (P + kFp64Waves * B - 1) / (kFp64Waves * B), order);
-    const int jp = tp.jp, pb = tp.pb;
-    const int pbase = pb * (kFp64Waves * B) + wave * B;
-    if (pbase >= P) return;
-    if (d.route) {
-        int any = 0;                                 // the loads together: no test between them
+        const int N = d.N, P = d.P;
+        const int n_jb = (N + kFp64Cols - 1) / kFp64Cols;
+        const int n_pairs = (n_jb + 1) / 2;
+        const TilePos tp = tile_pos(local, n_pairs, (P + kFp64Waves * B - 1) / (kFp64Waves * B), order);
+        const int jp = tp.jp, pb = tp.pb;
+        const int pbase = pb * (kFp64Waves * B) + wave * B;
+        if (pbase >= P) return;
+        if (d.route) {
+            int any = 0;                                 // the loads together: no test between them
 #pragma unroll
-        for (int b = 0; b < B; ++b) any |= gld(d.route + min(pbase + b, P - 1));
-        if (!any) return;
-    }
-    const int32_t *__restrict__ labels = d.pop[parity];
-    const double *__restrict__ C = d.C;
-    const __amdgpu_buffer_rsrc_t c_r = __builtin_amdgcn_make_buffer_rsrc((void *)C, (short)0, 8 * N * N, kBufWord3);   // N <= 4096
-
-    auto fetch_labels = [&](int i0, int *v) {
-        const int ir = i0 + lane;
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int p = pbase + b;
-            v[b] = (ir < N && p < P) ? gld(labels + (size_t)p * N + ir) : (int)0x80000001;
+            for (int b = 0; b < B; ++b) any |= gld(d.route + min(pbase + b, P - 1));
+            if (!any) return;
         }
-    };
-    auto store_labels = [&](int buf, const int *v) {
-#pragma unroll
-        for (int q = 0; q < B / 4; ++q)
-            lab_s[wave][buf][lane][q] = make_int4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-    };
+        const int32_t *__restrict__ labels = d.pop[parity];
+        const double *__restrict__ C = d.C;
+        const __amdgpu_buffer_rsrc_t c_r = __builtin_amdgcn_make_buffer_rsrc((void *)C, (short)0, 8 * N * N, kBufWord3);   // N <= 4096
 
-    // The four waves of a SIMD have equal work but, left to themselves, the oldest issues first and
-    // the youngest ends alone, at half the rate (they lived 74% of the launch on average): the
-    // highest priority goes round by wave slot, a chunk each (86%; 188.7 -> 176.6 us at N = 1024, P = 4096).
-    // Not where the launch has more than one round of workgroups and the upper triangle of C (4 N^2 bytes) is larger
-    // than the L2s (N > 2896): the waves that turns keep out of step share fewer C rows there, and a young wave's end is
-    // covered by the next round. N = 4096, P = 4096: 2758 us with turns, 2286 without; N = 3584, P = 4672: 2199 / 1999;
-    // N = 3072, P = 4096: 1345 / 1317. Below, with more rounds, they win or lose up to 4% (N = 2560, P = 2464:
-    // 649 / 671; P = 4928: 1196 / 1185); within one round they win at every N (3584, P = 864: 414 / 460).
-    const bool turns = total <= kFp64Round || 4ll * N * N <= kL2Bytes;
-    const int slot = __builtin_amdgcn_s_getreg((3 << 11) | 4);   // HW_ID.WAVE_ID
-    // The triangle is folded: column blocks n_jb-1-jp (jp + 1 ... n_jb chunks of rows) and
-    // jp are done by the same workgroup, so every workgroup has n_jb + 1 chunks of work.
-    for (int half = 0; half < 2; ++half) {
-        const int jb = half == 0 ? n_jb - 1 - jp : jp;
-        if (half == 1 && jb == n_jb - 1 - jp) break;       // middle block of an odd count: once
-        const int j = jb * kFp64Cols + lane;
-        const bool jok = j < N;
-
-        int lj[B];
-        double acc[B];
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int p = pbase + b;
-            lj[b] = (jok && p < P) ? gld(labels + (size_t)p * N + j) : (int)0x80000000;
-            acc[b] = 0.0;
-        }
-
-        const int nchunks = jb + 1;                      // rows 0 .. 64 (jb + 1) - 1
-        int nxt[B];
-        fetch_labels(0, nxt);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();                 // previous block's reads of buffer 0 are done
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        store_labels(0, nxt);
-        // C loads go through a buffer descriptor over C: the lane's column offset stays in one
-        // register and the row offset is a scalar, so a load costs no vector address arithmetic.
-        // Rows past N read row N - 1 (the range check of a buffer leaves the scalar offset out) and
-        // lanes past N column N - 1; the former are >= j, the latter never stored. Chunks before the
-        // last hold rows i < 64 jb <= j only, so their values need no test.
-        const int jc = jok ? j : N - 1;
-        const uint32_t jc_off = 8u * (uint32_t)jc;
-        // (The clamp only where rows may be past N: in every load it cost 3%.)
-        auto load_c = [&](auto clamped, double *c, int i) {
-#pragma unroll
-            for (int q = 0; q < kFp64Ahead; ++q) {
-                const int row = fp64_row(i + q, N, decltype(clamped)::value);
-                c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)row * (uint32_t)N, 0));
-            }
-        };
-        double ca[kFp64Ahead], cb[kFp64Ahead];
-        load_c(std::true_type{}, ca, 0);
-        auto chunk = [&](auto checked_tag, int ch) {
-            constexpr bool checked = decltype(checked_tag)::value;
-            if (turns) {
-                switch ((ch + slot) & 3) {
-                case 0: __builtin_amdgcn_s_setprio(0); break;
-                case 1: __builtin_amdgcn_s_setprio(1); break;
-                case 2: __builtin_amdgcn_s_setprio(2); break;
-                default: __builtin_amdgcn_s_setprio(3); break;
-                }
-            }
-            const int i0 = ch * 64;
-            const int buf = ch & 1;
-            if (ch + 1 < nchunks) fetch_labels(i0 + 64, nxt);   // in flight during this chunk
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-            constexpr int kRows = 16 / B;                    // of one add block
-            int ra[kRows][B], rb[kRows][B];
-            auto labels_of = [&](int *rl, int r) {
-#pragma unroll
-                for (int u = 0; u < B / 4; ++u) {
-                    const int4 v = lab_s[wave][buf][r & 63][u];
-                    rl[4 * u + 0] = v.x;
-                    rl[4 * u + 1] = v.y;
-                    rl[4 * u + 2] = v.z;
-                    rl[4 * u + 3] = v.w;
-                }
-            };
-            // rows r .. r + kFp64Ahead - 1 with values c, the labels of the first kRows in rl; the
-            // C loads of the next rows go out before them, the label reads of a block's rows before
-            // the block above it (the barriers keep the compiler from moving a read next to its use)
-            auto rows = [&](auto clamped, int r, double *c, double *cn) {
-                load_c(clamped, cn, i0 + r + kFp64Ahead);
-#pragma unroll
-                for (int q = 0; q < kFp64Ahead; q += kRows) {
-                    int(*cur)[B] = q / kRows & 1 ? rb : ra, (*next)[B] = q / kRows & 1 ? ra : rb;
-#pragma unroll
-                    for (int u = 0; u < kRows; ++u) labels_of(next[u], r + q + kRows + u);
-                    __builtin_amdgcn_sched_barrier(0);
-                    double cq[kRows];
-#pragma unroll
-                    for (int u = 0; u < kRows; ++u) {
-                        cq[u] = c[q + u];
-                        if constexpr (checked) cq[u] = i0 + r + q + u < j ? cq[u] : 0.0;
-                    }
-                    if constexpr (B == 16) add_if_equal16(acc, cur[0], lj, cq[0]);
-                    else add_if_equal8(acc, cur[0], cur[1], lj, cq[0], cq[1]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-#pragma unroll
-            for (int u = 0; u < kRows; ++u) labels_of(ra[u], u);
-            constexpr std::bool_constant<fp64_clamps(checked, 64 - 2 * kFp64Ahead)> within{};   // groups 0 .. 64 - 2 kFp64Ahead
-            constexpr std::bool_constant<fp64_clamps(checked, 64 - kFp64Ahead)> next{};         // the last: rows of the next chunk
-            for (int r = 0; r < 64 - 2 * kFp64Ahead; r += 2 * kFp64Ahead) {
-                rows(within, r, ca, cb);
-                rows(within, r + kFp64Ahead, cb, ca);
-            }
-            rows(within, 64 - 2 * kFp64Ahead, ca, cb);
-            rows(next, 64 - kFp64Ahead, cb, ca);
-            if (ch + 1 < nchunks) store_labels(buf ^ 1, nxt);
-        };
-        for (int ch = 0; ch + 1 < nchunks; ++ch) chunk(std::false_type{}, ch);
-        chunk(std::true_type{}, nchunks - 1);
-        if (jok) {
-            const double cjj = gld(C + (size_t)j * N + j);
+        auto fetch_labels = [&](int i0, int *v) {
+            const int ir = i0 + lane;
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const int p = pbase + b;
-                if (p < P) gst(d.wsum + (size_t)p * N + j, fma(2.0, acc[b], cjj));
+                v[b] = (ir < N && p < P) ? gld(labels + (size_t)p * N + ir) : (int)0x80000001;
+            }
+        };
+        auto store_labels = [&](int buf, const int *v) {
+#pragma unroll
+            for (int q = 0; q < B / 4; ++q)
+                lab_s[wave][buf][lane][q] = make_int4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        };
+
+        // The four waves of a SIMD have equal work but, left to themselves, the oldest issues first and
+        // the youngest ends alone, at half the rate (they lived 74% of the launch on average): the
+        // highest priority goes round by wave slot, a chunk each (86%; 188.7 -> 176.6 us at N = 1024, P = 4096).
+        // Not where the launch has more than one round of workgroups and the upper triangle of C (4 N^2 bytes) is larger
+        // than the L2s (N > 2896): the waves that turns keep out of step share fewer C rows there, and a young wave's end is
+        // covered by the next round. N = 4096, P = 4096: 2758 us with turns, 2286 without; N = 3584, P = 4672: 2199 / 1999;
+        // N = 3072, P = 4096: 1345 / 1317. Below, with more rounds, they win or lose up to 4% (N = 2560, P = 2464:
+        // 649 / 671; P = 4928: 1196 / 1185); within one round they win at every N (3584, P = 864: 414 / 460).
+        const bool turns = total <= kFp64Round || 4ll * N * N <= kL2Bytes;
+        const int slot = __builtin_amdgcn_s_getreg((3 << 11) | 4);   // HW_ID.WAVE_ID
+        // The triangle is folded: column blocks n_jb-1-jp (jp + 1 ... n_jb chunks of rows) and
+        // jp are done by the same workgroup, so every workgroup has n_jb + 1 chunks of work.
+        for (int half = 0; half < 2; ++half) {
+            const int jb = half == 0 ? n_jb - 1 - jp : jp;
+            if (half == 1 && jb == n_jb - 1 - jp) break;       // middle block of an odd count: once
+            const int j = jb * kFp64Cols + lane;
+            const bool jok = j < N;
+
+            int lj[B];
+            double acc[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int p = pbase + b;
+                lj[b] = (jok && p < P) ? gld(labels + (size_t)p * N + j) : (int)0x80000000;
+                acc[b] = 0.0;
+            }
+
+            const int nchunks = jb + 1;                      // rows 0 .. 64 (jb + 1) - 1
+            int nxt[B];
+            fetch_labels(0, nxt);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();                 // previous block's reads of buffer 0 are done
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            store_labels(0, nxt);
+            // C loads go through a buffer descriptor over C: the lane's column offset stays in one
+            // register and the row offset is a scalar, so a load costs no vector address arithmetic.
+            // Rows past N read row N - 1 (the range check of a buffer leaves the scalar offset out) and
+            // lanes past N column N - 1; the former are >= j, the latter never stored. Chunks before the
+            // last hold rows i < 64 jb <= j only, so their values need no test.
+            const int jc = jok ? j : N - 1;
+            const uint32_t jc_off = 8u * (uint32_t)jc;
+            // (The clamp only where rows may be past N: in every load it cost 3%.)
+            auto load_c = [&](auto clamped, double *c, int i) {
+#pragma unroll
+                for (int q = 0; q < kFp64Ahead; ++q) {
+                    const int row = fp64_row(i + q, N, decltype(clamped)::value);
+                    c[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(c_r, jc_off, 8u * (uint32_t)row * (uint32_t)N, 0));
+                }
+            };
+            double ca[kFp64Ahead], cb[kFp64Ahead];
+            load_c(std::true_type{}, ca, 0);
+            auto chunk = [&](auto checked_tag, int ch) {
+                constexpr bool checked = decltype(checked_tag)::value;
+                if (turns) {
+                    switch ((ch + slot) & 3) {
+                    case 0: __builtin_amdgcn_s_setprio(0); break;
+                    case 1: __builtin_amdgcn_s_setprio(1); break;
+                    case 2: __builtin_amdgcn_s_setprio(2); break;
+                    default: __builtin_amdgcn_s_setprio(3); break;
+                    }
+                }
+                const int i0 = ch * 64;
+                const int buf = ch & 1;
+                if (ch + 1 < nchunks) fetch_labels(i0 + 64, nxt);   // in flight during this chunk
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+                constexpr int kRows = 16 / B;                    // of one add block
+                int ra[kRows][B], rb[kRows][B];
+                auto labels_of = [&](int *rl, int r) {
+#pragma unroll
+                    for (int u = 0; u < B / 4; ++u) {
+                        const int4 v = lab_s[wave][buf][r & 63][u];
+                        rl[4 * u + 0] = v.x;
+                        rl[4 * u + 1] = v.y;
+                        rl[4 * u + 2] = v.z;
+                        rl[4 * u + 3] = v.w;
+                    }
+                };
+                // rows r .. r + kFp64Ahead - 1 with values c, the labels of the first kRows in rl; the
+                // C loads of the next rows go out before them, the label reads of a block's rows before
+                // the block above it (the barriers keep the compiler from moving a read next to its use)
+                auto rows = [&](auto clamped, int r, double *c, double *cn) {
+                    load_c(clamped, cn, i0 + r + kFp64Ahead);
+#pragma unroll
+                    for (int q = 0; q < kFp64Ahead; q += kRows) {
+                        int(*cur)[B] = q / kRows & 1 ? rb : ra, (*next)[B] = q / kRows & 1 ? ra : rb;
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) labels_of(next[u], r + q + kRows + u);
+                        __builtin_amdgcn_sched_barrier(0);
+                        double cq[kRows];
+#pragma unroll
+                        for (int u = 0; u < kRows; ++u) {
+                            cq[u] = c[q + u];
+                            if constexpr (checked) cq[u] = i0 + r + q + u < j ? cq[u] : 0.0;
+                        }
+                        if constexpr (B == 16) add_if_equal16(acc, cur[0], lj, cq[0]);
+                        else add_if_equal8(acc, cur[0], cur[1], lj, cq[0], cq[1]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+#pragma unroll
+                for (int u = 0; u < kRows; ++u) labels_of(ra[u], u);
+                constexpr std::bool_constant<fp64_clamps(checked, 64 - 2 * kFp64Ahead)> within{};   // groups 0 .. 64 - 2 kFp64Ahead
+                constexpr std::bool_constant<fp64_clamps(checked, 64 - kFp64Ahead)> next{};         // the last: rows of the next chunk
+                for (int r = 0; r < 64 - 2 * kFp64Ahead; r += 2 * kFp64Ahead) {
+                    rows(within, r, ca, cb);
+                    rows(within, r + kFp64Ahead, cb, ca);
+                }
+                rows(within, 64 - 2 * kFp64Ahead, ca, cb);
+                rows(next, 64 - kFp64Ahead, cb, ca);
+                if (ch + 1 < nchunks) store_labels(buf ^ 1, nxt);
+            };
+            for (int ch = 0; ch + 1 < nchunks; ++ch) chunk(std::false_type{}, ch);
+            chunk(std::true_type{}, nchunks - 1);
+            if (jok) {
+                const double cjj = gld(C + (size_t)j * N + j);
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const int p = pbase + b;
+                    if (p < P) gst(d.wsum + (size_t)p * N + j, fma(2.0, acc[b], cjj));
+                }
             }
         }
-    }
     };
     if constexpr (LISTED) {
         each_listed_tile(t, parity, total, [&](int tile) {
@@ -645,7 +646,8 @@ __device__ __forceinline__ void finish_one(const Tables &t, int k, int p, int ma
 __global__ __launch_bounds__(kFinThreads) void k_finish(Tables t, int max_n, int parity, int32_t *status) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int g = blockIdx.x;
-    if (none_dense(t, parity) | (g >= const_at(t.inds, t.n_inst))) return;               // the grid may exceed the total (capacity-sized graph)
+    const bool none = none_dense(t, parity), past = g >= const_at(t.inds, t.n_inst);   // the grid may exceed the total
+    if (none | past) return;                         // (capacity-sized graph); one wait for both loads
     const int k = find_inst(t.inds, t.n_inst, g);
     finish_one(t, k, g - const_at(t.inds, k), max_n, parity, status, smem);
 }

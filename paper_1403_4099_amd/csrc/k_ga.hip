@@ -775,7 +775,7 @@ __global__ __launch_bounds__(T) void k_rank_sus(Tables t, int gen_off) {
 
 hipError_t launch_rank_sus(Tables t, int max_p, int gen_off, hipStream_t s) {
     if (max_p <= 1024)
-        hipLaunchKernelGGL((k_rank_sus<1024, 1024 / 1024>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
+        hipLaunchKernelGGL((k_rank_sus<1024, 1>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
     else if (max_p <= 2048)
         hipLaunchKernelGGL((k_rank_sus<1024, 2>), dim3(t.n_inst), dim3(1024), 0, s, t, gen_off);
     else if (max_p <= kSusSortMax)

@@ -954,53 +954,54 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(
     const int total = const_at(t.tiles, t.n_inst);       // the grid may exceed it (capacity-sized graph)
     const int first = MODE == kTileSplit && (int)blockIdx.x >= total ? 1 : 0;   // the tile's blocks: long, short
     const int end = MODE == kTileSplit ? first + 1 : 2, wg = (int)blockIdx.x - (MODE == kTileSplit ? first * total : 0);
-    if (none_dense(t, parity) | (wg >= total)) return;
+    const bool none = none_dense(t, parity), past = wg >= total;   // one wait for both loads
+    if (none | past) return;
     auto work = [&](const InstDesc &d, int local) {
-    const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
-    const int n_pairs = (n_jb + 1) / 2;
-    const TilePos tp = tile_pos(local, n_pairs, (d.P + B - 1) / B, order);
-    const int jp = tp.jp, pb = tp.pb;
-    // Label -> code tables: every entry set to kCodeNone (B tables of cstride bytes,
-    // one contiguous, 16-byte aligned region; cstride >= N is a multiple of 16). The
-    // column and packed blocks leave their entries set, and the tables are cleared
-    // again between the two blocks of a folded pair (a block's last reads of them
-    // precede the barrier that closes its row loop); the LUT block restores its own
-    // entries.
-    uint8_t *code = lds + mfma_lds_code_off(B, KIND);
-    auto clear_codes = [&]() {
-        const int n16 = B * cstride / 16;
-        for (int i = threadIdx.x; i < n16; i += 256)
-            *(uint4 *)(code + 16 * (size_t)i) = uint4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-    };
-    clear_codes();
-    if constexpr (KIND == kKindLut) lut_table_init(lds);
-    __syncthreads();
-    if constexpr (KIND == kKindPacked) {
-        const MfmaLdsPacked s{(uint16_t *)lds, code, lds + mfma_lds_ring_off(B, cstride, KIND),
-                              (uint32_t *)(lds + mfma_lds_scratch_off(B, cstride, KIND)), cstride};
-        mfma_block_packed<B>(d, n_jb - 1 - jp, pb, parity, s);
-        if (jp != n_jb - 1 - jp) {
-            clear_codes();
-            __syncthreads();
-            mfma_block_packed<B>(d, jp, pb, parity, s);
-        }
-    } else if constexpr (KIND == kKindLut) {
-        mfma_block_lut<B>(d, n_jb - 1 - jp, pb, parity, lds, cstride);
-        if (jp != n_jb - 1 - jp) {
-            __syncthreads();
-            mfma_block_lut<B>(d, jp, pb, parity, lds, cstride);
-        }
-    } else {
-        const MfmaLdsCols s{(uint32_t *)lds, code, cstride};
-        if (!first) mfma_block_cols<B>(d, n_jb - 1 - jp, pb, parity, s);
-        if (end == 2 && jp != n_jb - 1 - jp) {
-            if (!first) {
+        const int n_jb = (d.N + kMfmaCols - 1) / kMfmaCols;
+        const int n_pairs = (n_jb + 1) / 2;
+        const TilePos tp = tile_pos(local, n_pairs, (d.P + B - 1) / B, order);
+        const int jp = tp.jp, pb = tp.pb;
+        // Label -> code tables: every entry set to kCodeNone (B tables of cstride bytes,
+        // one contiguous, 16-byte aligned region; cstride >= N is a multiple of 16). The
+        // column and packed blocks leave their entries set, and the tables are cleared
+        // again between the two blocks of a folded pair (a block's last reads of them
+        // precede the barrier that closes its row loop); the LUT block restores its own
+        // entries.
+        uint8_t *code = lds + mfma_lds_code_off(B, KIND);
+        auto clear_codes = [&]() {
+            const int n16 = B * cstride / 16;
+            for (int i = threadIdx.x; i < n16; i += 256)
+                *(uint4 *)(code + 16 * (size_t)i) = uint4{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+        };
+        clear_codes();
+        if constexpr (KIND == kKindLut) lut_table_init(lds);
+        __syncthreads();
+        if constexpr (KIND == kKindPacked) {
+            const MfmaLdsPacked s{(uint16_t *)lds, code, lds + mfma_lds_ring_off(B, cstride, KIND),
+                                  (uint32_t *)(lds + mfma_lds_scratch_off(B, cstride, KIND)), cstride};
+            mfma_block_packed<B>(d, n_jb - 1 - jp, pb, parity, s);
+            if (jp != n_jb - 1 - jp) {
                 clear_codes();
                 __syncthreads();
+                mfma_block_packed<B>(d, jp, pb, parity, s);
             }
-            mfma_block_cols<B>(d, jp, pb, parity, s);
+        } else if constexpr (KIND == kKindLut) {
+            mfma_block_lut<B>(d, n_jb - 1 - jp, pb, parity, lds, cstride);
+            if (jp != n_jb - 1 - jp) {
+                __syncthreads();
+                mfma_block_lut<B>(d, jp, pb, parity, lds, cstride);
+            }
+        } else {
+            const MfmaLdsCols s{(uint32_t *)lds, code, cstride};
+            if (!first) mfma_block_cols<B>(d, n_jb - 1 - jp, pb, parity, s);
+            if (end == 2 && jp != n_jb - 1 - jp) {
+                if (!first) {
+                    clear_codes();
+                    __syncthreads();
+                }
+                mfma_block_cols<B>(d, jp, pb, parity, s);
+            }
         }
-    }
     };
     if constexpr (MODE == kTileListed) {
         each_listed_tile(t, parity, total, [&](int tile) {
