@@ -910,8 +910,8 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
     }
     const int total = const_at(t.breeds, t.n_inst);
     if (wg >= total) return;                               // the grid may exceed the total (capacity-sized graph)
-    // runs of workgroups of up to 512 children on one XCD: its L2 holds their instance's parents
-    const int run = shape.run, run8 = wg / (kXcds * run), in8 = wg % (kXcds * run);
+    // runs of workgroups on one XCD: its L2 holds their instance's parents
+    const int run = kBreedRun, run8 = wg / (kXcds * run), in8 = wg % (kXcds * run);
     if ((run8 + 1) * kXcds * run <= total) wg = run8 * kXcds * run + in8 % kXcds * run + in8 / kXcds;
     const int k = find_inst(t.breeds, t.n_inst, wg);
     const InstDesc &d = const_at(t.desc, k);
@@ -998,7 +998,7 @@ __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off
 
 // The draws of every launch size, beside the ranking's, fit in LDS for every N the library takes.
 constexpr bool breed_layout_ok() {
-    for (int inds : {1, 4096, 16384, 65536})
+    for (int inds : {1, 4096, 65536})
         if (breed_lds_bytes(PGA_N_MAX, breed_shape(inds)) + sizeof(RankLds) + 16 > (size_t)kMaxLdsBytes) return false;
     return true;
 }

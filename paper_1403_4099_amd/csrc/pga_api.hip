@@ -806,7 +806,7 @@ int pga_evolve(pga_ctx *ctx, const pga_instance *inst, int32_t n_inst, int32_t g
     int32_t *pi = pf + (nb + 1), *pe = pi + (nb + 1), *pb = pe + (nb + 1);
     pf[0] = pi[0] = pe[0] = pb[0] = 0;
     memset(pb + (nb + 1), 0, sizeof(int32_t) * (kListCounters + kTileCounters));     // the lists start empty
-    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0, BreedShape{0, 0, 0}, 0};
+    Shape sh{nb, 0, 0, 0, Variant{form, 0, 0, 0}, 0, 0, 0, route_frac(), 0, 0, BreedShape{0, 0}, 0};
     int total_p = 0;
     for (int k = 0; k < n_inst; ++k) {
         sh.max_n = std::max(sh.max_n, (int)inst[k].N);

@@ -487,10 +487,12 @@ hipError_t launch_eval(Tables t, int total_inds, int blocks, size_t lds, int par
 hipError_t launch_rank(Tables t, int gen_off, int final, hipStream_t s);
 // Shape of a breed launch: the most passes of a slot's lanes over its gene pairs (few in small
 // launches, whose time is a slot's chain of passes; many in large ones, where few lanes per
-// slot keep all of them busy), at least this many slots per workgroup, and the workgroups of a run on one XCD.
+// slot keep all of them busy), and at least this many slots per workgroup of an instance of at most kBreedSmallN stocks.
 struct BreedShape {
-    int passes, min_chr, run;
+    int passes, min_small;
 };
+constexpr int kBreedSmallN = 128;
+constexpr int kBreedRun = 16;    // workgroups of a run on one XCD (8: within 2% everywhere)
 struct BreedSplit {
     int gl, chr;             // lanes per slot, slots per workgroup: powers of two, gl chr >= 256
 };
@@ -498,7 +500,7 @@ __host__ __device__ constexpr BreedSplit breed_split(int N, const BreedShape &b)
     const int npair = (N + 1) / 2;
     int gl = 16;
     while (gl < 256 && gl * b.passes < npair) gl *= 2;
-    const int chr = 256 / gl > b.min_chr ? 256 / gl : b.min_chr;
+    const int chr = N <= kBreedSmallN && 256 / gl < b.min_small ? b.min_small : 256 / gl;
     return BreedSplit{gl, chr};
 }
 // LDS of a breed workgroup of an instance of N stocks: per slot its two parents, whether it crosses, and four
@@ -506,22 +508,27 @@ __host__ __device__ constexpr BreedSplit breed_split(int N, const BreedShape &b)
 __host__ __device__ constexpr size_t breed_bytes(int N, const BreedShape &b) {
     return sizeof(uint32_t) * (size_t)breed_split(N, b).chr * (3 + 4 * (size_t)((N + 127) / 128));
 }
-// The most over N = 1 .. max_n. The slots fall as N rises, the words rise: the largest is at the last N of one of the lane
-// counts, 2 gl passes, or at max_n. (Counted for 2 max_n stocks it was 66 304 bytes, beyond what a workgroup may
-// allocate, at 65 536 slots beside N = 4096; 33 536 are needed.)
+// The most over N = 1 .. max_n. The words rise with N and the slots fall: the largest is at the last N of one of the slot
+// counts, kBreedSmallN or 2 gl passes, or at max_n.
 constexpr size_t breed_lds_bytes(int max_n, const BreedShape &b) {
     size_t most = breed_bytes(max_n, b);
-    for (int gl = 16; gl < 256 && 2 * gl * b.passes < max_n; gl *= 2) {
-        const size_t x = breed_bytes(2 * gl * b.passes, b);
+    auto at = [&](int n) {
+        const size_t x = n < max_n ? breed_bytes(n, b) : 0;
         most = x > most ? x : most;
-    }
+    };
+    at(kBreedSmallN);
+    for (int gl = 16; gl < 256; gl *= 2) at(2 * gl * b.passes);
     return most;
 }
-// (us per generation at 2, 4 and 8 passes: one instance of 4096 slots, N = 1024: 74, 72, 71; ten
-// instances of 1024, N of 64 to 1024: 215, 212, 215; 131 072 slots of N ~ U{32..512}: 576 at 8, 16 and 32)
+// Why the lines lie there (us of a breed launch in the trace). 4096 slots: 2 / 8 passes 6.5 / 9.7 at 1 x 1000 slots of N =
+// 500 and 9.1 / 10.4 at 3 x 1000 of N <= 900, but 15.2 / 13.2 at 4096 slots of N = 1024 and 22 / 17 at 16 000 of N ~
+// U{32..512}. 65 536 slots: 8 / 16 passes 25.4 / 26.7 at 32 768 slots of N ~ U{32..512}, 39.6 / 36.4 at 65 536 and
+// 97.6 / 97.6 at 131 072; 16 / 64 slots a workgroup 14.9 / 11.5 at 66 000 and 26 / 17.6 at 131 000 slots of N <= 32,
+// 36.4 / 32.9 at 131 000 of N = 96, 42.4 / 40.5 at N = 128; past it they lose: 64 / 75 at N = 200, 112 / 129 at
+// N = 300, 161 / 216 at 66 000 of N = 1024, 611 / 1279 of N = 4096. Below 65 536, 16 / 64 slots 6.5 / 8 at 20 000 of
+// N = 18.
 constexpr BreedShape breed_shape(int inds) {
-    if (inds >= 65536) return BreedShape{16, 64, 8};
-    return BreedShape{inds >= 4096 ? 8 : 2, inds >= 16384 ? 8 : 1, 16};
+    return BreedShape{inds >= 65536 ? 16 : inds >= 4096 ? 8 : 2, inds >= 65536 ? 64 : 1};
 }
 inline int breed_blocks(int N, int P, const BreedShape &b) { return ceil_div(P, breed_split(N, b).chr); }
 hipError_t launch_init(Tables t, int blocks, const BreedShape &b, hipStream_t s);
