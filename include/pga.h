@@ -258,11 +258,12 @@ double pga_route_get(void);
  * threads and devices of the process and guarded by a lock.
  *
  * For PGA_FORM_BF16X2 the variants differ also in their kind:
- *   kind 2 (the default kernel): one column per stock; the one-hot B operand
- *     is read from LDS: an 8-bit row mask per (individual, label code, group
- *     of 8 rows), set by LDS atomics when the rows are staged, indexes a
- *     256-entry table of bf16 one-hot octets;
- *   kind 0: one column per stock, the one-hot built in registers;
+ *   kind 0 (the default kernel): one column per stock, the one-hot B operand
+ *     built in registers;
+ *   kind 2: one column per stock; the one-hot is read from LDS: an 8-bit row
+ *     mask per (individual, label code, group of 8 rows), set by LDS atomics
+ *     when the rows are staged, indexes a 256-entry table of bf16 one-hot
+ *     octets;
  *   kind 1 (packed): columns only for the labels with n_s >= 2 of each
  *     individual's 16-stock tiles, packed over the workgroup's individuals
  *     into groups of 16 (fewer MFMAs, more LDS and scalar work; a small extra

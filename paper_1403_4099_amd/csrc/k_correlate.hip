@@ -148,13 +148,14 @@ int gram_tiles(int N) {
     return nt * (nt + 1) / 2;
 }
 
-// Slices per tile for a given N (upper bound) and, with T known, the slices used:
-// as many as keep all workgroups resident at once (one per CU: the LDS of one leaves
-// no room for a second), at most kGMaxSplit, and at least 64 samples per slice. One
-// slice more and a few workgroups start a second round, as long as the first:
-// a correlation call at N = 1307 (66 tiles), T = 2000 takes 151 us with 3 slices,
-// 205 with 4; at T = 295, where slices also end at a quarter of a chunk instead
-// of a whole one, the Gram takes 26 us against 42.
+// Slices per tile for a given N (upper bound) and, with T known, the slices used: as many as keep all workgroups
+// resident at once (one per CU: the LDS of one leaves no room for a second), at most kGMaxSplit, and at least 64
+// samples per slice. One slice more and a few workgroups start a second round, as long as the first: a correlation
+// call at N = 1307 (66 tiles), T = 2000 takes 151 us with 3 slices, 205 with 4; at T = 295, where slices also
+// end at a quarter of a chunk instead of a whole one, the Gram takes 26 us against 42. Above 128 tiles the
+// rule gives one slice whatever the rounds, which is not the best: their number over the slices sets the time there.
+// N = 2048 (136 tiles), T = 4096: 624 us with one slice, 626 / 437 / 488 with two / three / four; N = 2900 (276
+// tiles): 1238, 947 / 861 / 822. At T = 300 a slice's partial tiles cost what it gains: N = 2048 77, 82 / 70 / 81.
 int gram_split_max(int N) {
     const int S = 256 / gram_tiles(N);
     return S < 1 ? 1 : (S > kGMaxSplit ? kGMaxSplit : S);
@@ -403,8 +404,8 @@ __global__ __launch_bounds__(256) void k_corr_finish(const double *part, int N, 
 // through 4 KB of LDS of its own. (Loads in operand order, where neighbouring lanes hold
 // different rows, cost one address per lane: 58 us at N = 18, T = 4096, now 32.) The first
 // kSmAhead steps of a wave stay in registers between the means and the products, so up to
-// T = 512 R is read once; the sums of squares are accumulated in the same order in every tile.
-// The eight partial tiles meet in LDS and are added in wave order.
+// T = 256 R is read once, and twice above (EWMA: always once); the sums of squares are accumulated in the
+// same order in every tile. The eight partial tiles meet in LDS and are added in wave order.
 //   EWMA: x_it = sw_t (R_it - m_t) with m and sw from k_ewma_mean; S is updated in place, and its
 //   old diagonal is read from the copy that k_ewma_mean made (another tile updates it here).
 // What bounds it: the chain of a few dependent memory reads and the L2 reads of 32 rows per tile

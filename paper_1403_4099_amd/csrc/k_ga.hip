@@ -895,8 +895,8 @@ __device__ __forceinline__ void fold_rank(const Tables &t, int k, int parity, in
 //      slot leaves few lanes idle (136 pairs: 9 passes of 16, against 3 of 64).
 // Every draw is keyed by child and gene pair, so a child is the same bits
 // whatever gl and chr are. Large launches are near the memory: 256 instances of
-// N ~ U{32..512} read two parents per child and write it, 430 MB in 133 us (3.2
-// TB/s; 198 us with a wave per slot and all draws in it). (Loading the next
+// N ~ U{32..512} read two parents per child and write it, 430 MB in 95 us (4.5
+// TB/s; 133 us with 64 slots a workgroup, 198 with a wave per slot and all draws in it). (Loading the next
 // pass's genes before the draw: 139 us, and no gain in small launches.)
 __global__ __launch_bounds__(256) void k_breed(Tables t, int parity, int gen_off, int fold, int sus_listed, BreedShape shape) {
     extern __shared__ __align__(16) uint32_t blds[];       // [parent A, B | crosses][chr], words [4 nq][chr]
